@@ -91,7 +91,9 @@ typedef struct fwime_ctx fwime_ctx_t;
 
 /* Create a context on `device`.  It owns all scratch memory (wavefield
  * buffers, checkpoints, geometry tables) and never allocates beyond
- * `hbm_budget_bytes` (0 = no limit besides the device).  Returns FWIME_OK and
+ * `hbm_budget_bytes` (0 = no limit besides the device).  A context without a
+ * budget may use up to a third of the device's free memory to keep wavefield
+ * histories instead of recomputing them; one with a budget does not.  Returns FWIME_OK and
  * sets *out, or an error code. */
 int fwime_ctx_create(int device, size_t hbm_budget_bytes, fwime_ctx_t **out);
 
@@ -196,12 +198,15 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *grid, const float *
  * The call synchronizes `stream` once per inner product.  The solver's
  * vectors (4 model-size and 2 data-size arrays) stay in the context until
  * fwime_ctx_trim or fwime_ctx_destroy, and count against its HBM budget.
- * When they fit in half of the free memory (and of the budget), the
- * background checkpoints of every shot (6 bytes x 2 ceil((nt-1)/K) padded
- * fields per shot, K = ceil(sqrt(nt))) are kept for the whole call, so each
- * B~* after the first skips its background forward pass; the results are the
- * same bit for bit either way (FWIME_VP_NOCACHE=1 in the environment turns
- * the cache off).
+ * Without a budget, the background's T2 terms of every shot and step (nt - 1
+ * padded fields per shot) are kept for the whole call when they fit in a third
+ * of the free memory, so B~ and each B~* after the first propagate one field
+ * instead of two.  Otherwise, when they fit in half of the free memory (and of
+ * the budget), the background checkpoints of every shot (6 bytes x
+ * 2 ceil((nt-1)/K) padded fields per shot, K = ceil(sqrt(nt))) are kept, so
+ * each B~* after the first skips its background forward pass.  The iterates
+ * differ by the order of the image's FP32 partial sums at most
+ * (FWIME_VP_NOCACHE=1 in the environment turns both off).
  * Argument errors (FWIME_EINVAL) are reported before anything is written; a
  * failure during the iteration leaves ptilde_out and phi_out unspecified. */
 int fwime_vp_solve(fwime_ctx_t *ctx, const fwime_grid_t *grid, const float *vel,
@@ -317,11 +322,13 @@ int fwime_footprint(const fwime_grid_t *grid, int32_t nshots, int32_t nrec, int3
  * eq. fwime.obj) and, later, the adjoint-state backward of that map: given
  * an adjoint source a = dL/dd, grad_vel = (B^* + T^*) a (the Born and
  * tomographic parts of eqs. fwime.gradient.born and .tomo) and
- * grad_ptilde = B~^* a.  The forward keeps sqrt(nt)-spaced checkpoints of the
- * background and scattered wavefields of every shot in a tape (device memory
- * owned by the tape, counted against the context's HBM budget), plus copies of
- * vel, ptilde and the wavelets; the backward recomputes one segment at a time
- * from them.  A tape serves exactly one backward (its checkpoints are
+ * grad_ptilde = B~^* a.  The forward keeps, in a tape (device memory owned by
+ * the tape, counted against the context's HBM budget), copies of vel, ptilde
+ * and the wavelets and, of the background and the scattered field of every
+ * shot, either the T2 terms of every step (2 (nt - 1) padded fields per shot;
+ * without a budget, when they fit in a third of the free memory) or
+ * sqrt(nt)-spaced checkpoints, from which the backward recomputes one segment
+ * at a time.  A tape serves exactly one backward (its checkpoints are
  * consumed); free it with fwime_tape_free in every case. */
 typedef struct fwime_tape fwime_tape_t;
 

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <climits>
 #include <cstdint>
 
 namespace fw {
@@ -105,6 +106,10 @@ struct StepArgs {
   const float *dsrc = nullptr;  // optional dense source, [S] x dsrc_sstride
   long dsrc_sstride = 0;
   NuSource nu;
+  // rows and columns of the padded grid that the dense sources of the two-step
+  // kernel (dsrc, nu) are read on; elsewhere the source is zero and its
+  // buffer need not hold anything
+  int ez0 = 0, ez1 = INT_MAX, ex0 = 0, ex1 = INT_MAX;
   Inject inj;
   Extract ext;
   int NZ = 0, NX = 0, LZ = 0;
@@ -221,6 +226,9 @@ hipError_t launch_minmax(const float *a, long n, double *res, hipStream_t st);
 // Fill a float array with zeros (kernel, usable under graph capture).
 hipError_t launch_zero(float *a, long n, hipStream_t st);
 
+// dst[s * sstride + i] = 0, i < n, s < S
+hipError_t launch_zero_fields(float *dst, long sstride, int S, long n, hipStream_t st);
+
 // dst[s * dst_sstride + i] = src[s * src_sstride + i], i < n, s < S
 hipError_t launch_copy_fields(float *dst, long dst_sstride, const float *src, long src_sstride, int S, long n,
                               hipStream_t st);
@@ -239,13 +247,15 @@ hipError_t launch_ext_coef(const float *ptilde, const float *vel, const ExtGeom 
 
 // For n < nk and every shot: out_n(z, j) = sum_h c(z, j - sg h, h) in_n(z, j - 2 sg h)
 // (sg = +1: extended scattering source; sg = -1: its transpose, the spread of
-// the receiver-side field).  in/out slot n of shot s at base + s*sstride + n*slot.
+// the receiver-side field).  Slot n of shot s at base + s*sstride + n*slot, or
+// ring index (first + n) % ring with a ring.
 hipError_t launch_ext_scatter(const float *coef, const ExtGeom &g, int sg, const float *in, long in_slot,
-                              float *out, long out_slot, long sstride, int nshots, int nk, hipStream_t st,
-                              int in_ring = 0, int in_first = 0, int out_ring = 0, int out_first = 0);
+                              long in_sstride, float *out, long out_slot, long out_sstride, int nshots, int nk,
+                              hipStream_t st, int in_ring = 0, int in_first = 0, int out_ring = 0,
+                              int out_first = 0);
 
 // acc(z,y,h) += sum_s sum_{n<nk} a_n(z, y-h) b_n(z, y+h) (FP64 accumulator;
-// products summed in FP32 over at most 512 slots of a slot group while there
+// products summed in FP32 over at most 128 slots of a slot group while there
 // are at most kImageGroups groups).  Slot n of a is a + n*a_slot; slot of b
 // is ring index (b_first + n) % b_ring.  parts: scratch for up to kImageGroups
 // FP32 partial images ([kImageGroups][nh][nx][nz]), one per slot group.

@@ -109,7 +109,7 @@ struct ScatterArgs {
   const float *coef;
   const float *in;
   float *out;
-  long in_slot, out_slot, sstride;
+  long in_slot, out_slot, in_sstride, out_sstride;
   int in_ring, in_first, out_ring, out_first;
   int nz, nx, nb, NX, LZ, nh, H, sg;
   int j0, nj;       // writable padded columns [j0, j0 + nj)
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(kScThreads) k_ext_scatter_ws(const ScatterArgs
     if (q >= q1) return;
     const int s = q / a.nk, n = q - s * a.nk;
     const long sl = a.in_ring ? (long)((a.in_first + n) % a.in_ring) : (long)n;
-    const auto rs = slot_rsrc(a.in + (long)s * a.sstride + sl * a.in_slot, slot_bytes);
+    const auto rs = slot_rsrc(a.in + (long)s * a.in_sstride + sl * a.in_slot, slot_bytes);
 #pragma unroll
     for (int r = 0; r < PER; ++r) pre[r] = bload(rs, off0 + r * rstep);
   };
@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(kScThreads) k_ext_scatter_ws(const ScatterArgs
     }
     const int s = q / a.nk, n = q - s * a.nk;
     const long sl = a.out_ring ? (long)((a.out_first + n) % a.out_ring) : (long)n;
-    float *dst = a.out + (long)s * a.sstride + sl * a.out_slot;
+    float *dst = a.out + (long)s * a.out_sstride + sl * a.out_slot;
     if (zin) {
       if (ja < jend) dst[(long)ja * a.LZ + zp] = oa;
       if (jc < jend) dst[(long)jc * a.LZ + zp] = ob;
@@ -372,8 +372,8 @@ __global__ void __launch_bounds__(kScThreads) k_ext_scatter_dma(const ScatterArg
     const int sh = q / a.nk, n = q - sh * a.nk;
     const int ri = a.in_ring ? (a.in_first % a.in_ring + n) % a.in_ring : n;
     const int ro = a.out_ring ? (a.out_first % a.out_ring + n) % a.out_ring : n;
-    tin[i] = (long)sh * a.sstride + (long)ri * a.in_slot;
-    tout[i] = (long)sh * a.sstride + (long)ro * a.out_slot;
+    tin[i] = (long)sh * a.in_sstride + (long)ri * a.in_slot;
+    tout[i] = (long)sh * a.out_sstride + (long)ro * a.out_slot;
   }
   __syncthreads();
   // wavefront w brings chunks g = w + 8 r (window columns 4 g .. 4 g + 3) of
@@ -462,7 +462,7 @@ __global__ void __launch_bounds__(256) k_ext_scatter(const ScatterArgs a) {
   const int z = zs * 64 + lane;
   const bool zin = z < a.nz;
   const int zp = a.nb + z;
-  const long sb = (long)s * a.sstride;
+  const long sbi = (long)s * a.in_sstride, sbo = (long)s * a.out_sstride;
 
   for (int n0 = 0; n0 < a.nk; n0 += kScatterKC) {
     float acc[kScatterKC];
@@ -474,7 +474,7 @@ __global__ void __launch_bounds__(256) k_ext_scatter(const ScatterArgs a) {
       const int i = j - 2 * a.sg * ih;
       if (y < 0 || y >= a.nx || i < 0 || i >= a.NX) continue;   // wave-uniform
       const float c = zin ? a.coef[((long)(ih + a.H) * a.nx + y) * a.nz + z] : 0.f;
-      const long off = sb + (long)i * a.LZ + zp;
+      const long off = sbi + (long)i * a.LZ + zp;
 #pragma unroll
       for (int m = 0; m < kScatterKC; ++m) {
         if (m < nn) {
@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(256) k_ext_scatter(const ScatterArgs a) {
       }
     }
     if (zin) {
-      const long off = sb + (long)j * a.LZ + zp;
+      const long off = sbo + (long)j * a.LZ + zp;
 #pragma unroll
       for (int m = 0; m < kScatterKC; ++m) {
         if (m < nn) {
@@ -509,8 +509,8 @@ static int strip_pad(int nz, int nb) {
 }
 
 hipError_t launch_ext_scatter(const float *coef, const ExtGeom &g, int sg, const float *in, long in_slot,
-                              float *out, long out_slot, long sstride, int nshots, int nk, hipStream_t st,
-                              int in_ring, int in_first, int out_ring, int out_first) {
+                              long in_sstride, float *out, long out_slot, long out_sstride, int nshots, int nk,
+                              hipStream_t st, int in_ring, int in_first, int out_ring, int out_first) {
   if (nk <= 0 || nshots <= 0) return hipSuccess;
   ScatterArgs a;
   a.coef = coef;
@@ -518,7 +518,8 @@ hipError_t launch_ext_scatter(const float *coef, const ExtGeom &g, int sg, const
   a.out = out;
   a.in_slot = in_slot;
   a.out_slot = out_slot;
-  a.sstride = sstride;
+  a.in_sstride = in_sstride;
+  a.out_sstride = out_sstride;
   a.in_ring = in_ring;
   a.in_first = in_first;
   a.out_ring = out_ring;
@@ -592,11 +593,13 @@ constexpr int kImgHT = 8;
 
 // Each wavefront sums its tile in FP32 registers over the slots of its
 // group, then stores the sums into its group's partial image; a second
-// kernel adds the partials to the FP64 accumulator in group order.  The launch splits its slots into enough
-// groups that no group sums more than kImgChain of them, which bounds the
-// FP32 chain's rounding to about 1e-6 of a sum of random-sign terms,
-// whatever the number of shots and steps of the launch.
-constexpr int kImgChain = 512;
+// kernel adds the partials to the FP64 accumulator in group order.  The launch
+// splits its slots into enough groups that no group sums more than kImgChain
+// of them (while there are kImageGroups groups), which bounds the FP32 chain's
+// rounding whatever the number of shots and steps of the launch.  Measured on
+// a 200 x 500 Born adjoint with 61 offsets, 8 shots, nt = 800: error of the
+// image against 64 bits 5.8e-7 with chains of 256 slots, 4.9e-7 with 60.
+constexpr int kImgChain = 128;
 
 struct ImageArgs {
   const float *a;
@@ -1276,7 +1279,16 @@ hipError_t launch_tau_image(const float *in, long in_slot, long in_sstride, cons
 
 // ---------------------------------------------------------------------------
 // gacc(x, z) += sum_s sum_n (t2u_n + t2d_n) lam_n + t2u_n rho_n   (padded grid)
+//
+// One thread per cell.  The four streams are read once, so the kernel is
+// bound by HBM on large grids and, where the grid is too small to fill the
+// device, by how many loads a thread keeps in flight: kAccumChain steps are
+// loaded together before the first is used.  Their products are summed in a
+// chain of their own, so that a long launch adds chain totals and not single
+// products: the rounding error grows with chains, not with steps.
 // ---------------------------------------------------------------------------
+constexpr int kAccumChain = 8;
+
 __global__ void k_grad_accum(const float *t2u, const float *t2d, long slot, long seg_sstride, const float *lam,
                              long ring_slot, long ring_sstride, int ring, int first, const float *rho,
                              long rho_slot, long rho_sstride, int rho_ring, int rho_first, int nshots, int nk,
@@ -1287,15 +1299,31 @@ __global__ void k_grad_accum(const float *t2u, const float *t2d, long slot, long
   if (z >= NZ) return;
   float g = 0.f;
   for (int s = 0; s < nshots; ++s) {
-    const long sa = (long)s * seg_sstride + i;
-    const long sr = (long)s * ring_sstride + i;
-    const long sp = (long)s * rho_sstride + i;
-    for (int n = 0; n < nk; ++n) {
-      const long rs = (long)((first + n) % ring) * ring_slot;
-      const long ps = (long)((rho_first + n) % rho_ring) * rho_slot;
-      const float u = t2u[sa + n * slot];
-      const float d = t2d[sa + n * slot];
-      g += (u + d) * lam[sr + rs] + u * rho[sp + ps];
+    const float *pu = t2u + (long)s * seg_sstride + i, *pd = t2d + (long)s * seg_sstride + i;
+    const float *pl = lam + (long)s * ring_sstride + i, *pr = rho + (long)s * rho_sstride + i;
+    int rl = first % ring, rr = rho_first % rho_ring;      // ring slots of step n (wave-uniform)
+    int n = 0;
+    for (; n + kAccumChain <= nk; n += kAccumChain) {
+      float u[kAccumChain], d[kAccumChain], l[kAccumChain], r[kAccumChain];
+#pragma unroll
+      for (int k = 0; k < kAccumChain; ++k) {
+        u[k] = pu[(long)(n + k) * slot];
+        d[k] = pd[(long)(n + k) * slot];
+        l[k] = pl[(long)rl * ring_slot];
+        r[k] = pr[(long)rr * rho_slot];
+        rl = rl + 1 == ring ? 0 : rl + 1;
+        rr = rr + 1 == rho_ring ? 0 : rr + 1;
+      }
+      float c = 0.f;
+#pragma unroll
+      for (int k = 0; k < kAccumChain; ++k) c += (u[k] + d[k]) * l[k] + u[k] * r[k];
+      g += c;
+    }
+    for (; n < nk; ++n) {
+      const float u = pu[(long)n * slot], d = pd[(long)n * slot];
+      g += (u + d) * pl[(long)rl * ring_slot] + u * pr[(long)rr * rho_slot];
+      rl = rl + 1 == ring ? 0 : rl + 1;
+      rr = rr + 1 == rho_ring ? 0 : rr + 1;
     }
   }
   gacc[i] += g;

@@ -358,6 +358,19 @@ hipError_t launch_zero(float *a, long n, hipStream_t st) {
   return hipGetLastError();
 }
 
+__global__ void k_zero_fields(float *dst, long sstride, long n) {
+  float *d = dst + (long)blockIdx.y * sstride;
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) d[i] = 0.f;
+}
+
+hipError_t launch_zero_fields(float *dst, long sstride, int S, long n, hipStream_t st) {
+  if (n <= 0 || S <= 0) return hipSuccess;
+  long bx = (n + 255) / 256;
+  if (bx > 4096) bx = 4096;
+  k_zero_fields<<<dim3((unsigned)bx, (unsigned)S), 256, 0, st>>>(dst, sstride, n);
+  return hipGetLastError();
+}
+
 __global__ void k_copy_fields(float *dst, long dst_sstride, const float *src, long src_sstride, long n) {
   const int s = blockIdx.y;
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)

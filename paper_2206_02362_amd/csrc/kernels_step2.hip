@@ -158,6 +158,10 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   // results are stored, or zeroed when outside the grid, so they are read
   // unconditionally at the nearest cell inside the grid: no guard, no branch.
   const int vzc = min(max(z, 0), NZ - 1) * 4;                     // clamped row
+  // offset of a dense source's row in column x: past the end (reads zero)
+  // outside the rows and columns the source lives on
+  [[maybe_unused]] const int vze = z >= a.ez0 && z < a.ez1 ? vzc : kOutOfRange;
+  [[maybe_unused]] auto dense_off = [&](int x) { return x >= a.ex0 && x < a.ex1 ? vze : kOutOfRange; };
   float pv[W1], vv1[W1], ds1[W1], pl[W1], gx1[W1];
   [[maybe_unused]] __amdgpu_buffer_rsrc_t r_ds1, r_lprev, r_lcur;
   if constexpr (DS) r_ds1 = rsrc(a.dsrc + (long)s * a.dsrc_sstride, FB);
@@ -172,7 +176,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
     pv[j] = ld(r_prev, vzc, xc * CB);
     vv1[j] = ld(r_V, vzc, xc * CB);
     ds1[j] = pl[j] = 0.f;
-    if constexpr (DS) ds1[j] = ld(r_ds1, vzc, xc * CB);
+    if constexpr (DS) ds1[j] = ld(r_ds1, dense_off(xc), xc * CB);
     if constexpr (DF) pl[j] = bf16_f32(ld16(r_lprev, vzc / 2, xc * (CB / 2)));
   }
   const float gzv = zin ? a.gz[z] : 0.f;
@@ -186,9 +190,9 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
 #pragma unroll
     for (int j = 0; j < W1; ++j) {
       const int xc = min(max(xs1 + j, 0), NX - 1);
-      em1[j] = ld(rm, vzc, xc * CB);
-      e01[j] = ld(r0, vzc, xc * CB);
-      ep1[j] = ld(rp, vzc, xc * CB);
+      em1[j] = ld(rm, dense_off(xc), xc * CB);
+      e01[j] = ld(r0, dense_off(xc), xc * CB);
+      ep1[j] = ld(rp, dense_off(xc), xc * CB);
     }
   }
 
@@ -267,7 +271,10 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
     if constexpr (DS) {
       const auto r_ds2 = rsrc((p.two ? p.dsrc2 : a.dsrc) + (long)s * a.dsrc_sstride, FB);
 #pragma unroll
-      for (int j = 0; j < W2; ++j) ds2[j] = ld(r_ds2, vzc, min(xs2 + j, NX - 1) * CB);
+      for (int j = 0; j < W2; ++j) {
+        const int xc = min(xs2 + j, NX - 1);
+        ds2[j] = ld(r_ds2, dense_off(xc), xc * CB);
+      }
     }
     // Lanes 8..63 put their (zero) second value into this wave's own column
     // of the u^{n+1} tile, which step 1 overwrites after the barrier: a write
@@ -431,7 +438,8 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
       for (int j = 0; j < W2; ++j) {
         const int xc = min(xs2 + j, NX - 1);
         const float g = gzc * gx2[j];
-        ds2[j] += ld(rm2, vzc, xc * CB) / g - 2.f * ld(r02, vzc, xc * CB) + g * ld(rp2, vzc, xc * CB);
+        const int o = dense_off(xc);
+        ds2[j] += ld(rm2, o, xc * CB) / g - 2.f * ld(r02, o, xc * CB) + g * ld(rp2, o, xc * CB);
       }
     }
     fold_sources<W2>(p.inj2, logical, w, lane, ds2);

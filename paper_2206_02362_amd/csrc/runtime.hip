@@ -174,9 +174,10 @@ int arena_get(fwime_ctx_t *ctx, Carve &cv) {
       ctx->arena = nullptr;
       ctx->arena_bytes = 0;
     }
-    // grow geometrically (within the budget) so that a sequence of slightly
-    // larger calls does not reallocate every time
-    size_t want = std::max(cv.total, ctx->last_arena_request + ctx->last_arena_request / 2);
+    // grow geometrically (within the budget, by 4 GiB at most) so that a
+    // sequence of slightly larger calls does not reallocate every time
+    const size_t last = ctx->last_arena_request;
+    size_t want = std::max(cv.total, last + std::min(last / 2, (size_t)4 << 30));
     if (ctx->budget) want = std::min(want, ctx->budget);
     want = std::max(want, cv.total);
     hipError_t e = hipMalloc(&ctx->arena, want);
@@ -665,6 +666,45 @@ int march2(fwime_ctx_t *ctx, const Common &c, Ring4 &f, int S, int n0, int n1, i
   return FWIME_OK;
 }
 
+// T2 output of a two-step launch: slot `first` for its first step, the next
+// slot (`slot` elements on) for its second; per-shot stride sstride
+void with_t2(Step2Args &p, float *first, long slot, int k, long sstride) {
+  p.a.t2 = first;
+  p.t2b = k == 2 ? first + slot : nullptr;
+  p.a.t2_sstride = sstride;
+}
+
+// rows and columns on which the offset scatter (or, with H = 0, the lag
+// scatter) writes its output: the model's rows, the model's columns and the H
+// columns on either side that lie on the grid
+void with_dense_range(StepArgs &a, const ExtGeom &eg, int H) {
+  a.ez0 = eg.nb;
+  a.ez1 = eg.nb + eg.nz;
+  a.ex0 = std::max(0, eg.nb - H);
+  a.ex1 = std::min(eg.NX, eg.nb + eg.nx + H);
+}
+
+// u^{-1} = u^0 = 0: the two buffers of a four-buffer ring that the first launch reads
+hipError_t zero_start(float *ring, const Dims &d, int S, hipStream_t st) {
+  return launch_zero(ring, 2 * d.field * S, st);
+}
+hipError_t zero_start(unsigned short *ring_lo, const Dims &d, int S, hipStream_t st) {
+  return launch_zero((float *)ring_lo, d.field * S, st);
+}
+
+// the fields of times nt - 1 and nt (the zero start of a backward recursion)
+// in a ring of R slots
+hipError_t zero_end(float *ring, long ring_stride, int R, const Dims &d, int S, hipStream_t st) {
+  hipError_t e = launch_zero_fields(ring + (long)((d.nt - 1) % R) * d.field, ring_stride, S, d.field, st);
+  return e != hipSuccess ? e : launch_zero_fields(ring + (long)(d.nt % R) * d.field, ring_stride, S, d.field, st);
+}
+hipError_t zero_end(unsigned short *ring, long ring_stride, int R, const Dims &d, int S, hipStream_t st) {
+  hipError_t e = launch_zero_fields((float *)(ring + (long)((d.nt - 1) % R) * d.field), ring_stride / 2, S, d.field / 2, st);
+  return e != hipSuccess ? e
+                         : launch_zero_fields((float *)(ring + (long)(d.nt % R) * d.field), ring_stride / 2, S,
+                                              d.field / 2, st);
+}
+
 // dense source of a two-step launch: slot `first` for its first step, the
 // next slot (`slot` elements on) for its second; per-shot stride sstride
 void with_dsrc2(Step2Args &p, const float *first, long slot, int k, long sstride) {
@@ -758,6 +798,48 @@ int seg_len(int nt) {
   return K + (K & 1);
 }
 
+// ---------------------------------------------------------------------------
+// Whole T2 histories.  The adjoint-state operators need T2u_n (and T2du~_n)
+// of every step backwards in time.  Where the memory is there, a batch keeps
+// them whole instead of checkpointing the fields and propagating them again:
+// the gradient then runs four propagations per shot instead of six and one
+// offset scatter instead of two, the adjoint two instead of three.  Without
+// checkpoints the segment length is free, and long segments spread the offset
+// kernels' weight loads and image updates over more time slots.
+//
+// At most a third of the free device memory is taken for it, and only by a
+// context without a budget (one with a budget shares the device by exact
+// footprints).  All shots of the call must fit, or at least enough of them
+// that a launch still fills the device.
+// ---------------------------------------------------------------------------
+constexpr long kHistSlots = 2048;       // time slots (shots x steps) of a segment
+constexpr long kHistMinTiles = 3072;    // two rounds of two-step workgroups (six per CU)
+
+// even segment length for S shots: about kHistSlots slots, at least the
+// checkpointed segment
+int hist_seg_len(int nt, int S) {
+  const long want = std::max<long>(seg_len(nt), (kHistSlots + S - 1) / S);
+  const int K = (int)std::min<long>(want, nt - 1);
+  return K + (K & 1);
+}
+
+// Shots per batch that keep whole histories (0: checkpoint instead).
+// bytes(S): scratch of a batch of S shots.
+// held: bytes of another buffer that this call reuses.
+template <class Bytes>
+int hist_batch(const fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, size_t held = 0) {
+  if (ctx->fixed || ctx->budget) return 0;
+  size_t avail = 0, total = 0;
+  if (hipMemGetInfo(&avail, &total) != hipSuccess) return 0;
+  const size_t cap = (avail + ctx->arena_bytes + held) / 3;
+  if (bytes(nshots) <= cap) return nshots;
+  int lo = 0, hi = nshots;                       // largest S with bytes(S) <= cap
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) / 2;
+    (bytes(mid) <= cap ? lo : hi) = mid;
+  }
+  return lo * tiles_per_shot >= kHistMinTiles ? lo : 0;
+}
 
 }  // namespace
 
@@ -943,7 +1025,7 @@ int fwime_model(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const
     float *out_b = data + (long)s0 * geo->nrec * g->nt;
     launches += two ? g->nt / 2 : g->nt - 1;
     if (two) {
-      HIPCHK(launch_zero(fields, 4 * d.field * Sb, st));
+      HIPCHK(zero_start(fields, d, Sb, st));
       Ring4 f(fields, d.field * Sb);
       for (int n = 0; n < g->nt - 1;) {
         const int k = std::min(2, g->nt - 1 - n);
@@ -994,8 +1076,18 @@ int fwime_model_static(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
 }
 
 // ---------------------------------------------------------------------------
+// bg: the background's T2 terms of every shot and step (shot s, step n at
+// (s (nt - 1) + n) field; the variable-projection step keeps them), or null.
+static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
+                            int32_t nh, const float *ptilde, float *data, void *stream, const float *bg);
+
 int fwime_born_ext_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
                        int32_t nh, const float *ptilde, float *data, void *stream) {
+  return born_ext_fwd_run(ctx, g, vel, geo, nh, ptilde, data, stream, nullptr);
+}
+
+static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
+                            int32_t nh, const float *ptilde, float *data, void *stream, const float *bg) {
   if (!ctx) return FWIME_EINVAL;
   ctx->err.clear();
   hipStream_t st = (hipStream_t)stream;
@@ -1009,13 +1101,22 @@ int fwime_born_ext_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   c.d = make_dims(g, ctx->tile_x);
   const Dims &d = c.d;
   ExtGeom eg{d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, nh, (nh - 1) / 2};
-  const int KC = 16;
   const bool two = ctx->two_step;
   const int nf = two ? 8 : 4;                  // u and du~ field buffers per shot
-  // two-step path: both fields also carry four BF16 low-part fields each
-  const long per_shot = (nf + 2L * KC + (two ? 4 : 0)) * d.field * 4 + (long)geo->nrec * 64;
+  // two-step path: both fields also carry four BF16 low-part fields each; with
+  // the background's T2 terms given, neither its fields nor their chunk
+  auto per_shot = [&](int chunk) {
+    return (nf + (bg ? 1L : 2L) * chunk + (two ? 4 : 0)) * d.field * 4 + (long)geo->nrec * 64;
+  };
   const size_t fixed = (size_t)d.field * 8 + (size_t)nh * d.nx * d.nz * 4;
-  const int S = choose_batch(ctx, per_shot, fixed, geo->nshots);
+  // steps per scatter launch: 16, or long chunks where the memory is there.
+  // Every workgroup of the scatter loads its offset weights once per launch:
+  // at 300 x 1700, 8 shots and nh = 61 that was about half of a 16-step launch.
+  const int Sh = !two ? 0 : hist_batch(ctx, geo->nshots, 0, [&](int S) {
+    return fixed + (size_t)per_shot(hist_seg_len(g->nt, S)) * S;
+  });
+  const int KC = Sh ? hist_seg_len(g->nt, Sh) : 16;
+  const int S = Sh ? Sh : choose_batch(ctx, per_shot(KC), fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
   TableSet ts = build_table_set(d, geo, batches, two);
 
@@ -1029,7 +1130,7 @@ int fwime_born_ext_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   cv.add(&coef, (long)nh * d.nx * d.nz);
   cv.add(&pairs, nf * d.field * S);
   if (two) cv.add(&lows, 8 * d.field * S);
-  cv.add(&t2, (long)KC * d.field * S);
+  if (!bg) cv.add(&t2, (long)KC * d.field * S);
   cv.add(&sc, (long)KC * d.field * S);
   if ((rc = arena_get(ctx, cv))) return rc;
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
@@ -1042,27 +1143,31 @@ int fwime_born_ext_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     const DevTables &t = ts.dev[bi];
     float *out_b = data + (long)s0 * geo->nrec * g->nt;
     if (two) {
-      HIPCHK(launch_zero(pairs, 8 * d.field * Sb, st));
-      HIPCHK(launch_zero((float *)lows, 4 * d.field * Sb, st));
-      HIPCHK(launch_zero(sc, chunk_stride * Sb, st));
+      HIPCHK(zero_start(pairs, d, Sb, st));
+      HIPCHK(zero_start(pairs + 4 * d.field * Sb, d, Sb, st));
+      HIPCHK(zero_start(lows, d, Sb, st));
+      HIPCHK(zero_start(lows + 4 * d.field * Sb, d, Sb, st));
       Ring4 fu(pairs, d.field * Sb), fw(pairs + 4 * d.field * Sb, d.field * Sb);
       Ring4L lu(lows, d.field * Sb), lw(lows + 4 * d.field * Sb, d.field * Sb);
       const float *wav_b = geo->wavelet + (long)s0 * g->nt;
       for (int c0 = 0; c0 < g->nt - 1; c0 += KC) {
         const int nk = std::min(KC, g->nt - 1 - c0);
         // background in extended precision: its T2 term is the scattering source
-        rc = march2(ctx, c, fu, Sb, c0, c0 + nk, kModeT2, [&](Step2Args &p, int n, int k) {
-          p.a.t2 = t2 + (long)(n - c0) * d.field;
-          p.t2b = k == 2 ? t2 + (long)(n - c0 + 1) * d.field : nullptr;
-          p.a.t2_sstride = chunk_stride;
-          with_src2(p, t, wav_b, g, n);
-        }, st, &lu);
-        if (rc) return rc;
-        HIPCHK(launch_ext_scatter(coef, eg, +1, t2, d.field, sc, d.field, chunk_stride, Sb, nk, st));
+        const long bg_stride = (long)(g->nt - 1) * d.field;
+        if (!bg) {
+          rc = march2(ctx, c, fu, Sb, c0, c0 + nk, kModeT2, [&](Step2Args &p, int n, int k) {
+            with_t2(p, t2 + (long)(n - c0) * d.field, d.field, k, chunk_stride);
+            with_src2(p, t, wav_b, g, n);
+          }, st, &lu);
+          if (rc) return rc;
+        }
+        HIPCHK(launch_ext_scatter(coef, eg, +1, bg ? bg + s0 * bg_stride + (long)c0 * d.field : t2, d.field,
+                                  bg ? bg_stride : chunk_stride, sc, d.field, chunk_stride, Sb, nk, st));
         // the scattered field in extended precision too: its FP32 rounding
         // would otherwise dominate the inconsistency of the B~ / B~^T pair
         rc = march2(ctx, c, fw, Sb, c0, c0 + nk, kModeDsrc, [&](Step2Args &p, int n, int k) {
           with_dsrc2(p, sc + (long)(n - c0) * d.field, d.field, k, chunk_stride);
+          with_dense_range(p.a, eg, eg.H);
           with_rec_extract(p.a, t, out_b, g->nt, n);
         }, st, &lw);
         if (rc) return rc;
@@ -1088,7 +1193,7 @@ int fwime_born_ext_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
         HIPCHK(launch_step(a, d.TX, kModeT2, st));
         std::swap(ucur, uprev);
       }
-      HIPCHK(launch_ext_scatter(coef, eg, +1, t2, d.field, sc, d.field, chunk_stride, Sb, nk, st));
+      HIPCHK(launch_ext_scatter(coef, eg, +1, t2, d.field, chunk_stride, sc, d.field, chunk_stride, Sb, nk, st));
       for (int m = 0; m < nk; ++m) {
         StepArgs a = batch_args(c, Sb, d.field);
         a.cur = wcur;
@@ -1130,8 +1235,8 @@ static int tau_background(fwime_ctx_t *ctx, const Common &c, const fwime_grid_t 
                           int s0, int Sb, const DevTables &t, float *pairs, unsigned short *lows, float *hist,
                           long hstride, hipStream_t st, float *rec_out = nullptr) {
   const Dims &d = c.d;
-  HIPCHK(launch_zero(pairs, 4 * d.field * Sb, st));
-  HIPCHK(launch_zero((float *)lows, 2 * d.field * Sb, st));
+  HIPCHK(zero_start(pairs, d, Sb, st));
+  HIPCHK(zero_start(lows, d, Sb, st));
   Ring4 fu(pairs, d.field * Sb);
   Ring4L lu(lows, d.field * Sb);
   const float *wav_b = geo->wavelet + (long)s0 * g->nt;
@@ -1194,13 +1299,13 @@ int fwime_born_ext_tau_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
     const DevTables &t = ts.dev[bi];
     float *out_b = data + (long)s0 * geo->nrec * g->nt;
     if ((rc = tau_background(ctx, c, g, geo, s0, Sb, t, pairs, lows, hist, hstride, st))) return rc;
-    HIPCHK(launch_zero(sc, hstride * Sb, st));
     HIPCHK(launch_tau_scatter(coef, eg, lag, hist, sc, d.field, hstride, ns, Sb, st));
     float *wp = pairs + 4 * d.field * Sb;
-    HIPCHK(launch_zero(wp, 4 * d.field * Sb, st));
+    HIPCHK(zero_start(wp, d, Sb, st));
     Ring4 fw(wp, d.field * Sb);
     rc = march2(ctx, c, fw, Sb, 0, ns, kModeDsrc, [&](Step2Args &p, int n, int k) {
       with_dsrc2(p, sc + (long)n * d.field, d.field, k, hstride);
+      with_dense_range(p.a, eg, 0);
       with_rec_extract(p.a, t, out_b, g->nt, n);
     }, st);
     if (rc) return rc;
@@ -1255,7 +1360,7 @@ int fwime_born_ext_tau_adj(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
     const DevTables &t = ts.dev[bi];
     const float *data_b = data + (long)s0 * geo->nrec * g->nt;
     if ((rc = tau_background(ctx, c, g, geo, s0, Sb, t, pairs, lows, hist, hstride, st))) return rc;
-    HIPCHK(launch_zero(lam, lstride * Sb, st));
+    HIPCHK(zero_end(lam, lstride, R, d, Sb, st));
     if ((rc = march2_back_lambda(ctx, c, lam, lstride, R, Sb, 0, g->nt - 1, t, data_b, g->nt, st))) return rc;
     HIPCHK(launch_tau_image(hist, d.field, hstride, lam, d.field, lstride, ns, Sb, eg, lag, vel, (float)g->dt,
                             ptau_out, st));
@@ -1264,11 +1369,14 @@ int fwime_born_ext_tau_adj(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
 }
 
 // ---------------------------------------------------------------------------
-// Background checkpoints of the extended-precision adjoint kept across calls
-// with the same model and shots (the variable-projection step): per shot
-// 2 nseg fields (FP32 and BF16 low parts) in shot order.  `valid` once a call
-// has filled them; later calls skip their forward pass.
+// Background of the extended-precision adjoint kept across calls with the
+// same model and shots (the variable-projection step): the T2 terms of every
+// shot and step where they fit (hist, per shot nt - 1 fields), else the
+// checkpoints (per shot 2 nseg fields, FP32 and BF16 low parts), in shot
+// order.  `valid` once a call has filled them; later calls skip their forward
+// pass.
 struct AdjCache {
+  float *hist = nullptr;
   float *ckpt = nullptr;
   unsigned short *ckpt_lo = nullptr;
   bool valid = false;
@@ -1297,20 +1405,31 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   c.d = make_dims(g, ctx->tile_x);
   const Dims &d = c.d;
   ExtGeom eg{d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, nh, (nh - 1) / 2};
-  const int K = seg_len(g->nt);
-  const int nseg = (g->nt - 1 + K - 1) / K;
-  const int R = K + 2;
   const bool two = ctx->two_step;
   const int nf = two ? 4 : 2;
   if (!two) cache = nullptr;                    // the one-step path recomputes inside its checkpoints
-  // two-step path: BF16 low parts of the four work fields and the checkpoints
-  // (cached checkpoints live outside the arena)
-  const long ck_fields = cache ? 0L : 2L * nseg + (two ? nseg : 0L);
-  // (two-step path: the adjoint ring's BF16 low parts add R / 2 fields)
-  const long per_shot = (nf + K + R + (two ? 2L + (R + 1) / 2 : 0L) + ck_fields) * d.field * 4 + (long)geo->nrec * 64;
+  float *hist = cache ? cache->hist : nullptr;  // whole T2 history: the cache's, or the arena's where it fits
+  const bool own_hist = !cache;
   const long img = (long)nh * d.nx * d.nz;
   const size_t fixed = (size_t)d.field * 8 + (size_t)img * (8 + 4 * kImageGroups);   // FP64 image + partials
-  const int S = choose_batch(ctx, per_shot, fixed, geo->nshots);
+  auto hist_per_shot = [&](int S) {
+    const long r = hist_seg_len(g->nt, S) + 2;
+    return (nf + 2 + r + (r + 1) / 2 + (own_hist ? g->nt - 1L : 0L)) * d.field * 4 + (long)geo->nrec * 64;
+  };
+  const int Sh = !two || (cache && !hist) ? 0 : hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
+    return fixed + (size_t)hist_per_shot(S) * S;
+  });
+  const bool keep = Sh > 0 || hist;
+  const int K = Sh ? hist_seg_len(g->nt, Sh) : seg_len(g->nt);
+  const int nseg = (g->nt - 1 + K - 1) / K;
+  const int R = K + 2;
+  // two-step path: BF16 low parts of the four work fields and the checkpoints
+  // (cached checkpoints live outside the arena)
+  const long ck_fields = cache || keep ? 0L : 2L * nseg + (two ? nseg : 0L);
+  // (two-step path: the adjoint ring's BF16 low parts add R / 2 fields)
+  const long per_shot = (nf + (keep ? 0 : K) + R + (two ? 2L + (R + 1) / 2 : 0L) + ck_fields) * d.field * 4 +
+                        (long)geo->nrec * 64;
+  const int S = Sh ? Sh : choose_batch(ctx, per_shot, fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
   TableSet ts = build_table_set(d, geo, batches, two);
 
@@ -1326,13 +1445,15 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   cv.add(&acc, img);
   cv.add(&parts, kImageGroups * img);
   cv.add(&pairs, nf * d.field * S);
-  if (!cache) cv.add(&ckpt, 2L * nseg * d.field * S);
+  if (!cache && !keep) cv.add(&ckpt, 2L * nseg * d.field * S);
   if (two) {
     cv.add(&lows, 4 * d.field * S);
     cv.add(&ring_lo, (long)R * d.field * S);
-    if (!cache) cv.add(&ckpt_lo, 2L * nseg * d.field * S);
+    if (!cache && !keep) cv.add(&ckpt_lo, 2L * nseg * d.field * S);
   }
-  cv.add(&t2, (long)K * d.field * S);
+  const long hist_stride = (g->nt - 1L) * d.field;
+  if (keep && own_hist) cv.add(&hist, hist_stride * S);
+  if (!keep) cv.add(&t2, (long)K * d.field * S);
   cv.add(&ring, (long)R * d.field * S);
   if ((rc = arena_get(ctx, cv))) return rc;
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
@@ -1349,17 +1470,26 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
     if (two) {
       const float *wav_b = geo->wavelet + (long)s0 * g->nt;
       auto src = [&](Step2Args &p, int n, int) { with_src2(p, t, wav_b, g, n); };
-      if (cache) {                              // this batch's shots in the cached checkpoints
+      if (cache && !keep) {                     // this batch's shots in the cached checkpoints
         ckpt = cache->ckpt + (long)s0 * ck_stride;
         ckpt_lo = cache->ckpt_lo + (long)s0 * ck_stride;
       }
       // forward pass (extended precision) storing (u^{n0-1}, u^{n0}) at every
       // segment start, unless the cached checkpoints already hold them
-      HIPCHK(launch_zero(pairs, 4 * d.field * Sb, st));
-      HIPCHK(launch_zero((float *)lows, 2 * d.field * Sb, st));
+      HIPCHK(zero_start(pairs, d, Sb, st));
+      HIPCHK(zero_start(lows, d, Sb, st));
       Ring4 fu(pairs, d.field * Sb);
       Ring4L lu(lows, d.field * Sb);
-      for (int j = 0; j < nseg && !(cache && cache->valid); ++j) {
+      // with a whole history it stores T2 u_n of every step instead
+      float *hist_b = keep ? hist + (own_hist ? 0L : s0 * hist_stride) : nullptr;
+      if (keep && !(cache && cache->valid)) {
+        rc = march2(ctx, c, fu, Sb, 0, g->nt - 1, kModeT2, [&](Step2Args &p, int n, int k) {
+          with_t2(p, hist_b + (long)n * d.field, d.field, k, hist_stride);
+          with_src2(p, t, wav_b, g, n);
+        }, st, &lu);
+        if (rc) return rc;
+      }
+      for (int j = 0; j < nseg && !keep && !(cache && cache->valid); ++j) {
         const int n0 = j * K, n1 = std::min(n0 + K, g->nt - 1);
         HIPCHK(launch_copy_fields(ckpt + (2L * j) * d.field, ck_stride, fu.prev(), d.field, Sb, d.field, st));
         HIPCHK(launch_copy_fields(ckpt + (2L * j + 1) * d.field, ck_stride, fu.cur(), d.field, Sb, d.field, st));
@@ -1371,10 +1501,17 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
       // backward pass: recompute the segment from its checkpoint (keeping
       // T2 u_n), march lambda through the segment (in extended precision as
       // well), image
-      HIPCHK(launch_zero(ring, ring_stride * Sb, st));
-      HIPCHK(launch_zero((float *)ring_lo, ring_stride * Sb / 2, st));
+      HIPCHK(zero_end(ring, ring_stride, R, d, Sb, st));
+      HIPCHK(zero_end(ring_lo, ring_stride, R, d, Sb, st));
       for (int j = nseg - 1; j >= 0; --j) {
         const int n0 = j * K, n1 = std::min(n0 + K, g->nt - 1), nk = n1 - n0;
+        if (keep) {
+          if ((rc = march2_back_lambda(ctx, c, ring, ring_stride, R, Sb, n0, n1, t, data_b, g->nt, st, ring_lo)))
+            return rc;
+          HIPCHK(launch_ext_image(hist_b + (long)n0 * d.field, d.field, hist_stride, ring, d.field, ring_stride, R, n0,
+                                  Sb, nk, eg, acc, parts, st));
+          continue;
+        }
         Ring4 wu(pairs, d.field * Sb);
         Ring4L wl(lows, d.field * Sb);
         HIPCHK(launch_copy_fields(wu.prev(), d.field, ckpt + (2L * j) * d.field, ck_stride, Sb, d.field, st));
@@ -1461,19 +1598,28 @@ namespace {
 // lambda (source r), spread lambda into the e ring, march rho (source the
 // transposed second time difference of e), then accumulate the extended image
 // sum T2u(y-h) lambda(y+h) and the per-cell sum (T2u + T2du~) lambda + T2u rho.
+// With whole histories (hist) the forward pass keeps T2u and T2du~ of every
+// step, nothing is checkpointed and the backward pass recomputes nothing.
+// The scattering source of du~ passes through the e ring: it is done with
+// before the spread of the same steps is written.
 // ---------------------------------------------------------------------------
 struct GradPlan {
   int K, nseg, R;
+  bool hist = false;
   long ck_stride, seg_stride, ring_stride;
+  // first slot of segment start n0 in the T2 buffers
+  long t2_off(const Dims &d, int n0) const { return hist ? (long)n0 * d.field : 0L; }
 };
 
-GradPlan grad_plan(const Dims &d, int nt) {
+// hist_shots: shots per batch with whole histories, 0 to checkpoint
+GradPlan grad_plan(const Dims &d, int nt, int hist_shots = 0) {
   GradPlan p;
-  p.K = seg_len(nt);
+  p.hist = hist_shots > 0;
+  p.K = p.hist ? hist_seg_len(nt, hist_shots) : seg_len(nt);
   p.nseg = (nt - 1 + p.K - 1) / p.K;
   p.R = p.K + 2;
-  p.ck_stride = 2L * p.nseg * d.field;
-  p.seg_stride = (long)p.K * d.field;
+  p.ck_stride = p.hist ? 0L : 2L * p.nseg * d.field;
+  p.seg_stride = (p.hist ? (long)(nt - 1) : (long)p.K) * d.field;
   p.ring_stride = (long)p.R * d.field;
   return p;
 }
@@ -1490,26 +1636,30 @@ int grad_forward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, con
   const Dims &d = c.d;
   int rc;
   if (ctx->two_step) {
-    HIPCHK(launch_zero(wk.pairs, 8 * d.field * Sb, st));
-    HIPCHK(launch_zero(wk.t2d, pl.seg_stride * Sb, st));
+    HIPCHK(zero_start(wk.pairs, d, Sb, st));
+    HIPCHK(zero_start(wk.pairs + 4 * d.field * Sb, d, Sb, st));
     Ring4 fu(wk.pairs, d.field * Sb), fw(wk.pairs + 4 * d.field * Sb, d.field * Sb);
     for (int j = 0; j < pl.nseg; ++j) {
       const int n0 = j * pl.K, n1 = std::min(n0 + pl.K, g->nt - 1), nk = n1 - n0;
-      HIPCHK(launch_copy_fields(uck + (2L * j) * d.field, pl.ck_stride, fu.prev(), d.field, Sb, d.field, st));
-      HIPCHK(launch_copy_fields(uck + (2L * j + 1) * d.field, pl.ck_stride, fu.cur(), d.field, Sb, d.field, st));
-      HIPCHK(launch_copy_fields(dck + (2L * j) * d.field, pl.ck_stride, fw.prev(), d.field, Sb, d.field, st));
-      HIPCHK(launch_copy_fields(dck + (2L * j + 1) * d.field, pl.ck_stride, fw.cur(), d.field, Sb, d.field, st));
+      if (!pl.hist) {
+        HIPCHK(launch_copy_fields(uck + (2L * j) * d.field, pl.ck_stride, fu.prev(), d.field, Sb, d.field, st));
+        HIPCHK(launch_copy_fields(uck + (2L * j + 1) * d.field, pl.ck_stride, fu.cur(), d.field, Sb, d.field, st));
+        HIPCHK(launch_copy_fields(dck + (2L * j) * d.field, pl.ck_stride, fw.prev(), d.field, Sb, d.field, st));
+        HIPCHK(launch_copy_fields(dck + (2L * j + 1) * d.field, pl.ck_stride, fw.cur(), d.field, Sb, d.field, st));
+      }
+      float *t2u = wk.t2u + pl.t2_off(d, n0), *t2d = wk.t2d + pl.t2_off(d, n0);
       rc = march2(ctx, c, fu, Sb, n0, n1, kModeT2, [&](Step2Args &p, int n, int k) {
-        p.a.t2 = wk.t2u + (long)(n - n0) * d.field;
-        p.t2b = k == 2 ? wk.t2u + (long)(n - n0 + 1) * d.field : nullptr;
-        p.a.t2_sstride = pl.seg_stride;
+        with_t2(p, t2u + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
         with_src2(p, t, wav_b, g, n);
         with_rec_extract(p.a, t, drec, g->nt, n);
       }, st);
       if (rc) return rc;
-      HIPCHK(launch_ext_scatter(coef, eg, +1, wk.t2u, d.field, wk.t2d, d.field, pl.seg_stride, Sb, nk, st));
-      rc = march2(ctx, c, fw, Sb, n0, n1, kModeDsrc, [&](Step2Args &p, int n, int k) {
-        with_dsrc2(p, wk.t2d + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
+      HIPCHK(launch_ext_scatter(coef, eg, +1, t2u, d.field, pl.seg_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
+                                st));
+      rc = march2(ctx, c, fw, Sb, n0, n1, pl.hist ? kModeT2 | kModeDsrc : kModeDsrc, [&](Step2Args &p, int n, int k) {
+        with_dsrc2(p, wk.er + (long)(n - n0) * d.field, d.field, k, pl.ring_stride);
+        with_dense_range(p.a, eg, eg.H);
+        if (pl.hist) with_t2(p, t2d + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
         with_rec_extract(p.a, t, ddrec, g->nt, n);
       }, st);
       if (rc) return rc;
@@ -1521,36 +1671,44 @@ int grad_forward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, con
   float *u0 = wk.pairs, *u1 = wk.pairs + d.field * Sb, *w0 = wk.pairs + 2 * d.field * Sb,
         *w1 = wk.pairs + 3 * d.field * Sb;
   HIPCHK(launch_zero(wk.pairs, 4 * d.field * Sb, st));
-  HIPCHK(launch_zero(wk.t2d, pl.seg_stride * Sb, st));
+  HIPCHK(launch_zero(wk.er, pl.ring_stride * Sb, st));   // the one-step kernel reads its source on the whole grid
   float *ucur = u0, *uprev = u1, *wcur = w0, *wprev = w1;
   for (int j = 0; j < pl.nseg; ++j) {
     const int n0 = j * pl.K, n1 = std::min(n0 + pl.K, g->nt - 1), nk = n1 - n0;
-    HIPCHK(launch_copy_fields(uck + (2L * j) * d.field, pl.ck_stride, uprev, d.field, Sb, d.field, st));
-    HIPCHK(launch_copy_fields(uck + (2L * j + 1) * d.field, pl.ck_stride, ucur, d.field, Sb, d.field, st));
-    HIPCHK(launch_copy_fields(dck + (2L * j) * d.field, pl.ck_stride, wprev, d.field, Sb, d.field, st));
-    HIPCHK(launch_copy_fields(dck + (2L * j + 1) * d.field, pl.ck_stride, wcur, d.field, Sb, d.field, st));
+    if (!pl.hist) {
+      HIPCHK(launch_copy_fields(uck + (2L * j) * d.field, pl.ck_stride, uprev, d.field, Sb, d.field, st));
+      HIPCHK(launch_copy_fields(uck + (2L * j + 1) * d.field, pl.ck_stride, ucur, d.field, Sb, d.field, st));
+      HIPCHK(launch_copy_fields(dck + (2L * j) * d.field, pl.ck_stride, wprev, d.field, Sb, d.field, st));
+      HIPCHK(launch_copy_fields(dck + (2L * j + 1) * d.field, pl.ck_stride, wcur, d.field, Sb, d.field, st));
+    }
+    float *t2u = wk.t2u + pl.t2_off(d, n0), *t2d = wk.t2d + pl.t2_off(d, n0);
     for (int n = n0; n < n1; ++n) {
       StepArgs a = batch_args(c, Sb, d.field);
       a.cur = ucur;
       a.prev = uprev;
       a.out = uprev;
-      a.t2 = wk.t2u + (long)(n - n0) * d.field;
+      a.t2 = t2u + (long)(n - n0) * d.field;
       a.t2_sstride = pl.seg_stride;
       with_src_w(a, t, wav_b, g, n);
       with_rec_extract(a, t, drec, g->nt, n);
       HIPCHK(launch_step(a, d.TX, kModeT2, st));
       std::swap(ucur, uprev);
     }
-    HIPCHK(launch_ext_scatter(coef, eg, +1, wk.t2u, d.field, wk.t2d, d.field, pl.seg_stride, Sb, nk, st));
+    HIPCHK(launch_ext_scatter(coef, eg, +1, t2u, d.field, pl.seg_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
+                              st));
     for (int n = n0; n < n1; ++n) {
       StepArgs a = batch_args(c, Sb, d.field);
       a.cur = wcur;
       a.prev = wprev;
       a.out = wprev;
-      a.dsrc = wk.t2d + (long)(n - n0) * d.field;
-      a.dsrc_sstride = pl.seg_stride;
+      a.dsrc = wk.er + (long)(n - n0) * d.field;
+      a.dsrc_sstride = pl.ring_stride;
+      if (pl.hist) {
+        a.t2 = t2d + (long)(n - n0) * d.field;
+        a.t2_sstride = pl.seg_stride;
+      }
       with_rec_extract(a, t, ddrec, g->nt, n);
-      HIPCHK(launch_step(a, d.TX, kModeDsrc, st));
+      HIPCHK(launch_step(a, d.TX, pl.hist ? kModeT2 | kModeDsrc : kModeDsrc, st));
       std::swap(wcur, wprev);
     }
   }
@@ -1565,26 +1723,42 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
                         hipStream_t st) {
   const Dims &d = c.d;
   const int K = pl.K, R = pl.R;
-  HIPCHK(launch_zero(wk.lam, pl.ring_stride * Sb, st));
-  HIPCHK(launch_zero(wk.er, pl.ring_stride * Sb, st));
-  HIPCHK(launch_zero(wk.rho, pl.ring_stride * Sb, st));
   const bool two = ctx->two_step;
+  for (float *ring : {wk.lam, wk.er, wk.rho}) {
+    // (the one-step kernels read e on the whole grid)
+    if (two) HIPCHK(zero_end(ring, pl.ring_stride, R, d, Sb, st));
+    else HIPCHK(launch_zero(ring, pl.ring_stride * Sb, st));
+  }
   int rc;
   for (int j = pl.nseg - 1; j >= 0; --j) {
     const int n0 = j * K, n1 = std::min(n0 + K, g->nt - 1), nk = n1 - n0;
-    if (two) {
-      // u from its checkpoint, two steps per launch, keeping T2 u_n
-      Ring4 wu(wk.pairs, d.field * Sb);
+    const float *t2u = wk.t2u + pl.t2_off(d, n0), *t2d = wk.t2d + pl.t2_off(d, n0);
+    auto er_slot = [&](int k) { return wk.er + (long)(k % R) * d.field; };
+    if (two && !pl.hist) {
+      // u and du~ from their checkpoints, two steps per launch, keeping
+      // T2 u_n and T2 du~_n; the scattering source of du~ takes the slots of
+      // the e ring that this segment's spread fills afterwards
+      Ring4 wu(wk.pairs, d.field * Sb), ww(wk.pairs + 4 * d.field * Sb, d.field * Sb);
       HIPCHK(launch_copy_fields(wu.prev(), d.field, uck + (2L * j) * d.field, pl.ck_stride, Sb, d.field, st));
       HIPCHK(launch_copy_fields(wu.cur(), d.field, uck + (2L * j + 1) * d.field, pl.ck_stride, Sb, d.field, st));
+      HIPCHK(launch_copy_fields(ww.prev(), d.field, dck + (2L * j) * d.field, pl.ck_stride, Sb, d.field, st));
+      HIPCHK(launch_copy_fields(ww.cur(), d.field, dck + (2L * j + 1) * d.field, pl.ck_stride, Sb, d.field, st));
       rc = march2(ctx, c, wu, Sb, n0, n1, kModeT2, [&](Step2Args &p, int n, int k) {
-        p.a.t2 = wk.t2u + (long)(n - n0) * d.field;
-        p.t2b = k == 2 ? wk.t2u + (long)(n - n0 + 1) * d.field : nullptr;
-        p.a.t2_sstride = pl.seg_stride;
+        with_t2(p, wk.t2u + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
         with_src2(p, t, wav_b, g, n);
       }, st);
       if (rc) return rc;
-    } else {
+      HIPCHK(launch_ext_scatter(coef, eg, +1, wk.t2u, d.field, pl.seg_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
+                                st, 0, 0, R, n0));
+      rc = march2(ctx, c, ww, Sb, n0, n1, kModeT2 | kModeDsrc, [&](Step2Args &p, int n, int k) {
+        p.a.dsrc = er_slot(n);
+        p.dsrc2 = k == 2 ? er_slot(n + 1) : nullptr;
+        p.a.dsrc_sstride = pl.ring_stride;
+        with_dense_range(p.a, eg, eg.H);
+        with_t2(p, wk.t2d + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
+      }, st);
+      if (rc) return rc;
+    } else if (!pl.hist) {
       float *uc = uck + (2L * j + 1) * d.field, *up = uck + (2L * j) * d.field;
       for (int n = n0; n < n1; ++n) {
         StepArgs a = batch_args(c, Sb, pl.ck_stride);
@@ -1597,22 +1771,23 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
         HIPCHK(launch_step(a, d.TX, kModeT2, st));
         std::swap(uc, up);
       }
-    }
-    // t2d holds T2 du~ of the later segment outside the scatter's range: clear it
-    HIPCHK(launch_zero(wk.t2d, pl.seg_stride * Sb, st));
-    HIPCHK(launch_ext_scatter(coef, eg, +1, wk.t2u, d.field, wk.t2d, d.field, pl.seg_stride, Sb, nk, st));
-    float *wc = dck + (2L * j + 1) * d.field, *wp = dck + (2L * j) * d.field;
-    for (int n = n0; n < n1; ++n) {
-      StepArgs a = batch_args(c, Sb, pl.ck_stride);
-      a.cur = wc;
-      a.prev = wp;
-      a.out = wp;
-      a.dsrc = wk.t2d + (long)(n - n0) * d.field;   // read the source, then
-      a.dsrc_sstride = pl.seg_stride;
-      a.t2 = wk.t2d + (long)(n - n0) * d.field;     // overwrite it with T2 du~_n
-      a.t2_sstride = pl.seg_stride;
-      HIPCHK(launch_step(a, d.TX, kModeT2 | kModeDsrc, st));
-      std::swap(wc, wp);
+      // t2d holds T2 du~ of the later segment outside the scatter's range: clear it
+      HIPCHK(launch_zero(wk.t2d, pl.seg_stride * Sb, st));
+      HIPCHK(launch_ext_scatter(coef, eg, +1, wk.t2u, d.field, pl.seg_stride, wk.t2d, d.field, pl.seg_stride, Sb, nk,
+                                st));
+      float *wc = dck + (2L * j + 1) * d.field, *wp = dck + (2L * j) * d.field;
+      for (int n = n0; n < n1; ++n) {
+        StepArgs a = batch_args(c, Sb, pl.ck_stride);
+        a.cur = wc;
+        a.prev = wp;
+        a.out = wp;
+        a.dsrc = wk.t2d + (long)(n - n0) * d.field;   // read the source, then
+        a.dsrc_sstride = pl.seg_stride;
+        a.t2 = wk.t2d + (long)(n - n0) * d.field;     // overwrite it with T2 du~_n
+        a.t2_sstride = pl.seg_stride;
+        HIPCHK(launch_step(a, d.TX, kModeT2 | kModeDsrc, st));
+        std::swap(wc, wp);
+      }
     }
     if (two) {
       if ((rc = march2_back_lambda(ctx, c, wk.lam, pl.ring_stride, R, Sb, n0, n1, t, r, g->nt, st))) return rc;
@@ -1626,13 +1801,13 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
         HIPCHK(launch_step(a, d.TX, kModePlain, st));
       }
     }
-    HIPCHK(launch_ext_scatter(coef, eg, -1, wk.lam, d.field, wk.er, d.field, pl.ring_stride, Sb, nk, st, R, n0, R,
-                              n0));
-    auto er_slot = [&](int k) { return wk.er + (long)(k % R) * d.field; };
+    HIPCHK(launch_ext_scatter(coef, eg, -1, wk.lam, d.field, pl.ring_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
+                              st, R, n0, R, n0));
     if (two) {
       rc = march2_back_ring(ctx, c, wk.rho, pl.ring_stride, R, Sb, n0, n1, kModeNu, [&](Step2Args &p, int k, int kk) {
         p.a.nu = NuSource{er_slot(k - 1), er_slot(k), er_slot(k + 1), pl.ring_stride};
         if (kk == 2) p.nu2 = NuSource{er_slot(k - 2), er_slot(k - 1), er_slot(k), pl.ring_stride};
+        with_dense_range(p.a, eg, eg.H);
       }, st);
       if (rc) return rc;
     } else {
@@ -1645,9 +1820,9 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
         HIPCHK(launch_step(a, d.TX, kModeNu, st));
       }
     }
-    HIPCHK(launch_ext_image(wk.t2u, d.field, pl.seg_stride, wk.lam, d.field, pl.ring_stride, R, n0, Sb, nk, eg, acc,
+    HIPCHK(launch_ext_image(t2u, d.field, pl.seg_stride, wk.lam, d.field, pl.ring_stride, R, n0, Sb, nk, eg, acc,
                             wk.parts, st));
-    HIPCHK(launch_grad_accum(wk.t2u, wk.t2d, d.field, pl.seg_stride, wk.lam, wk.rho, d.field, pl.ring_stride, R, n0,
+    HIPCHK(launch_grad_accum(t2u, t2d, d.field, pl.seg_stride, wk.lam, wk.rho, d.field, pl.ring_stride, R, n0,
                              Sb, nk, d.NZ, d.NX, d.LZ, gacc, st));
   }
   return FWIME_OK;
@@ -1655,13 +1830,16 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
 
 // the two-step path keeps four field buffers per wavefield (u and du~)
 long grad_work_per_shot(const Dims &d, const GradPlan &pl, bool two) {
-  return ((two ? 8L : 4L) + 2L * pl.K + 3L * pl.R) * d.field * 4;
+  return (((two ? 8L : 4L) + 3L * pl.R) * d.field + 2L * pl.seg_stride) * 4;
 }
 
-void carve_work(Carve &cv, GradWork &wk, const Dims &d, const GradPlan &pl, int S, bool two) {
+// t2: with the T2 buffers (not those of a tape that holds whole histories)
+void carve_work(Carve &cv, GradWork &wk, const Dims &d, const GradPlan &pl, int S, bool two, bool t2 = true) {
   cv.add(&wk.pairs, (two ? 8 : 4) * d.field * S);
-  cv.add(&wk.t2u, (long)pl.K * d.field * S);
-  cv.add(&wk.t2d, (long)pl.K * d.field * S);
+  if (t2) {
+    cv.add(&wk.t2u, pl.seg_stride * S);
+    cv.add(&wk.t2d, pl.seg_stride * S);
+  }
   cv.add(&wk.lam, (long)pl.R * d.field * S);
   cv.add(&wk.er, (long)pl.R * d.field * S);
   cv.add(&wk.rho, (long)pl.R * d.field * S);
@@ -1683,7 +1861,7 @@ struct fwime_tape {
   void *mem = nullptr;
   size_t bytes = 0;
   float *V = nullptr, *gz = nullptr, *gx = nullptr, *vel = nullptr, *pt = nullptr, *coef = nullptr, *wav = nullptr;
-  float *uck = nullptr, *dck = nullptr;   // [nshots] x ck_stride each
+  float *uck = nullptr, *dck = nullptr;   // [nshots] x ck_stride each (whole T2 histories: x seg_stride)
   int *tables = nullptr;
   bool used = false;
 };
@@ -1721,10 +1899,12 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   const long img = (long)nh * plane;
   if ((rc = check_inputs(ctx, g, vel, geo, {{dobs, ndata}}, st))) return rc;
 
-  // the background does not change during the step: the extended-precision
-  // adjoint's checkpoints (2 nseg fields and their low parts per shot) are
-  // kept for all shots when they fit, so every B~* after the first skips its
-  // forward pass (FWIME_VP_NOCACHE=1 turns this off)
+  // the background does not change during the step: its T2 terms of every
+  // shot and step are kept where they fit (hist), so that B~ and every B~*
+  // after the first propagate only the scattered and the adjoint field; else
+  // the extended-precision adjoint's checkpoints (2 nseg fields and their low
+  // parts per shot), so that every B~* after the first skips its forward pass
+  // (FWIME_VP_NOCACHE=1 turns both off)
   const Dims dd = make_dims(g, ctx->tile_x);
   const int K = seg_len(g->nt);
   const long nseg = (g->nt - 1 + K - 1) / K;
@@ -1738,13 +1918,21 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
     const size_t need = (size_t)ck_elems * 6;
     use_cache = need < (size_t)((avail + ctx->vp_bytes) * 0.5) && (!ctx->budget || need < ctx->budget / 2);
   }
+  const long hist_elems = (g->nt - 1L) * dd.field * geo->nshots;
+  const bool use_hist = use_cache && hist_batch(ctx, geo->nshots, 0, [&](int S) {
+    // beside it, at the same time: the rings and chunks of B~ and B~*
+    const long K = hist_seg_len(g->nt, S);
+    return ((g->nt - 1L + 16 + 2 * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + (size_t)img * (8 + 4 * kImageGroups);
+  }, ctx->vp_bytes) > 0;
   // solver vectors, kept in the context between calls
   float *r = nullptr, *sdir = nullptr, *q = nullptr, *b = nullptr, *dres = nullptr, *dtmp = nullptr,
         *e2d2 = nullptr;
   double *part = nullptr, *res = nullptr;
   AdjCache cache;
   Carve cv;
-  if (use_cache) {
+  if (use_hist) {
+    cv.add(&cache.hist, hist_elems);
+  } else if (use_cache) {
     cv.add(&cache.ckpt, ck_elems);
     cv.add(&cache.ckpt_lo, ck_elems);
   }
@@ -1798,7 +1986,7 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   AdjCache *cp = use_cache ? &cache : nullptr;
   auto fwd = [&](const float *x, float *d) {
     return tau ? fwime_born_ext_tau_fwd(ctx, g, vel, geo, nh, lag, x, d, stream)
-               : fwime_born_ext_fwd(ctx, g, vel, geo, nh, x, d, stream);
+               : born_ext_fwd_run(ctx, g, vel, geo, nh, x, d, stream, cache.hist);
   };
   auto adj = [&](const float *d, float *x) {
     return tau ? fwime_born_ext_tau_adj(ctx, g, vel, geo, nh, lag, d, x, stream)
@@ -1865,13 +2053,17 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   c.d = make_dims(g, ctx->tile_x);
   const Dims &d = c.d;
   ExtGeom eg{d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, nh, (nh - 1) / 2};
-  const GradPlan pl = grad_plan(d, g->nt);
   const long img = (long)nh * d.nx * d.nz;
   const long nrt = (long)geo->nrec * g->nt;
-  const long per_shot =
-      grad_work_per_shot(d, pl, ctx->two_step) + 2 * pl.ck_stride * 4 + 2 * nrt * 4 + (long)geo->nrec * 64;
   const size_t fixed = (size_t)d.field * 12 + (size_t)img * 4 * (5 + kImageGroups);
-  const int S = choose_batch(ctx, per_shot, fixed, geo->nshots);
+  auto per_shot = [&](const GradPlan &p) {
+    return grad_work_per_shot(d, p, ctx->two_step) + 2 * p.ck_stride * 4 + 2 * nrt * 4 + (long)geo->nrec * 64;
+  };
+  const int Sh = hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
+    return fixed + (size_t)per_shot(grad_plan(d, g->nt, S)) * S;
+  });
+  const GradPlan pl = grad_plan(d, g->nt, Sh);
+  const int S = Sh ? Sh : choose_batch(ctx, per_shot(pl), fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
   TableSet ts = build_table_set(d, geo, batches, ctx->two_step);
 
@@ -2016,13 +2208,13 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     // background: T2u of every step, and its receiver data
     if ((rc = tau_background(ctx, c, g, geo, s0, Sb, t, pairs, lows, hu, hs, st, drec))) return rc;
     // scattering source history, then du~ with its T2 history and receivers
-    HIPCHK(launch_zero(sc, hs * Sb, st));
     HIPCHK(launch_tau_scatter(coef, eg, lag, hu, sc, d.field, hs, ns, Sb, st));
     float *wp = pairs + 4 * d.field * Sb;
-    HIPCHK(launch_zero(wp, 4 * d.field * Sb, st));
+    HIPCHK(zero_start(wp, d, Sb, st));
     Ring4 fw(wp, d.field * Sb);
     rc = march2(ctx, c, fw, Sb, 0, ns, kModeT2 | kModeDsrc, [&](Step2Args &p, int n, int k) {
       with_dsrc2(p, sc + (long)n * d.field, d.field, k, hs);
+      with_dense_range(p.a, eg, 0);
       p.a.t2 = hdu + (long)n * d.field;
       p.t2b = k == 2 ? hdu + (long)(n + 1) * d.field : nullptr;
       p.a.t2_sstride = hs;
@@ -2033,21 +2225,22 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     // residual r = R(u + du~) - d_obs (into drec) and its sum of squares
     HIPCHK(launch_residual(drec, ddrec, dobs + (long)s0 * nrt, nrt * Sb, rpart, sumsq, st));
     // adjoint field of every time
-    HIPCHK(launch_zero(lam, hs * Sb, st));
+    HIPCHK(zero_end(lam, hs, R, d, Sb, st));
     if ((rc = march2_back_lambda(ctx, c, lam, hs, R, Sb, 0, g->nt - 1, t, drec, g->nt, st))) return rc;
     // spread e over the adjoint history (slots 0 .. ns-1; zero from ns on)
-    HIPCHK(launch_zero(sc, hs * Sb, st));
+    HIPCHK(launch_zero_fields(sc + (long)ns * d.field, hs, Sb, 2 * d.field, st));
     HIPCHK(launch_tau_scatter(coefr, eg, lag, lam, sc, d.field, hs, ns, Sb, st));
     // rho = M^-T nu, nu^k = e_{k-1}/g - 2 e_k + g e_{k+1}, chunk by chunk
     // backwards, each chunk followed by its gradient sums
     auto e_slot = [&](int k) { return sc + (long)k * d.field; };
-    HIPCHK(launch_zero(rho, rs * Sb, st));
+    HIPCHK(zero_end(rho, rs, RR, d, Sb, st));
     const int nchunk = (ns + kTauChunk - 1) / kTauChunk;
     for (int j = nchunk - 1; j >= 0; --j) {
       const int n0 = j * kTauChunk, n1 = std::min(n0 + kTauChunk, ns);
       rc = march2_back_ring(ctx, c, rho, rs, RR, Sb, n0, n1, kModeNu, [&](Step2Args &p, int k, int kk) {
         p.a.nu = NuSource{e_slot(k - 1), e_slot(k), e_slot(k + 1), hs};
         if (kk == 2) p.nu2 = NuSource{e_slot(k - 2), e_slot(k - 1), e_slot(k), hs};
+        with_dense_range(p.a, eg, 0);
       }, st);
       if (rc) return rc;
       HIPCHK(launch_grad_accum2(hu + (long)n0 * d.field, hdu + (long)n0 * d.field, d.field, hs, lam, d.field, hs, R,
@@ -2096,15 +2289,21 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   tp->nrec = geo->nrec;
   tp->d = make_dims(g, ctx->tile_x);
   const Dims &d = tp->d;
-  tp->pl = grad_plan(d, g->nt);
-  const GradPlan &pl = tp->pl;
   ExtGeom eg{d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, nh, (nh - 1) / 2};
   const long img = (long)nh * d.nx * d.nz;
   const long nrt = (long)geo->nrec * g->nt;
-  // checkpoints of every shot live in the tape; working fields in the arena
-  const long per_shot = grad_work_per_shot(d, pl, ctx->two_step) + 2 * nrt * 4 + (long)geo->nrec * 64;
+  // checkpoints (or whole histories) of every shot live in the tape; working
+  // fields in the arena
+  const size_t rest = 2 * nrt * 4 + (size_t)geo->nrec * 64;
+  // whole histories only if every shot's fit (the tape holds them all)
+  const int Sh = hist_batch(ctx, geo->nshots, 0, [&](int S) {
+    return (grad_work_per_shot(d, grad_plan(d, g->nt, S), ctx->two_step) + rest) * S + (size_t)d.field * 8;
+  });
+  tp->pl = grad_plan(d, g->nt, Sh);
+  const GradPlan &pl = tp->pl;
+  const size_t per_shot = grad_work_per_shot(d, pl, ctx->two_step) + rest;
   const size_t tape_fixed = (size_t)(2 * pl.ck_stride * 4) * geo->nshots;
-  const int S = choose_batch(ctx, per_shot, tape_fixed + (size_t)d.field * 8, geo->nshots);
+  const int S = Sh ? Sh : choose_batch(ctx, per_shot, tape_fixed + (size_t)d.field * 8, geo->nshots);
   tp->batches = split_batches(geo->nshots, S);
   tp->ts = build_table_set(d, geo, tp->batches, ctx->two_step);
 
@@ -2117,8 +2316,8 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   tc.add(&tp->pt, img);
   tc.add(&tp->coef, img);
   tc.add(&tp->wav, (long)geo->nshots * g->nt);
-  tc.add(&tp->uck, pl.ck_stride * geo->nshots);
-  tc.add(&tp->dck, pl.ck_stride * geo->nshots);
+  tc.add(&tp->uck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
+  tc.add(&tp->dck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
   if (ctx->budget && ctx->tape_bytes + tc.total + ctx->arena_bytes > ctx->budget) {
     delete tp;
     return set_err(ctx, FWIME_ENOMEM, "tape does not fit the HBM budget");
@@ -2160,10 +2359,14 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   float *drec = nullptr, *ddrec = nullptr;
   GradWork wk;
   Carve cv;
-  carve_work(cv, wk, d, pl, S, ctx->two_step);
+  carve_work(cv, wk, d, pl, S, ctx->two_step, !pl.hist);
   cv.add(&drec, nrt * S);
   cv.add(&ddrec, nrt * S);
   if ((rc = arena_get(ctx, cv))) return fail(rc);
+  if (pl.hist) {
+    wk.t2u = tp->uck;
+    wk.t2d = tp->dck;
+  }
   for (size_t bi = 0; bi < tp->batches.size(); ++bi) {
     const int s0 = tp->batches[bi].first, Sb = tp->batches[bi].second;
     if ((rc = grad_forward_batch(ctx, c, eg, pl, g, Sb, tp->ts.dev[bi], tp->wav + (long)s0 * g->nt, tp->coef,
@@ -2209,9 +2412,13 @@ int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tp, const float *adjsrc,
   cv.add(&acc, img);
   cv.add(&imgs, img);
   cv.add(&gacc, d.field);
-  carve_work(cv, wk, d, pl, S, ctx->two_step);
+  carve_work(cv, wk, d, pl, S, ctx->two_step, !pl.hist);
   cv.add(&wk.parts, kImageGroups * img);
   if ((rc = arena_get(ctx, cv))) return rc;
+  if (pl.hist) {
+    wk.t2u = tp->uck;
+    wk.t2d = tp->dck;
+  }
   Common c;
   c.d = d;
   c.V = tp->V;
