@@ -67,6 +67,9 @@ __host__ __device__ inline void tile_coords(int logical, int ntz, int ntx, int S
 // Per-tile injection list (compressed rows over tile*kWaves + wave).
 // An entry {(j << 6) | lz, idx} adds  val[idx * stride_idx + t] * scale  to the
 // source term of the cell in column j (of the wave's columns) and row lz.
+// In the two-step lists every entry of a bucket that names a cell twice also
+// carries kInjRepeat.
+constexpr int kInjRepeat = 1 << 30;
 struct Inject {
   const int *ptr = nullptr;     // [ntiles_total * kWaves + 1]
   const int2 *ent = nullptr;
@@ -182,7 +185,7 @@ struct Step2Args {
 
 // mode: kModePlain, kModeT2, kModeDsrc, kModeT2 | kModeDsrc (a.t2 and a.dsrc in
 // distinct buffers), kModeNu, kModeDF, kModeT2 | kModeDF or kModeDsrc | kModeDF
-// (plus kModeFS, added when p.a.fs >= 0)
+// (plus kModeFS, added when p.a.fs >= 0); with a dense source no point sources
 hipError_t launch_step2(const Step2Args &p, int tile_x, int mode, hipStream_t st);
 
 // One job of a two-step multi-job launch: its step arguments (fields, times

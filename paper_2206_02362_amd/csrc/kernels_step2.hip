@@ -72,37 +72,67 @@ __device__ __forceinline__ float df_update(float g, float c, float cl, float pv,
   return hi;
 }
 
-// Adds a wavefront's point sources to its per-column source registers, in list
-// order (the order in which the one-step kernel adds them).  Done before the
-// column march so that the march itself has no loop inside.  Lane l fetches
-// entry l of each batch of 64 and its sample, so a batch costs two dependent
-// loads however many entries it has; the entries are then broadcast one by
-// one from registers.
-template <int W>
-__device__ __forceinline__ void fold_sources(const Inject &inj, int logical, int w, int lane, float (&src)[W]) {
-  if (inj.ptr == nullptr) return;
-  const int e1 = inj.ptr[logical * kWaves + w + 1];
-  for (int b = inj.ptr[logical * kWaves + w]; b < e1; b += 64) {   // wave-uniform
-    const int cnt = min(64, e1 - b);
-    int key = 0;
-    float val = 0.f;
-    if (lane < cnt) {
-      const int2 en = inj.ent[b + lane];
-      key = en.x;
+// A wavefront's point sources (injection list entries of its columns).  The
+// chain list range -> entries -> samples misses the L2, which every launch
+// starts cold, at each link: formed where the samples are added, it took a
+// 100 x 200 adjoint launch (a receiver in every column) from 7.5 to 11.7 us.
+// range() and fetch() therefore come right behind the tile loads, so that the
+// scalar loads of the ranges overlap them, and the rest is in a branch that
+// wavefronts without sources skip.
+struct Sources {
+  int i0 = 0, cnt = 0;
+  int2 en = {0, 0};
+  float val = 0.f;
+
+  // no branch: without a list two readable words of `any` stand in for it
+  __device__ __forceinline__ void range(const Inject &inj, int logical, int w, const float *any) {
+    const int *at = inj.ptr ? inj.ptr + (logical * kWaves + w) : reinterpret_cast<const int *>(any);
+    i0 = at[0];
+    cnt = inj.ptr ? at[1] - i0 : 0;
+  }
+  // entries b .. b + 63 of the list and their samples, one per lane
+  __device__ __forceinline__ void fetch(const Inject &inj, int lane, int b) {
+    if (b + lane < cnt) {
+      en = inj.ent[i0 + b + lane];
       val = inj.val[(long)en.y * inj.stride_idx + inj.t] * inj.scale;
     }
-    for (int k = 0; k < cnt; ++k) {
-      const int kx = __builtin_amdgcn_readlane(key, k);
-      const float kv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, val), k));
-      const int j = kx >> 6;
-      if ((kx & 63) == lane) {
-#pragma unroll
-        for (int jj = 0; jj < W; ++jj)
-          if (jj == j) src[jj] += kv;
-      }
-    }
   }
-}
+  // Adds the samples to the wavefront's per-column source registers in list
+  // order (the order in which the one-step kernel adds them).  A list whose
+  // cells are all different (no kInjRepeat on its entries) goes through LDS:
+  // `cols`, W columns of ROWS floats of the caller's own, takes every sample
+  // at its cell at once.  Else, or without such columns (null), the entries
+  // are broadcast one by one.
+  template <int W, int ROWS>
+  __device__ __forceinline__ void add(const Inject &inj, int lane, float (*cols)[ROWS], float (&src)[W]) {
+    if (cnt == 0) return;                     // wave-uniform
+    if (cols == nullptr || (__builtin_amdgcn_readfirstlane(en.x) & kInjRepeat)) {
+      for (int b = 0; b < cnt; b += 64) {
+        if (b > 0) fetch(inj, lane, b);
+        const int n = min(64, cnt - b);
+        for (int k = 0; k < n; ++k) {
+          const int kx = __builtin_amdgcn_readlane(en.x, k) & ~kInjRepeat;
+          const float kv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, val), k));
+          const int j = kx >> 6;
+          if ((kx & 63) == lane) {
+#pragma unroll
+            for (int jj = 0; jj < W; ++jj)
+              if (jj == j) src[jj] += kv;
+          }
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < W; ++j) cols[j][lane] = 0.f;
+    for (int b = 0; b < cnt; b += 64) {
+      if (b > 0) fetch(inj, lane, b);
+      if (b + lane < cnt) cols[en.x >> 6][en.x & 63] = val;
+    }
+#pragma unroll
+    for (int j = 0; j < W; ++j) src[j] += cols[j][lane];
+  }
+};
 
 // One 56 x TX tile of one shot; `logical` is the tile's position in the
 // launch order of tile_index.  extract_only: only sample u^n.  ext_next: sample
@@ -116,6 +146,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   constexpr bool NU = (MODE & kModeNu) != 0;
   constexpr bool DF = (MODE & kModeDF) != 0;
   constexpr bool FS = (MODE & kModeFS) != 0;
+  constexpr bool PS = !DS && !NU;             // a dense source and point sources exclude each other
   constexpr int C0 = Step2Tile<TX>::C0;
   constexpr int ROWS = Step2Tile<TX>::ROWS;
   constexpr int W1 = (TX + 8) / kWaves;      // step-1 columns per wave
@@ -158,6 +189,9 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   // results are stored, or zeroed when outside the grid, so they are read
   // unconditionally at the nearest cell inside the grid: no guard, no branch.
   const int vzc = min(max(z, 0), NZ - 1) * 4;                     // clamped row
+  // point sources of both steps; receivers e0 .. e1 - 1 of the tile
+  [[maybe_unused]] Sources src1, src2;
+  int e0, e1;
   // offset of a dense source's row in column x: past the end (reads zero)
   // outside the rows and columns the source lives on
   [[maybe_unused]] const int vze = z >= a.ez0 && z < a.ez1 ? vzc : kOutOfRange;
@@ -197,13 +231,14 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   }
 
   float vv2[W2], ds2[W2], gx2[W2];
+#pragma unroll
+  for (int j = 0; j < W2; ++j) ds2[j] = 0.f;
   auto load_step2_operands = [&]() {
 #pragma unroll
     for (int j = 0; j < W2; ++j) {
       const int xc = min(xs2 + j, NX - 1);
       gx2[j] = a.gx[xc];
       vv2[j] = ld(r_V, vzc, xc * CB);
-      ds2[j] = 0.f;
     }
   };
 
@@ -276,6 +311,19 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
         ds2[j] = ld(r_ds2, dense_off(xc), xc * CB);
       }
     }
+    {
+      const int *at = a.ext.ptr ? a.ext.ptr + logical : reinterpret_cast<const int *>(a.gx);
+      e0 = at[0];
+      e1 = a.ext.ptr ? at[1] : e0;
+    }
+    if constexpr (PS) {
+      src1.range(a.inj, logical, w, a.gx);
+      src2.range(p.inj2, logical, w, a.gx);
+      if (src1.cnt | src2.cnt) {              // wave-uniform
+        src1.fetch(a.inj, lane, 0);
+        src2.fetch(p.inj2, lane, 0);
+      }
+    }
     // Lanes 8..63 put their (zero) second value into this wave's own column
     // of the u^{n+1} tile, which step 1 overwrites after the barrier: a write
     // without a branch keeps the compiler from moving those loads into one.
@@ -294,8 +342,6 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   __syncthreads();
 
   // receivers of u^n (time t)
-  const int e0 = a.ext.ptr ? a.ext.ptr[logical] : 0;
-  const int e1 = a.ext.ptr ? a.ext.ptr[logical + 1] : 0;
   for (int e = e0 + tid; e < e1; e += 256) {
     const int2 en = a.ext.ent[e];
     a.ext.out[(long)en.y * a.ext.stride_idx + a.ext.t] = sh.u0[(en.x >> 6) + 2 * kR][(en.x & 63) + 2 * kR];
@@ -316,7 +362,11 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   }
   // ---- step 1: u^{n+1} on the tile plus a 4-cell halo --------------------
   {
-    fold_sources<W1>(a.inj, logical, w, lane, ds1);
+    // through this wavefront's own columns of the u^{n+1} tile, not yet written
+    if constexpr (PS) {
+      src1.add(a.inj, lane, &sh.u1[w * W1], ds1);
+      if constexpr (EARLY2) src2.add(p.inj2, lane, &sh.u1[w * W1], ds2);
+    }
     const auto r_out = rsrc(a.out + soff, FB);
     [[maybe_unused]] __amdgpu_buffer_rsrc_t r_t2, r_lout;
     if constexpr (T2) r_t2 = rsrc(a.t2 + (long)s * a.t2_sstride, FB);
@@ -442,7 +492,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
         ds2[j] += ld(rm2, o, xc * CB) / g - 2.f * ld(r02, o, xc * CB) + g * ld(rp2, o, xc * CB);
       }
     }
-    fold_sources<W2>(p.inj2, logical, w, lane, ds2);
+    if constexpr (PS && !EARLY2) src2.add<W2, ROWS>(p.inj2, lane, nullptr, ds2);
     const auto r_out = rsrc(p.out2 + soff, FB);
     [[maybe_unused]] __amdgpu_buffer_rsrc_t r_t2, r_lout;
     if constexpr (T2) r_t2 = rsrc(p.t2b + (long)s * a.t2_sstride, FB);
@@ -614,6 +664,7 @@ static hipError_t launch_step2_tx(const Step2Args &p, int mode, hipStream_t st) 
   const long total = (long)p.a.ntz * p.a.ntx * p.a.nshots;
   const dim3 grid((unsigned)((total + 7) / 8 * 8));
   if (p.a.fs >= 0) mode |= kModeFS;
+  if ((mode & (kModeDsrc | kModeNu)) && (p.a.inj.ptr || p.inj2.ptr)) return hipErrorInvalidValue;
   switch (mode) {
 #define FW_STEP2_MODE(M)                                     \
   case M: k_step2<TX, M><<<grid, 256, 0, st>>>(p); break;    \

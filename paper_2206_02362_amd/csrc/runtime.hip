@@ -345,6 +345,23 @@ void csr_build(std::vector<int> &ptr, std::vector<int2> &ent, long nbucket,
                      [](const int2 &a, const int2 &c) { return (a.x >> 6) < (c.x >> 6); });
 }
 
+// kInjRepeat on every entry of a bucket that names a cell twice (buckets are
+// sorted by column: only entries of one column can name the same cell)
+void mark_repeats(const std::vector<int> &ptr, std::vector<int2> &ent) {
+  for (size_t b = 0; b + 1 < ptr.size(); ++b) {
+    bool repeat = false;
+    uint64_t rows = 0;
+    for (int e = ptr[b]; e < ptr[b + 1]; ++e) {
+      if (e > ptr[b] && (ent[e].x >> 6) != (ent[e - 1].x >> 6)) rows = 0;
+      const uint64_t bit = 1ull << (ent[e].x & 63);
+      repeat = repeat || (rows & bit);
+      rows |= bit;
+    }
+    if (repeat)
+      for (int e = ptr[b]; e < ptr[b + 1]; ++e) ent[e].x |= kInjRepeat;
+  }
+}
+
 HostTables build_tables(const Dims &d, const fwime_geom_t *geo, int s0, int S) {
   HostTables t;
   const int CPW = d.TX / kWaves;
@@ -420,6 +437,10 @@ HostTables build_tables2(const Dims &d, const fwime_geom_t *geo, int s0, int S) 
   csr_build(t.rext_ptr, t.rext_ent, ntiles, rext);
   csr_build(t.rinj1_ptr, t.rinj1_ent, ntiles * kWaves, rinj1);
   csr_build(t.rinj_ptr, t.rinj_ent, ntiles * kWaves, rinj2);
+  mark_repeats(t.src1_ptr, t.src1_ent);
+  mark_repeats(t.src_ptr, t.src_ent);
+  mark_repeats(t.rinj1_ptr, t.rinj1_ent);
+  mark_repeats(t.rinj_ptr, t.rinj_ent);
   return t;
 }
 
