@@ -295,7 +295,7 @@ typedef struct {
  * launch loop is bracketed by two HIP events recorded on the call's stream;
  * this call then waits for the second event and reports the elapsed time
  * and the number of stencil launches (a launch advances every active shot
- * by one or two time steps).  Without timing, last_stencil_launches is -1. */
+ * by one to four time steps).  Without timing, last_stencil_launches is -1. */
 int fwime_ctx_info(const fwime_ctx_t *ctx, fwime_info_t *out);
 
 /* Turn the event timing above on (on != 0) or off.  It adds two event

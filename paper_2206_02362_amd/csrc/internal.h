@@ -31,11 +31,38 @@ __device__ __forceinline__ float ld(__amdgpu_buffer_rsrc_t r, int voff, int soff
 __device__ __forceinline__ void st(__amdgpu_buffer_rsrc_t r, float v, int voff, int soff) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
 }
+// store to `base` as a buffer of `bytes` bytes: size zero drops it
+__device__ __forceinline__ void st_f(float *base, unsigned bytes, float v, int voff, int soff) {
+  st(rsrc(base, bytes), v, voff, soff);
+}
 __device__ __forceinline__ unsigned short ld16(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   return __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
 }
 __device__ __forceinline__ void st16(__amdgpu_buffer_rsrc_t r, unsigned short v, int voff, int soff) {
   __builtin_amdgcn_raw_buffer_store_b16(v, r, voff, soff, 0);
+}
+
+__device__ __forceinline__ float bf16_f32(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
+__device__ __forceinline__ unsigned short f32_bf16(float f) {   // round to nearest even (finite values)
+  const unsigned u = __float_as_uint(f);
+  return (unsigned short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+}
+
+// Brings every 64-byte line of a kernel's arguments (`bytes` of them) into the
+// scalar cache with one round trip.  The compiler loads arguments where it
+// first needs them; a launch starts with cold caches, so each of those loads,
+// one after the other, waits for memory (about 0.9 us of a launch in all).  For
+// kernels with registers to spare: in the two-step kernel it cost a wavefront
+// per SIMD and large grids more than small ones gained.
+template <int bytes>
+__device__ __forceinline__ void warm_args() {
+  // volatile: the words are dropped, not kept in registers for later uses
+  auto *w = (const volatile __attribute__((address_space(4))) int *)__builtin_amdgcn_kernarg_segment_ptr();
+  int x[(bytes + 63) / 64];
+#pragma unroll
+  for (int i = 0; i < (bytes + 63) / 64; ++i) x[i] = w[i * 16];
+#pragma unroll
+  for (int i = 0; i < (bytes + 63) / 64; ++i) asm volatile("" ::"s"(x[i]));
 }
 
 // Order of the stencil tiles of one launch (S shots, ntz x ntx tiles each).
@@ -97,13 +124,18 @@ struct NuSource {
   long sstride = 0;                                          // per-shot stride
 };
 
+// What a kernel's first loads need comes first: the arguments are fetched from
+// cold caches, line by line, as they are used.
 struct StepArgs {
+  int NZ = 0, NX = 0, LZ = 0;
+  int nshots = 0, ntz = 0, ntx = 0;
+  long sstride = 0;             // elements between shots in cur/prev/out
   const float *cur = nullptr;   // field at the current time, [S][NX][LZ]
   const float *prev = nullptr;  // field one step behind (read)
-  float *out = nullptr;         // next field (may alias prev)
   const float *V = nullptr;     // v^2 dt^2, [NX][LZ]
   const float *gz = nullptr;    // taper along z, [LZ]
   const float *gx = nullptr;    // taper along x, [NX]
+  float *out = nullptr;         // next field (may alias prev)
   float *t2 = nullptr;          // optional V (L cur + src) output, [S] x t2_sstride
   long t2_sstride = 0;
   const float *dsrc = nullptr;  // optional dense source, [S] x dsrc_sstride
@@ -115,9 +147,6 @@ struct StepArgs {
   int ez0 = 0, ez1 = INT_MAX, ex0 = 0, ex1 = INT_MAX;
   Inject inj;
   Extract ext;
-  int NZ = 0, NX = 0, LZ = 0;
-  int nshots = 0, ntz = 0, ntx = 0;
-  long sstride = 0;             // elements between shots in cur/prev/out
   float cz[kR] = {};            // w_k / dz^2
   float cx[kR] = {};            // w_k / dx^2
   int fs = -1;                  // padded row of a free surface (mode kModeFS), -1: none
@@ -187,6 +216,40 @@ struct Step2Args {
 // distinct buffers), kModeNu, kModeDF, kModeT2 | kModeDF or kModeDsrc | kModeDF
 // (plus kModeFS, added when p.a.fs >= 0); with a dense source no point sources
 hipError_t launch_step2(const Step2Args &p, int tile_x, int mode, hipStream_t st);
+
+// Up to kMaxSteps time steps per launch on small tiles (see kernels_step4.hip).
+// prev = u^{n-1} and cur = u^n are read with halos; out[s] (if given) receives
+// the field after step s, in buffers that the launch does not read.  t2[s]:
+// V (L u + f) of step s.  ds: mode kModeDsrc the dense source of step s, mode
+// kModeNu the e slots of times k + 1, k, k - 1, ... (steps + 2 of them), read
+// on the rows and columns ez0 .. ex1 only.  inj: one list per (tile, wave of
+// kWaves4) over the tile plus kHalo4 cells for every step, the sample of step s
+// at inj.t + s inj_dt.  ext samples the input field of step s at ext.t + s.
+constexpr int kMaxSteps = 4;
+constexpr int kHalo4 = 4 * (kMaxSteps - 1);       // cells around the tile computed in the first step
+constexpr int kTZ4 = 64 - 2 * kHalo4;             // output rows per tile
+constexpr int kWaves4 = 8;
+struct Step4Args {
+  const float *prev = nullptr, *cur = nullptr;
+  float *out[kMaxSteps] = {};
+  const unsigned short *lo_prev = nullptr, *lo_cur = nullptr;
+  unsigned short *lo_out[kMaxSteps] = {};
+  float *t2[kMaxSteps] = {};
+  const float *ds[kMaxSteps + 2] = {};
+  const float *V = nullptr, *gz = nullptr, *gx = nullptr;
+  long sstride = 0, t2_sstride = 0, ds_sstride = 0;
+  Inject inj;
+  int inj_dt = 1;
+  Extract ext;
+  int ez0 = 0, ez1 = INT_MAX, ex0 = 0, ex1 = INT_MAX;
+  int NZ = 0, NX = 0, LZ = 0;
+  int nshots = 0, ntz = 0, ntx = 0;
+  float cz[kR] = {}, cx[kR] = {};
+  int fs = -1;
+  int steps = 0;
+};
+// modes as launch_step2; tile_x 8 or 16
+hipError_t launch_step4(const Step4Args &p, int tile_x, int mode, hipStream_t st);
 
 // One job of a two-step multi-job launch: its step arguments (fields, times
 // and the step flag are filled in per launch from buf and the step counter),

@@ -56,12 +56,6 @@ struct Step2Tile<TX, true> : Step2Tile<TX, false> {
   unsigned short l1[Step2Tile<TX, false>::C1][Step2Tile<TX, false>::ROWS];
 };
 
-__device__ __forceinline__ float bf16_f32(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
-__device__ __forceinline__ unsigned short f32_bf16(float f) {   // round to nearest even (finite values)
-  const unsigned u = __float_as_uint(f);
-  return (unsigned short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-
 // u = g (2 (c + cl) - g (p + pl) + r) in FP64, split into FP32 hi and BF16 lo
 __device__ __forceinline__ float df_update(float g, float c, float cl, float pv, float pl, double r,
                                            unsigned short &lo) {
@@ -88,7 +82,8 @@ struct Sources {
   __device__ __forceinline__ void range(const Inject &inj, int logical, int w, const float *any) {
     const int *at = inj.ptr ? inj.ptr + (logical * kWaves + w) : reinterpret_cast<const int *>(any);
     i0 = at[0];
-    cnt = inj.ptr ? at[1] - i0 : 0;
+    const int i1 = at[1];                     // loaded either way
+    cnt = inj.ptr ? i1 - i0 : 0;
   }
   // entries b .. b + 63 of the list and their samples, one per lane
   __device__ __forceinline__ void fetch(const Inject &inj, int lane, int b) {
@@ -192,6 +187,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   // point sources of both steps; receivers e0 .. e1 - 1 of the tile
   [[maybe_unused]] Sources src1, src2;
   int e0, e1;
+  int2 first = {0, 0};                        // this thread's first receiver
   // offset of a dense source's row in column x: past the end (reads zero)
   // outside the rows and columns the source lives on
   [[maybe_unused]] const int vze = z >= a.ez0 && z < a.ez1 ? vzc : kOutOfRange;
@@ -314,8 +310,10 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
     {
       const int *at = a.ext.ptr ? a.ext.ptr + logical : reinterpret_cast<const int *>(a.gx);
       e0 = at[0];
-      e1 = a.ext.ptr ? at[1] : e0;
+      const int i1 = at[1];
+      e1 = a.ext.ptr ? i1 : e0;
     }
+    if (e0 + tid < e1) first = a.ext.ent[e0 + tid];
     if constexpr (PS) {
       src1.range(a.inj, logical, w, a.gx);
       src2.range(p.inj2, logical, w, a.gx);
@@ -343,7 +341,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
 
   // receivers of u^n (time t)
   for (int e = e0 + tid; e < e1; e += 256) {
-    const int2 en = a.ext.ent[e];
+    const int2 en = e == e0 + tid ? first : a.ext.ent[e];
     a.ext.out[(long)en.y * a.ext.stride_idx + a.ext.t] = sh.u0[(en.x >> 6) + 2 * kR][(en.x & 63) + 2 * kR];
   }
   if (extract_only) return;
@@ -472,7 +470,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
 
   // receivers of u^{n+1} (time t + 1)
   for (int e = e0 + tid; e < e1; e += 256) {
-    const int2 en = a.ext.ent[e];
+    const int2 en = e == e0 + tid ? first : a.ext.ent[e];
     a.ext.out[(long)en.y * a.ext.stride_idx + a.ext.t + 1] = sh.u1[(en.x >> 6) + kR][(en.x & 63) + 2 * kR];
   }
   if (!p.two) return;
@@ -572,8 +570,10 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   }
 }
 
+// (at width 32, the LDS of an extended-precision tile allows four workgroups
+// per CU: without the bound, mode Dsrc | DF takes one register too many)
 template <int TX, int MODE>
-__global__ void __launch_bounds__(256) k_step2(const Step2Args p) {
+__global__ void __launch_bounds__(256, (TX == 32 && (MODE & kModeDF) ? 4 : 1)) k_step2(const Step2Args p) {
   __shared__ Step2Tile<TX, (MODE & kModeDF) != 0> sh;
   const int total = p.a.ntz * p.a.ntx * p.a.nshots;
   const int per = (total + 7) >> 3;

@@ -42,7 +42,8 @@ struct fwime_ctx {
   double *host_red = nullptr;   // pinned: reduction results
   size_t host_red_n = 0;        // doubles it holds
   int tile_x = 32;
-  bool two_step = true;         // plain propagation two time steps per launch
+  bool two_step = true;         // two or four time steps per launch (else one)
+  int steps = 0;                // 2 or 4: steps per launch whatever the size (0: chosen by size)
   size_t tape_bytes = 0;        // device memory held by live tapes
   size_t last_arena_request = 0;
   hipStream_t capture = nullptr;          // private stream used only to record graphs
@@ -113,6 +114,8 @@ double cfl_limit(double dz, double dx) {
 struct Dims {
   int nz, nx, nb, nt, NZ, NX, LZ, ntz, ntx, TX;
   int ntz2;     // 56-row tiles of the two-step kernel
+  // tiles of the four-step kernel, used instead of the two-step one when T = 4
+  int ntz4, ntx4, TX4, T;
   long field;   // NX * LZ
 };
 
@@ -129,8 +132,32 @@ Dims make_dims(const fwime_grid_t *g, int tx) {
   d.ntz = (d.NZ + kTZ - 1) / kTZ;
   d.ntz2 = (d.NZ + kTZ2 - 1) / kTZ2;
   d.ntx = (d.NX + tx - 1) / tx;
+  d.ntz4 = (d.NZ + kTZ4 - 1) / kTZ4;
+  d.T = 2;
+  d.TX4 = d.ntx4 = 0;
   d.field = (long)d.NX * d.LZ;
   return d;
+}
+
+// Steps per launch of the two-step path for batches of S shots.  A launch of
+// few workgroups costs its latency, not its work: four steps per launch then
+// take little longer than two.  The bounds are in two-step workgroups (56 x 32
+// cells of every shot); the extended-precision kernels (df), with more than
+// twice the instructions per cell, fill the device sooner.  Measured over 400
+// steps, two against four per launch: modeling 36 workgroups 1.65 / 0.86 ms,
+// 288 1.79 / 1.48, 330 1.91 / 1.85, 432 1.92 / 2.13; gradient 288 9.9 / 8.6,
+// 440 11.6 / 13.1; Born pair 36 11.1 / 5.9, 144 12.2 / 11.2, 220 13.1 / 16.3.
+// Tiles are eight columns wide while one round of them fits the 256 compute
+// units (one 100 x 200 shot: 0.86 against 0.93 ms; two: 1.01 against 0.96).
+constexpr int kStep4MaxTiles = 320, kStep4MaxTilesDF = 160, kStep4MaxNarrow = 256;
+
+void choose_steps(const fwime_ctx_t *ctx, Dims &d, int S, bool df) {
+  if (!ctx->two_step) return;
+  const long tiles = (long)d.ntz2 * d.ntx * S;
+  if (ctx->steps ? ctx->steps != 4 : tiles > (df ? kStep4MaxTilesDF : kStep4MaxTiles)) return;
+  d.T = 4;
+  d.TX4 = (long)d.ntz4 * ((d.NX + 7) / 8) * S <= kStep4MaxNarrow ? 8 : 16;
+  d.ntx4 = (d.NX + d.TX4 - 1) / d.TX4;
 }
 
 // ---------------------------------------------------------------------------
@@ -444,6 +471,44 @@ HostTables build_tables2(const Dims &d, const fwime_geom_t *geo, int s0, int S) 
   return t;
 }
 
+// Four-step tiling: one list per (tile, wave) for every step, over the tile plus
+// the kHalo4 cells around it that the first step computes; rext per tile.
+HostTables build_tables4(const Dims &d, const fwime_geom_t *geo, int s0, int S) {
+  HostTables t;
+  const int W = (d.TX4 + 2 * kHalo4) / kWaves4;
+  const long ntiles = (long)d.ntz4 * d.ntx4 * S;
+  auto tile_of = [&](int s, int txi, int tzi) { return tile_index(txi, tzi, s, d.ntz4, d.ntx4, S); };
+  std::vector<std::pair<long, int2>> src, rext, rinj;
+  auto add_inject = [&](int s, int px, int pz, int idx, std::vector<std::pair<long, int2>> &l) {
+    const int rx = (kHalo4 + d.TX4 - 1) / d.TX4, txi = px / d.TX4, tzi = pz / kTZ4;   // the halo reaches rx tiles
+    for (int tx = std::max(0, txi - rx); tx <= std::min(d.ntx4 - 1, txi + rx); ++tx)
+      for (int tz = std::max(0, tzi - 1); tz <= std::min(d.ntz4 - 1, tzi + 1); ++tz) {
+        const int jj = px - (tx * d.TX4 - kHalo4), lane = pz - (tz * kTZ4 - kHalo4);
+        if (jj < 0 || jj >= d.TX4 + 2 * kHalo4 || lane < 0 || lane >= 64) continue;
+        l.push_back({tile_of(s, tx, tz) * kWaves4 + jj / W, make_int2(((jj % W) << 6) | lane, idx)});
+      }
+  };
+  for (int s = 0; s < S; ++s) {
+    const int sg = s0 + s;
+    add_inject(s, geo->src_ix[sg] + d.nb, geo->src_iz[sg] + d.nb, s, src);
+    for (int r = 0; r < geo->nrec; ++r) {
+      const long ir = (long)sg * geo->nrec + r;
+      const int il = s * geo->nrec + r;
+      const int px = geo->rec_ix[ir] + d.nb, pz = geo->rec_iz[ir] + d.nb;
+      const int txi = px / d.TX4, tzi = pz / kTZ4;
+      rext.push_back({tile_of(s, txi, tzi), make_int2(((px - txi * d.TX4) << 6) | (pz - tzi * kTZ4), il)});
+      add_inject(s, px, pz, il, rinj);
+      t.cells.push_back(px * d.LZ + pz);
+    }
+  }
+  csr_build(t.src_ptr, t.src_ent, ntiles * kWaves4, src);
+  csr_build(t.rext_ptr, t.rext_ent, ntiles, rext);
+  csr_build(t.rinj_ptr, t.rinj_ent, ntiles * kWaves4, rinj);
+  mark_repeats(t.src_ptr, t.src_ent);
+  mark_repeats(t.rinj_ptr, t.rinj_ent);
+  return t;
+}
+
 size_t tables_ints(const HostTables &t) {
   return t.src_ptr.size() + t.rext_ptr.size() + t.rinj_ptr.size() + t.cells.size() + t.src1_ptr.size() +
          t.rinj1_ptr.size() +
@@ -462,7 +527,9 @@ TableSet build_table_set(const Dims &d, const fwime_geom_t *geo, const std::vect
                          bool two_step = false) {
   TableSet ts;
   for (auto &b : batches)
-    ts.host.push_back(two_step ? build_tables2(d, geo, b.first, b.second) : build_tables(d, geo, b.first, b.second));
+    ts.host.push_back(!two_step    ? build_tables(d, geo, b.first, b.second)
+                      : d.T == 4 ? build_tables4(d, geo, b.first, b.second)
+                                 : build_tables2(d, geo, b.first, b.second));
   return ts;
 }
 
@@ -607,10 +674,10 @@ void with_rec_extract(StepArgs &a, const DevTables &t, float *data, int nt, int 
   a.ext.t = n;
 }
 
-// Four field buffers of one batch for the two-step kernel: prev = f[i],
-// cur = f[i + 1]; a launch of k steps writes f[i + 2] (and f[i + 3]) and
-// advances i by k.  Neither output buffer is read by that launch, and after
-// it u^{n-1}, u^n, u^{n+1}, u^{n+2} are all still in memory.
+// Four field buffers of one batch: prev = f[i], cur = f[i + 1]; a launch
+// writes the last two fields it forms (its only one) to f[i + 2] and f[i + 3]
+// (f[i + 2]) and advances i by as many.  No output buffer is read by that
+// launch, and after it u^{n-1} and u^n are still in memory.
 template <class T>
 struct Ring4T {
   T *f[4];
@@ -621,24 +688,34 @@ struct Ring4T {
   T *at(int k) const { return f[(i + k) & 3]; }
   T *prev() const { return at(0); }
   T *cur() const { return at(1); }
-  void advance(int k) { i += k; }
+  // outputs of a launch of k steps
+  void outputs(T **out, int k) const {
+    for (int q = 0; q < k; ++q) out[q] = q < k - 2 ? nullptr : at(q - std::max(0, k - 2) + 2);
+  }
+  void advance(int k) { i += std::min(k, 2); }
 };
 using Ring4 = Ring4T<float>;
 using Ring4L = Ring4T<unsigned short>;   // BF16 low parts of an extended-precision field
 
-Step2Args step2_args(const Common &c, const Ring4 &f, int S, long sstride, int k) {
-  Step2Args p;
-  p.a = batch_args(c, S, sstride);
-  p.a.ntz = c.d.ntz2;
-  p.a.prev = f.prev();
-  p.a.cur = f.cur();
-  p.a.out = f.at(2);
-  p.out2 = k == 2 ? f.at(3) : nullptr;
-  p.two = k == 2;
-  return p;
+// One launch of up to d.T time steps, whichever kernel runs it: fields, outputs
+// and dense sources as in Step4Args, and what is injected and recorded.
+struct Steps : Step4Args {
+  const DevTables *tab = nullptr;        // the batch's lists
+  enum { kNone, kSource, kReceivers } inject = kNone;
+};
+
+// point sources, from time n on
+void with_src2(Steps &q, const DevTables &t, const float *wav_b, const fwime_grid_t *g, int n) {
+  q.tab = &t;
+  q.inject = Steps::kSource;
+  q.inj.val = wav_b;
+  q.inj.stride_idx = g->nt;
+  q.inj.t = n;
+  q.inj.scale = (float)(1.0 / (g->dx * g->dz));
+  q.inj_dt = 1;
 }
 
-// point sources: step-1 list at time n, step-2 list at time n + 1
+// the same for a two-step job descriptor: step-1 list at time n, step-2 list at time n + 1
 void with_src2(Step2Args &p, const DevTables &t, const float *wav_b, const fwime_grid_t *g, int n) {
   with_src_w(p.a, t, wav_b, g, n);
   p.a.inj.ptr = t.src1_ptr;
@@ -649,60 +726,156 @@ void with_src2(Step2Args &p, const DevTables &t, const float *wav_b, const fwime
   p.inj2.t = n + 1;
 }
 
-// receiver injection (adjoint sources): time k1 of `data` in step 1, k2 in
-// step 2 (k2 = k1 - 1 when the recursion runs backwards in time)
-void with_rec_inject2(Step2Args &p, const DevTables &t, const float *data, int nt, int k1, int k2) {
-  with_rec_inject(p.a, t, data, nt, k1);
-  p.a.inj.ptr = t.rinj1_ptr;
-  p.a.inj.ent = t.rinj1_ent;
-  p.inj2 = p.a.inj;
-  p.inj2.ptr = t.rinj_ptr;
-  p.inj2.ent = t.rinj_ent;
-  p.inj2.t = k2;
+// receiver injection (adjoint sources): times k, k - 1, ... of `data`
+void with_rec_inject2(Steps &q, const DevTables &t, const float *data, int nt, int k) {
+  q.tab = &t;
+  q.inject = Steps::kReceivers;
+  q.inj.val = data;
+  q.inj.stride_idx = nt;
+  q.inj.t = k;
+  q.inj.scale = 1.f;
+  q.inj_dt = -1;
 }
 
-// Advances ring f over the steps n0 .. n1 - 1 forward in time: two steps per
-// launch, one in the last launch when the count is odd.  setup(p, n, k) adds
-// the step-specific arguments of the launch that starts at step n.
-// With lo != nullptr the field is carried in extended precision (mode gets
-// kModeDF) and lo rotates with f.
-template <class Setup>
-int march2(fwime_ctx_t *ctx, const Common &c, Ring4 &f, int S, int n0, int n1, int mode, Setup setup,
-           hipStream_t st, Ring4L *lo = nullptr) {
-  for (int n = n0; n < n1;) {
-    const int k = std::min(2, n1 - n);
-    Step2Args p = step2_args(c, f, S, c.d.field, k);
-    if (lo) {
-      p.lo_prev = lo->prev();
-      p.lo_cur = lo->cur();
-      p.lo_out = lo->at(2);
-      p.lo_out2 = k == 2 ? lo->at(3) : nullptr;
-    }
-    setup(p, n, k);
-    HIPCHK(launch_step2(p, c.d.TX, lo ? (mode | kModeDF) : mode, st));
-    f.advance(k);
-    if (lo) lo->advance(k);
-    n += k;
-  }
-  return FWIME_OK;
+// records the fields of times n, n + 1, ... that the launch reads
+void with_rec_extract(Steps &q, const DevTables &t, float *data, int nt, int n) {
+  q.tab = &t;
+  q.ext.out = data;
+  q.ext.stride_idx = nt;
+  q.ext.t = n;
 }
 
-// T2 output of a two-step launch: slot `first` for its first step, the next
-// slot (`slot` elements on) for its second; per-shot stride sstride
-void with_t2(Step2Args &p, float *first, long slot, int k, long sstride) {
-  p.a.t2 = first;
-  p.t2b = k == 2 ? first + slot : nullptr;
-  p.a.t2_sstride = sstride;
+// T2 output: slot `first` for the first step, the next slots (`slot` elements
+// on) for the others; per-shot stride sstride
+void with_t2(Steps &q, float *first, long slot, int k, long sstride) {
+  for (int i = 0; i < k; ++i) q.t2[i] = first + i * slot;
+  q.t2_sstride = sstride;
 }
 
 // rows and columns on which the offset scatter (or, with H = 0, the lag
 // scatter) writes its output: the model's rows, the model's columns and the H
 // columns on either side that lie on the grid
-void with_dense_range(StepArgs &a, const ExtGeom &eg, int H) {
-  a.ez0 = eg.nb;
-  a.ez1 = eg.nb + eg.nz;
-  a.ex0 = std::max(0, eg.nb - H);
-  a.ex1 = std::min(eg.NX, eg.nb + eg.nx + H);
+void with_dense_range(Steps &q, const ExtGeom &eg, int H) {
+  q.ez0 = eg.nb;
+  q.ez1 = eg.nb + eg.nz;
+  q.ex0 = std::max(0, eg.nb - H);
+  q.ex1 = std::min(eg.NX, eg.nb + eg.nx + H);
+}
+
+// dense source: slot `first` for the first step, the next slots for the others
+void with_dsrc2(Steps &q, const float *first, long slot, int k, long sstride) {
+  for (int i = 0; i < k; ++i) q.ds[i] = first + i * slot;
+  q.ds_sstride = sstride;
+}
+
+// transposed second time difference of e as the source of the steps that read
+// times k, k - 1, ...; slot(t): the e slot of time t
+template <class Slot>
+void with_nu(Steps &q, Slot slot, int k, int kk, long sstride) {
+  for (int i = 0; i < kk + 2; ++i) q.ds[i] = slot(k + 1 - i);
+  q.ds_sstride = sstride;
+}
+
+// Launches k steps for S shots.
+hipError_t launch_steps(const Common &c, Steps &q, int S, long sstride, int k, int mode, hipStream_t st) {
+  const Dims &d = c.d;
+  const StepArgs &b = c.base;
+  if (d.T == 4) {
+    q.V = b.V;
+    q.gz = b.gz;
+    q.gx = b.gx;
+    q.NZ = b.NZ;
+    q.NX = b.NX;
+    q.LZ = b.LZ;
+    q.fs = b.fs;
+    std::copy(b.cz, b.cz + kR, q.cz);
+    std::copy(b.cx, b.cx + kR, q.cx);
+    q.nshots = S;
+    q.sstride = sstride;
+    q.ntz = d.ntz4;
+    q.ntx = d.ntx4;
+    q.steps = k;
+    if (q.inject != Steps::kNone) {
+      q.inj.ptr = q.inject == Steps::kSource ? q.tab->src_ptr : q.tab->rinj_ptr;
+      q.inj.ent = q.inject == Steps::kSource ? q.tab->src_ent : q.tab->rinj_ent;
+    }
+    if (q.ext.out) {
+      q.ext.ptr = q.tab->rext_ptr;
+      q.ext.ent = q.tab->rext_ent;
+    }
+    return launch_step4(q, d.TX4, mode, st);
+  }
+  Step2Args p;
+  p.a = batch_args(c, S, sstride);
+  p.a.ntz = d.ntz2;
+  p.a.prev = q.prev;
+  p.a.cur = q.cur;
+  p.a.out = q.out[0];
+  p.out2 = q.out[1];
+  p.two = k == 2;
+  p.lo_prev = q.lo_prev;
+  p.lo_cur = q.lo_cur;
+  p.lo_out = q.lo_out[0];
+  p.lo_out2 = q.lo_out[1];
+  p.a.t2 = q.t2[0];
+  p.t2b = q.t2[1];
+  p.a.t2_sstride = q.t2_sstride;
+  if (mode & kModeDsrc) {
+    p.a.dsrc = q.ds[0];
+    p.dsrc2 = q.ds[1];
+    p.a.dsrc_sstride = q.ds_sstride;
+  } else if (mode & kModeNu) {
+    p.a.nu = NuSource{q.ds[2], q.ds[1], q.ds[0], q.ds_sstride};
+    if (k == 2) p.nu2 = NuSource{q.ds[3], q.ds[2], q.ds[1], q.ds_sstride};
+  }
+  p.a.ez0 = q.ez0;
+  p.a.ez1 = q.ez1;
+  p.a.ex0 = q.ex0;
+  p.a.ex1 = q.ex1;
+  if (q.inject != Steps::kNone) {
+    const bool src = q.inject == Steps::kSource;
+    p.a.inj = p.inj2 = q.inj;
+    p.a.inj.ptr = src ? q.tab->src1_ptr : q.tab->rinj1_ptr;
+    p.a.inj.ent = src ? q.tab->src1_ent : q.tab->rinj1_ent;
+    p.inj2.ptr = src ? q.tab->src_ptr : q.tab->rinj_ptr;
+    p.inj2.ent = src ? q.tab->src_ent : q.tab->rinj_ent;
+    p.inj2.t = q.inj.t + q.inj_dt;
+  }
+  if (q.ext.out) {
+    p.a.ext = q.ext;
+    p.a.ext.ptr = q.tab->rext_ptr;
+    p.a.ext.ent = q.tab->rext_ent;
+  }
+  return launch_step2(p, d.TX, mode, st);
+}
+
+// Advances ring f over the steps n0 .. n1 - 1 forward in time, d.T steps per
+// launch and what is left in the last.  setup(q, n, k) adds the arguments of
+// the launch that starts at step n and takes k steps.
+// With lo != nullptr the field is carried in extended precision (mode gets
+// kModeDF) and lo rotates with f.  Counts its launches in *launches.
+template <class Setup>
+int march2(fwime_ctx_t *ctx, const Common &c, Ring4 &f, int S, int n0, int n1, int mode, Setup setup,
+           hipStream_t st, Ring4L *lo = nullptr, long *launches = nullptr) {
+  for (int n = n0; n < n1;) {
+    const int k = std::min(c.d.T, n1 - n);
+    Steps q;
+    q.prev = f.prev();
+    q.cur = f.cur();
+    f.outputs(q.out, k);
+    if (lo) {
+      q.lo_prev = lo->prev();
+      q.lo_cur = lo->cur();
+      lo->outputs(q.lo_out, k);
+    }
+    setup(q, n, k);
+    HIPCHK(launch_steps(c, q, S, c.d.field, k, lo ? (mode | kModeDF) : mode, st));
+    f.advance(k);
+    if (lo) lo->advance(k);
+    n += k;
+    if (launches) ++*launches;
+  }
+  return FWIME_OK;
 }
 
 // u^{-1} = u^0 = 0: the two buffers of a four-buffer ring that the first launch reads
@@ -726,14 +899,6 @@ hipError_t zero_end(unsigned short *ring, long ring_stride, int R, const Dims &d
                                               d.field / 2, st);
 }
 
-// dense source of a two-step launch: slot `first` for its first step, the
-// next slot (`slot` elements on) for its second; per-shot stride sstride
-void with_dsrc2(Step2Args &p, const float *first, long slot, int k, long sstride) {
-  p.a.dsrc = first;
-  p.dsrc2 = k == 2 ? first + slot : nullptr;
-  p.a.dsrc_sstride = sstride;
-}
-
 // BF16 arrays copied as 32-bit words (fields hold an even number of cells)
 hipError_t copy_lo(unsigned short *dst, long dst_sstride, const unsigned short *src, long src_sstride, int S, long n,
                    hipStream_t st) {
@@ -742,32 +907,29 @@ hipError_t copy_lo(unsigned short *dst, long dst_sstride, const unsigned short *
 
 // Adjoint recursion over a ring of R field slots (slot of time k: k % R),
 // from time k = k1 down to k0 + 1, producing the fields of times k1 - 1 ..
-// k0: two steps per launch.  setup(p, k, kk) adds the sources of the launch
-// that starts at time k.
+// k0: d.T steps per launch (no more than the slots a launch does not read).
+// setup(q, k, kk) adds the sources of the launch that starts at time k and
+// takes kk steps.
 // With lo != nullptr (a BF16 ring of the same shape) the field is carried in
 // extended precision (mode gets kModeDF).
 template <class Setup>
 int march2_back_ring(fwime_ctx_t *ctx, const Common &c, float *ring, long ring_stride, int R, int S, int k0, int k1,
                      int mode, Setup setup, hipStream_t st, unsigned short *lo = nullptr) {
   const long F = c.d.field;
+  const int most = std::min(c.d.T, R - 2);
   for (int k = k1; k >= k0 + 1;) {
-    const int kk = (k - 2 >= k0) ? 2 : 1;
-    Step2Args p;
-    p.a = batch_args(c, S, ring_stride);
-    p.a.ntz = c.d.ntz2;
-    p.a.cur = ring + (long)(k % R) * F;
-    p.a.prev = ring + (long)((k + 1) % R) * F;
-    p.a.out = ring + (long)((k - 1) % R) * F;
-    p.out2 = kk == 2 ? ring + (long)((k - 2) % R) * F : nullptr;
-    p.two = kk == 2;
+    const int kk = std::min(most, k - k0);
+    Steps q;
+    q.cur = ring + (long)(k % R) * F;
+    q.prev = ring + (long)((k + 1) % R) * F;
+    for (int i = 0; i < kk; ++i) q.out[i] = ring + (long)((k - 1 - i) % R) * F;
     if (lo) {
-      p.lo_cur = lo + (long)(k % R) * F;
-      p.lo_prev = lo + (long)((k + 1) % R) * F;
-      p.lo_out = lo + (long)((k - 1) % R) * F;
-      p.lo_out2 = kk == 2 ? lo + (long)((k - 2) % R) * F : nullptr;
+      q.lo_cur = lo + (long)(k % R) * F;
+      q.lo_prev = lo + (long)((k + 1) % R) * F;
+      for (int i = 0; i < kk; ++i) q.lo_out[i] = lo + (long)((k - 1 - i) % R) * F;
     }
-    setup(p, k, kk);
-    HIPCHK(launch_step2(p, c.d.TX, lo ? (mode | kModeDF) : mode, st));
+    setup(q, k, kk);
+    HIPCHK(launch_steps(c, q, S, ring_stride, kk, lo ? (mode | kModeDF) : mode, st));
     k -= kk;
   }
   return FWIME_OK;
@@ -778,7 +940,7 @@ int march2_back_lambda(fwime_ctx_t *ctx, const Common &c, float *ring, long ring
                        int k1, const DevTables &t, const float *data, int nt, hipStream_t st,
                        unsigned short *lo = nullptr) {
   return march2_back_ring(ctx, c, ring, ring_stride, R, S, k0, k1, kModePlain,
-                          [&](Step2Args &p, int k, int) { with_rec_inject2(p, t, data, nt, k, k - 1); }, st, lo);
+                          [&](Steps &q, int k, int) { with_rec_inject2(q, t, data, nt, k); }, st, lo);
 }
 
 int choose_batch(fwime_ctx_t *ctx, long per_shot_bytes, size_t fixed_bytes, int nshots) {
@@ -941,6 +1103,9 @@ int fwime_ctx_create(int device, size_t hbm_budget_bytes, fwime_ctx_t **out) {
   // FWIME_STEP1=1: one time step per launch everywhere (same results, bit for bit)
   const char *s1 = std::getenv("FWIME_STEP1");
   if (s1 && std::atoi(s1) != 0) ctx->two_step = false;
+  // FWIME_STEPS=2 or 4: that many per launch at every size (same results, bit for bit)
+  const char *sn = std::getenv("FWIME_STEPS");
+  if (sn && (std::atoi(sn) == 2 || std::atoi(sn) == 4)) ctx->steps = std::atoi(sn);
   *out = ctx;
   return FWIME_OK;
 }
@@ -1025,6 +1190,7 @@ int fwime_model(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const
   const long per_shot = nf * d.field * 4 + (long)geo->nrec * 64;
   const int S = choose_batch(ctx, per_shot, (size_t)d.field * 8, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, false);
   TableSet ts = build_table_set(d, geo, batches, two);
 
   float *fields = nullptr;
@@ -1044,19 +1210,15 @@ int fwime_model(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const
     const int s0 = batches[bi].first, Sb = batches[bi].second;
     const DevTables &t = ts.dev[bi];
     float *out_b = data + (long)s0 * geo->nrec * g->nt;
-    launches += two ? g->nt / 2 : g->nt - 1;
+    if (!two) launches += g->nt - 1;
     if (two) {
       HIPCHK(zero_start(fields, d, Sb, st));
       Ring4 f(fields, d.field * Sb);
-      for (int n = 0; n < g->nt - 1;) {
-        const int k = std::min(2, g->nt - 1 - n);
-        Step2Args p = step2_args(c, f, Sb, d.field, k);
+      rc = march2(ctx, c, f, Sb, 0, g->nt - 1, kModePlain, [&](Steps &p, int n, int) {
         with_src2(p, t, geo->wavelet + (long)s0 * g->nt, g, n);
-        with_rec_extract(p.a, t, out_b, g->nt, n);
-        HIPCHK(launch_step2(p, d.TX, kModePlain, st));
-        f.advance(k);
-        n += k;
-      }
+        with_rec_extract(p, t, out_b, g->nt, n);
+      }, st, nullptr, &launches);
+      if (rc) return rc;
       HIPCHK(launch_gather(f.cur(), d.field, t.cells, Sb, geo->nrec, out_b, g->nt, g->nt - 1, st));
       continue;
     }
@@ -1139,6 +1301,7 @@ static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   const int KC = Sh ? hist_seg_len(g->nt, Sh) : 16;
   const int S = Sh ? Sh : choose_batch(ctx, per_shot(KC), fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, true);
   TableSet ts = build_table_set(d, geo, batches, two);
 
   float *coef = nullptr, *pairs = nullptr, *t2 = nullptr, *sc = nullptr;
@@ -1176,7 +1339,7 @@ static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
         // background in extended precision: its T2 term is the scattering source
         const long bg_stride = (long)(g->nt - 1) * d.field;
         if (!bg) {
-          rc = march2(ctx, c, fu, Sb, c0, c0 + nk, kModeT2, [&](Step2Args &p, int n, int k) {
+          rc = march2(ctx, c, fu, Sb, c0, c0 + nk, kModeT2, [&](Steps &p, int n, int k) {
             with_t2(p, t2 + (long)(n - c0) * d.field, d.field, k, chunk_stride);
             with_src2(p, t, wav_b, g, n);
           }, st, &lu);
@@ -1186,10 +1349,10 @@ static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
                                   bg ? bg_stride : chunk_stride, sc, d.field, chunk_stride, Sb, nk, st));
         // the scattered field in extended precision too: its FP32 rounding
         // would otherwise dominate the inconsistency of the B~ / B~^T pair
-        rc = march2(ctx, c, fw, Sb, c0, c0 + nk, kModeDsrc, [&](Step2Args &p, int n, int k) {
+        rc = march2(ctx, c, fw, Sb, c0, c0 + nk, kModeDsrc, [&](Steps &p, int n, int k) {
           with_dsrc2(p, sc + (long)(n - c0) * d.field, d.field, k, chunk_stride);
-          with_dense_range(p.a, eg, eg.H);
-          with_rec_extract(p.a, t, out_b, g->nt, n);
+          with_dense_range(p, eg, eg.H);
+          with_rec_extract(p, t, out_b, g->nt, n);
         }, st, &lw);
         if (rc) return rc;
       }
@@ -1261,12 +1424,10 @@ static int tau_background(fwime_ctx_t *ctx, const Common &c, const fwime_grid_t 
   Ring4 fu(pairs, d.field * Sb);
   Ring4L lu(lows, d.field * Sb);
   const float *wav_b = geo->wavelet + (long)s0 * g->nt;
-  int rc = march2(ctx, c, fu, Sb, 0, g->nt - 1, kModeT2, [&](Step2Args &p, int n, int k) {
-    p.a.t2 = hist + (long)n * d.field;
-    p.t2b = k == 2 ? hist + (long)(n + 1) * d.field : nullptr;
-    p.a.t2_sstride = hstride;
+  int rc = march2(ctx, c, fu, Sb, 0, g->nt - 1, kModeT2, [&](Steps &p, int n, int k) {
+    with_t2(p, hist + (long)n * d.field, d.field, k, hstride);
     with_src2(p, t, wav_b, g, n);
-    if (rec_out) with_rec_extract(p.a, t, rec_out, g->nt, n);
+    if (rec_out) with_rec_extract(p, t, rec_out, g->nt, n);
   }, st, &lu);
   if (rc || !rec_out) return rc;
   HIPCHK(launch_gather(fu.cur(), d.field, t.cells, Sb, geo->nrec, rec_out, g->nt, g->nt - 1, st));
@@ -1295,6 +1456,7 @@ int fwime_born_ext_tau_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
   const size_t fixed = (size_t)d.field * 8 + (size_t)ntau * d.nx * d.nz * 4;
   const int S = choose_batch(ctx, per_shot, fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, true);
   TableSet ts = build_table_set(d, geo, batches, true);
 
   float *coef = nullptr, *pairs = nullptr, *hist = nullptr, *sc = nullptr;
@@ -1324,10 +1486,10 @@ int fwime_born_ext_tau_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
     float *wp = pairs + 4 * d.field * Sb;
     HIPCHK(zero_start(wp, d, Sb, st));
     Ring4 fw(wp, d.field * Sb);
-    rc = march2(ctx, c, fw, Sb, 0, ns, kModeDsrc, [&](Step2Args &p, int n, int k) {
+    rc = march2(ctx, c, fw, Sb, 0, ns, kModeDsrc, [&](Steps &p, int n, int k) {
       with_dsrc2(p, sc + (long)n * d.field, d.field, k, hstride);
-      with_dense_range(p.a, eg, 0);
-      with_rec_extract(p.a, t, out_b, g->nt, n);
+      with_dense_range(p, eg, 0);
+      with_rec_extract(p, t, out_b, g->nt, n);
     }, st);
     if (rc) return rc;
     HIPCHK(launch_gather(fw.cur(), d.field, t.cells, Sb, geo->nrec, out_b, g->nt, g->nt - 1, st));
@@ -1357,6 +1519,7 @@ int fwime_born_ext_tau_adj(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
   const size_t fixed = (size_t)d.field * 8;
   const int S = choose_batch(ctx, per_shot, fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, true);
   TableSet ts = build_table_set(d, geo, batches, true);
 
   float *pairs = nullptr, *hist = nullptr, *lam = nullptr;
@@ -1452,6 +1615,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
                         (long)geo->nrec * 64;
   const int S = Sh ? Sh : choose_batch(ctx, per_shot, fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, true);
   TableSet ts = build_table_set(d, geo, batches, two);
 
   float *pairs = nullptr, *ckpt = nullptr, *t2 = nullptr, *ring = nullptr;
@@ -1490,7 +1654,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
     const float *data_b = data + (long)s0 * geo->nrec * g->nt;
     if (two) {
       const float *wav_b = geo->wavelet + (long)s0 * g->nt;
-      auto src = [&](Step2Args &p, int n, int) { with_src2(p, t, wav_b, g, n); };
+      auto src = [&](Steps &p, int n, int) { with_src2(p, t, wav_b, g, n); };
       if (cache && !keep) {                     // this batch's shots in the cached checkpoints
         ckpt = cache->ckpt + (long)s0 * ck_stride;
         ckpt_lo = cache->ckpt_lo + (long)s0 * ck_stride;
@@ -1504,7 +1668,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
       // with a whole history it stores T2 u_n of every step instead
       float *hist_b = keep ? hist + (own_hist ? 0L : s0 * hist_stride) : nullptr;
       if (keep && !(cache && cache->valid)) {
-        rc = march2(ctx, c, fu, Sb, 0, g->nt - 1, kModeT2, [&](Step2Args &p, int n, int k) {
+        rc = march2(ctx, c, fu, Sb, 0, g->nt - 1, kModeT2, [&](Steps &p, int n, int k) {
           with_t2(p, hist_b + (long)n * d.field, d.field, k, hist_stride);
           with_src2(p, t, wav_b, g, n);
         }, st, &lu);
@@ -1539,10 +1703,8 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
         HIPCHK(launch_copy_fields(wu.cur(), d.field, ckpt + (2L * j + 1) * d.field, ck_stride, Sb, d.field, st));
         HIPCHK(copy_lo(wl.prev(), d.field, ckpt_lo + (2L * j) * d.field, ck_stride, Sb, d.field, st));
         HIPCHK(copy_lo(wl.cur(), d.field, ckpt_lo + (2L * j + 1) * d.field, ck_stride, Sb, d.field, st));
-        rc = march2(ctx, c, wu, Sb, n0, n1, kModeT2, [&](Step2Args &p, int n, int k) {
-          p.a.t2 = t2 + (long)(n - n0) * d.field;
-          p.t2b = k == 2 ? t2 + (long)(n - n0 + 1) * d.field : nullptr;
-          p.a.t2_sstride = t2_stride;
+        rc = march2(ctx, c, wu, Sb, n0, n1, kModeT2, [&](Steps &p, int n, int k) {
+          with_t2(p, t2 + (long)(n - n0) * d.field, d.field, k, t2_stride);
           with_src2(p, t, wav_b, g, n);
         }, st, &wl);
         if (rc) return rc;
@@ -1669,19 +1831,19 @@ int grad_forward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, con
         HIPCHK(launch_copy_fields(dck + (2L * j + 1) * d.field, pl.ck_stride, fw.cur(), d.field, Sb, d.field, st));
       }
       float *t2u = wk.t2u + pl.t2_off(d, n0), *t2d = wk.t2d + pl.t2_off(d, n0);
-      rc = march2(ctx, c, fu, Sb, n0, n1, kModeT2, [&](Step2Args &p, int n, int k) {
+      rc = march2(ctx, c, fu, Sb, n0, n1, kModeT2, [&](Steps &p, int n, int k) {
         with_t2(p, t2u + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
         with_src2(p, t, wav_b, g, n);
-        with_rec_extract(p.a, t, drec, g->nt, n);
+        with_rec_extract(p, t, drec, g->nt, n);
       }, st);
       if (rc) return rc;
       HIPCHK(launch_ext_scatter(coef, eg, +1, t2u, d.field, pl.seg_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
                                 st));
-      rc = march2(ctx, c, fw, Sb, n0, n1, pl.hist ? kModeT2 | kModeDsrc : kModeDsrc, [&](Step2Args &p, int n, int k) {
+      rc = march2(ctx, c, fw, Sb, n0, n1, pl.hist ? kModeT2 | kModeDsrc : kModeDsrc, [&](Steps &p, int n, int k) {
         with_dsrc2(p, wk.er + (long)(n - n0) * d.field, d.field, k, pl.ring_stride);
-        with_dense_range(p.a, eg, eg.H);
+        with_dense_range(p, eg, eg.H);
         if (pl.hist) with_t2(p, t2d + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
-        with_rec_extract(p.a, t, ddrec, g->nt, n);
+        with_rec_extract(p, t, ddrec, g->nt, n);
       }, st);
       if (rc) return rc;
     }
@@ -1764,18 +1926,17 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
       HIPCHK(launch_copy_fields(wu.cur(), d.field, uck + (2L * j + 1) * d.field, pl.ck_stride, Sb, d.field, st));
       HIPCHK(launch_copy_fields(ww.prev(), d.field, dck + (2L * j) * d.field, pl.ck_stride, Sb, d.field, st));
       HIPCHK(launch_copy_fields(ww.cur(), d.field, dck + (2L * j + 1) * d.field, pl.ck_stride, Sb, d.field, st));
-      rc = march2(ctx, c, wu, Sb, n0, n1, kModeT2, [&](Step2Args &p, int n, int k) {
+      rc = march2(ctx, c, wu, Sb, n0, n1, kModeT2, [&](Steps &p, int n, int k) {
         with_t2(p, wk.t2u + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
         with_src2(p, t, wav_b, g, n);
       }, st);
       if (rc) return rc;
       HIPCHK(launch_ext_scatter(coef, eg, +1, wk.t2u, d.field, pl.seg_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
                                 st, 0, 0, R, n0));
-      rc = march2(ctx, c, ww, Sb, n0, n1, kModeT2 | kModeDsrc, [&](Step2Args &p, int n, int k) {
-        p.a.dsrc = er_slot(n);
-        p.dsrc2 = k == 2 ? er_slot(n + 1) : nullptr;
-        p.a.dsrc_sstride = pl.ring_stride;
-        with_dense_range(p.a, eg, eg.H);
+      rc = march2(ctx, c, ww, Sb, n0, n1, kModeT2 | kModeDsrc, [&](Steps &p, int n, int k) {
+        for (int i = 0; i < k; ++i) p.ds[i] = er_slot(n + i);
+        p.ds_sstride = pl.ring_stride;
+        with_dense_range(p, eg, eg.H);
         with_t2(p, wk.t2d + (long)(n - n0) * d.field, d.field, k, pl.seg_stride);
       }, st);
       if (rc) return rc;
@@ -1825,10 +1986,9 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
     HIPCHK(launch_ext_scatter(coef, eg, -1, wk.lam, d.field, pl.ring_stride, wk.er, d.field, pl.ring_stride, Sb, nk,
                               st, R, n0, R, n0));
     if (two) {
-      rc = march2_back_ring(ctx, c, wk.rho, pl.ring_stride, R, Sb, n0, n1, kModeNu, [&](Step2Args &p, int k, int kk) {
-        p.a.nu = NuSource{er_slot(k - 1), er_slot(k), er_slot(k + 1), pl.ring_stride};
-        if (kk == 2) p.nu2 = NuSource{er_slot(k - 2), er_slot(k - 1), er_slot(k), pl.ring_stride};
-        with_dense_range(p.a, eg, eg.H);
+      rc = march2_back_ring(ctx, c, wk.rho, pl.ring_stride, R, Sb, n0, n1, kModeNu, [&](Steps &p, int k, int kk) {
+        with_nu(p, er_slot, k, kk, pl.ring_stride);
+        with_dense_range(p, eg, eg.H);
       }, st);
       if (rc) return rc;
     } else {
@@ -2086,6 +2246,7 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   const GradPlan pl = grad_plan(d, g->nt, Sh);
   const int S = Sh ? Sh : choose_batch(ctx, per_shot(pl), fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, false);
   TableSet ts = build_table_set(d, geo, batches, ctx->two_step);
 
   double *acc = nullptr;
@@ -2179,6 +2340,7 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   const size_t fixed = (size_t)d.field * 8 + (size_t)img * 4 * 3;
   const int S = choose_batch(ctx, per_shot, fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, c.d, S, true);
   TableSet ts = build_table_set(d, geo, batches, true);
 
   float *coef = nullptr, *coefr = nullptr, *acc = nullptr, *gacc = nullptr, *e2d2 = nullptr, *pairs = nullptr,
@@ -2233,13 +2395,11 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     float *wp = pairs + 4 * d.field * Sb;
     HIPCHK(zero_start(wp, d, Sb, st));
     Ring4 fw(wp, d.field * Sb);
-    rc = march2(ctx, c, fw, Sb, 0, ns, kModeT2 | kModeDsrc, [&](Step2Args &p, int n, int k) {
+    rc = march2(ctx, c, fw, Sb, 0, ns, kModeT2 | kModeDsrc, [&](Steps &p, int n, int k) {
       with_dsrc2(p, sc + (long)n * d.field, d.field, k, hs);
-      with_dense_range(p.a, eg, 0);
-      p.a.t2 = hdu + (long)n * d.field;
-      p.t2b = k == 2 ? hdu + (long)(n + 1) * d.field : nullptr;
-      p.a.t2_sstride = hs;
-      with_rec_extract(p.a, t, ddrec, g->nt, n);
+      with_dense_range(p, eg, 0);
+      with_t2(p, hdu + (long)n * d.field, d.field, k, hs);
+      with_rec_extract(p, t, ddrec, g->nt, n);
     }, st);
     if (rc) return rc;
     HIPCHK(launch_gather(fw.cur(), d.field, t.cells, Sb, geo->nrec, ddrec, g->nt, g->nt - 1, st));
@@ -2258,10 +2418,9 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     const int nchunk = (ns + kTauChunk - 1) / kTauChunk;
     for (int j = nchunk - 1; j >= 0; --j) {
       const int n0 = j * kTauChunk, n1 = std::min(n0 + kTauChunk, ns);
-      rc = march2_back_ring(ctx, c, rho, rs, RR, Sb, n0, n1, kModeNu, [&](Step2Args &p, int k, int kk) {
-        p.a.nu = NuSource{e_slot(k - 1), e_slot(k), e_slot(k + 1), hs};
-        if (kk == 2) p.nu2 = NuSource{e_slot(k - 2), e_slot(k - 1), e_slot(k), hs};
-        with_dense_range(p.a, eg, 0);
+      rc = march2_back_ring(ctx, c, rho, rs, RR, Sb, n0, n1, kModeNu, [&](Steps &p, int k, int kk) {
+        with_nu(p, e_slot, k, kk, hs);
+        with_dense_range(p, eg, 0);
       }, st);
       if (rc) return rc;
       HIPCHK(launch_grad_accum2(hu + (long)n0 * d.field, hdu + (long)n0 * d.field, d.field, hs, lam, d.field, hs, R,
@@ -2326,6 +2485,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   const size_t tape_fixed = (size_t)(2 * pl.ck_stride * 4) * geo->nshots;
   const int S = Sh ? Sh : choose_batch(ctx, per_shot, tape_fixed + (size_t)d.field * 8, geo->nshots);
   tp->batches = split_batches(geo->nshots, S);
+  choose_steps(ctx, tp->d, S, false);
   tp->ts = build_table_set(d, geo, tp->batches, ctx->two_step);
 
   Carve tc;   // tape memory
