@@ -391,4 +391,22 @@ hipError_t launch_cg_dir(float *s, const float *r, float beta, long n, hipStream
 // q[h] += e2d2[h] s[h] per offset plane of `plane` cells
 hipError_t launch_add_diag(float *q, const float *s, const float *e2d2, long plane, int nh, hipStream_t st);
 
+// L-BFGS direction from inner products, for up to kLbfgsGramPairs pairs.
+constexpr int kLbfgsGramPairs = 15;
+constexpr int kLbfgsGramBlocks = 512;     // workgroups of the inner-product launch
+struct LbfgsVectors {
+  const float *s[kLbfgsGramPairs] = {}, *y[kLbfgsGramPairs] = {}, *g = nullptr;
+  int k = 0;
+};
+struct LbfgsCoefs {
+  double s[kLbfgsGramPairs] = {}, y[kLbfgsGramPairs] = {}, g = 0.0;
+};
+// Partial products: block (b, group) stores its four rows x sixteen columns at
+// out[(group nblocks + b) 64], nblocks = lbfgs_gram_blocks(k, n) and
+// (2 k + 3) / 4 groups (at most kLbfgsGramBlocks blocks in all); row 4 group +
+// r is s or, from k on, y; column c is y_c, and g at c = k.
+int lbfgs_gram_blocks(int k, long n);
+hipError_t launch_lbfgs_gram(const LbfgsVectors &v, long n, double *out, hipStream_t st);
+hipError_t launch_lbfgs_combine(const LbfgsVectors &v, const LbfgsCoefs &c, long n, float *d, hipStream_t st);
+
 }  // namespace fw

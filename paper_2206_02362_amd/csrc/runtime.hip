@@ -3432,9 +3432,65 @@ namespace {
 constexpr int kLbfgsMaxEvals = 100;      // trial steps per line search
 constexpr long kLbfgsWorkHead = 4096;    // floats of the workspace before the vectors (dot partials)
 
-// d = H g by the two-loop recursion over the pairs S[i], Y[i] (oldest first),
+// d = -H g from the inner products of the pairs (oldest first) and g, at most
+// kLbfgsGramPairs of them: the same recursion as two_loop below, on numbers.
+// With q = g - sum_j alpha_j y_j and r = gamma q + sum_j (alpha_j - beta_j) s_j
+// written out, alpha_i = rho_i s_i.q and beta_i = rho_i y_i.r need s_i.y_j,
+// y_i.y_j, s_i.g and y_i.g only.  One synchronization; every pair's curvature
+// is checked before d is written.
+int gram_direction(fwime_ctx_t *ctx, long n, const std::vector<const float *> &S, const std::vector<const float *> &Y,
+                   const float *g, float *d, hipStream_t st) {
+  const int k = (int)S.size();
+  LbfgsVectors v;
+  std::copy(S.begin(), S.end(), v.s);
+  std::copy(Y.begin(), Y.end(), v.y);
+  v.g = g;
+  v.k = k;
+  LbfgsCoefs c;
+  c.g = -1.0;
+  if (k > 0) {
+    const int nb = lbfgs_gram_blocks(k, n), groups = (2 * k + 3) / 4;
+    int rc = host_red_reserve(ctx, (size_t)nb * groups * 64);
+    if (rc) return rc;
+    HIPCHK(launch_lbfgs_gram(v, n, ctx->host_red, st));
+    HIPCHK(hipStreamSynchronize(st));
+    std::vector<double> dot((size_t)groups * 64, 0.0);     // [row][16]
+    for (int gr = 0; gr < groups; ++gr)
+      for (int b = 0; b < nb; ++b)
+        for (int q = 0; q < 64; ++q) dot[gr * 64 + q] += ctx->host_red[((size_t)gr * nb + b) * 64 + q];
+    auto sy = [&](int i, int j) { return dot[i * 16 + j]; };         // s_i . y_j, j = k: s_i . g
+    auto yy = [&](int i, int j) { return dot[(k + i) * 16 + j]; };   // y_i . y_j, j = k: y_i . g
+    for (int i = 0; i < k; ++i)
+      if (!(sy(i, i) > 0.0) || !std::isfinite(sy(i, i)))
+        return set_err(ctx, FWIME_EINVAL, "pair " + std::to_string(i) + " has s.y <= 0 or non-finite");
+    const double gamma = sy(k - 1, k - 1) / yy(k - 1, k - 1);
+    std::vector<double> alpha(k), diff(k);
+    for (int i = k - 1; i >= 0; --i) {
+      double sq = sy(i, k);
+      for (int j = k - 1; j > i; --j) sq -= alpha[j] * sy(i, j);
+      alpha[i] = sq / sy(i, i);
+    }
+    for (int i = 0; i < k; ++i) {
+      double yr = yy(i, k);
+      for (int j = 0; j < k; ++j) yr -= alpha[j] * yy(i, j);
+      yr *= gamma;
+      for (int j = 0; j < i; ++j) yr += diff[j] * sy(j, i);
+      diff[i] = alpha[i] - yr / sy(i, i);
+    }
+    c.g = -gamma;
+    for (int i = 0; i < k; ++i) {
+      c.s[i] = -diff[i];
+      c.y[i] = gamma * alpha[i];
+    }
+  }
+  HIPCHK(launch_lbfgs_combine(v, c, n, d, st));
+  return FWIME_OK;
+}
+
+// d = -H g by the two-loop recursion over the pairs S[i], Y[i] (oldest first),
 // H_0 = (s.y / y.y of the newest pair) I; FP64 inner products, FP32 updates.
-// Every pair's curvature is checked before d is written.
+// Every pair's curvature is checked before d is written.  (For more pairs
+// than gram_direction takes: its inner products grow with their square.)
 int two_loop(fwime_ctx_t *ctx, long n, const std::vector<const float *> &S, const std::vector<const float *> &Y,
              const float *g, float *d, double *part, double *res, hipStream_t st) {
   const int k = (int)S.size();
@@ -3472,6 +3528,7 @@ int two_loop(fwime_ctx_t *ctx, long n, const std::vector<const float *> &S, cons
     if ((rc = dot(Y[i], d, yr))) return rc;
     HIPCHK(launch_axpby(S[i], (float)(alpha[i] - rho[i] * yr), d, 1.0f, n, st));
   }
+  HIPCHK(launch_axpby(d, 0.0f, d, -1.0f, n, st));
   return FWIME_OK;
 }
 
@@ -3489,6 +3546,12 @@ int fwime_lbfgs_direction(fwime_ctx_t *ctx, int64_t n, int32_t npairs, const flo
     return set_err(ctx, FWIME_EINVAL, "npairs must be in [0, " + std::to_string(kLbfgsMaxPairs) + "]");
   if (!g || !d_out || (npairs > 0 && (!s || !y))) return set_err(ctx, FWIME_EINVAL, "null vector");
   HIPCHK(hipSetDevice(ctx->device));
+  std::vector<const float *> S(npairs), Y(npairs);
+  for (int i = 0; i < npairs; ++i) {
+    S[i] = s + (long)i * n;
+    Y[i] = y + (long)i * n;
+  }
+  if (npairs <= kLbfgsGramPairs) return gram_direction(ctx, (long)n, S, Y, g, d_out, st);
   HIPCHK(hipStreamSynchronize(st));      // earlier work on the stream may still use the arena
   double *part = nullptr, *res = nullptr;
   Carve cv;
@@ -3496,14 +3559,7 @@ int fwime_lbfgs_direction(fwime_ctx_t *ctx, int64_t n, int32_t npairs, const flo
   cv.add(&res, 1);
   int rc;
   if ((rc = arena_get(ctx, cv))) return rc;
-  std::vector<const float *> S(npairs), Y(npairs);
-  for (int i = 0; i < npairs; ++i) {
-    S[i] = s + (long)i * n;
-    Y[i] = y + (long)i * n;
-  }
-  if ((rc = two_loop(ctx, (long)n, S, Y, g, d_out, part, res, st))) return rc;
-  HIPCHK(launch_axpby(d_out, 0.0f, d_out, -1.0f, (long)n, st));
-  return FWIME_OK;
+  return two_loop(ctx, (long)n, S, Y, g, d_out, part, res, st);
 }
 
 int fwime_lbfgs_minimize(fwime_ctx_t *ctx, int64_t n, int32_t memory, int32_t maxiter, double gtol,
@@ -3561,8 +3617,10 @@ int fwime_lbfgs_minimize(fwime_ctx_t *ctx, int64_t n, int32_t memory, int32_t ma
       S.push_back(sslot[j]);
       Y.push_back(yslot[j]);
     }
-    if ((rc = two_loop(ctx, (long)n, S, Y, g, d, part, res, st))) return rc;
-    HIPCHK(launch_axpby(d, 0.0f, d, -1.0f, (long)n, st));   // descent direction -H g
+    // descent direction -H g
+    if ((rc = (int)S.size() <= kLbfgsGramPairs ? gram_direction(ctx, (long)n, S, Y, g, d, st)
+                                               : two_loop(ctx, (long)n, S, Y, g, d, part, res, st)))
+      return rc;
     double dphi0;
     if ((rc = dot(g, d, dphi0))) return rc;
     if (!(dphi0 < 0.0)) break;
