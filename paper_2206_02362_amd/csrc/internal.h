@@ -286,8 +286,29 @@ hipError_t launch_gather(const float *field, long sstride, const int *cells, int
 hipError_t launch_prep(const float *vel, int nz, int nx, int nb, int NZ, int NX, int LZ, float dt,
                        float *V, hipStream_t st);
 
-// min, max and non-finite count of a device array (result in a device buffer of 3 doubles)
-hipError_t launch_minmax(const float *a, long n, double *res, hipStream_t st);
+// min, max and non-finite count of up to kRangeArrays device arrays: workgroup
+// b of the launch stores the triple of its share to out[3 b ..] (host memory);
+// array k has the workgroups block0[k] .. block0[k + 1] - 1 (at least one).
+constexpr int kRangeArrays = 64;
+struct RangeArgs {
+  const float *a[kRangeArrays];
+  long n[kRangeArrays];
+  int block0[kRangeArrays + 1];
+  int count = 0;
+};
+hipError_t launch_ranges(const RangeArgs &r, double *out, hipStream_t st);
+
+// One job of a multi-job preparation: V from vel, zero[0 .. nzero) = 0, by
+// nblocks workgroups from block0 on.
+struct PrepJob {
+  const float *vel;
+  float *V, *zero;
+  long nzero;
+  int nz, nx, nb, NZ, NX, LZ;
+  float dt;
+  int block0, nblocks;
+};
+hipError_t launch_prep_multi(const PrepJob *jobs, int njobs, int blocks, hipStream_t st);
 
 // Fill a float array with zeros (kernel, usable under graph capture).
 hipError_t launch_zero(float *a, long n, hipStream_t st);

@@ -324,19 +324,21 @@ hipError_t launch_gather(const float *field, long sstride, const int *cells, int
   return hipGetLastError();
 }
 
-__global__ void k_prep(const float *vel, int nz, int nx, int nb, int NZ, int NX, int LZ, float dt, float *V) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)NX * LZ) return;
+// v^2 dt^2 of element i of a padded field, zero in the rows past the grid
+__device__ __forceinline__ float padded_v2dt2(const float *vel, int nz, int nx, int nb, int NZ, int LZ, float dt,
+                                              long i) {
   const int x = (int)(i / LZ);
   const int z = (int)(i - (long)x * LZ);
-  if (z >= NZ) {
-    V[i] = 0.f;
-    return;
-  }
+  if (z >= NZ) return 0.f;
   const int mx = min(max(x - nb, 0), nx - 1);
   const int mz = min(max(z - nb, 0), nz - 1);
   const float v = vel[(long)mx * nz + mz];
-  V[i] = v * v * dt * dt;
+  return v * v * dt * dt;
+}
+
+__global__ void k_prep(const float *vel, int nz, int nx, int nb, int NZ, int NX, int LZ, float dt, float *V) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < (long)NX * LZ) V[i] = padded_v2dt2(vel, nz, nx, nb, NZ, LZ, dt, i);
 }
 
 hipError_t launch_prep(const float *vel, int nz, int nx, int nb, int NZ, int NX, int LZ, float dt, float *V,
@@ -386,56 +388,88 @@ hipError_t launch_copy_fields(float *dst, long dst_sstride, const float *src, lo
   return hipGetLastError();
 }
 
-// Block-reduced min / max / non-finite count, combined across blocks with
-// device-scope atomics on doubles (order-independent).
-__global__ void k_minmax(const float *a, long n, double *res) {
+// min / max / non-finite count of several arrays, one triple per workgroup.
+// Every call validates its inputs and waits for the answer, so what counts is
+// the round trip: one launch for all arrays, each workgroup on its own share
+// of one array, its triple stored straight to host memory.  (Per array, a
+// launch to clear a triple, one with three atomics per workgroup on it and a
+// copy took 25 us of atomics alone for 1.25 M values; 96 arrays of a batch 2.9
+// ms.)
+__global__ void __launch_bounds__(256) k_ranges(const RangeArgs r, double *out) {
+  int k = 0;                                         // this workgroup's array
+  for (int step = 32; step > 0; step >>= 1)
+    if (k + step < r.count && r.block0[k + step] <= (int)blockIdx.x) k += step;
+  const float *a = r.a[k];
+  const long n = r.n[k];
+  const int b = blockIdx.x - r.block0[k], nb = r.block0[k + 1] - r.block0[k];
   float mn = INFINITY, mx = -INFINITY;
-  double bad = 0.0;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    const float v = a[i];
+  int bad = 0;
+  auto take = [&](float v) {
     if (!isfinite(v)) {
-      bad += 1.0;
+      ++bad;
     } else {
       mn = fminf(mn, v);
       mx = fmaxf(mx, v);
     }
+  };
+  const long stride = (long)nb * 256;
+  long i = (long)b * 256 + threadIdx.x;
+  for (; i + 7 * stride < n; i += 8 * stride) {
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = a[i + q * stride];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) take(v[q]);
   }
+  for (; i < n; i += stride) take(a[i]);
+  double cnt = bad;
   for (int o = 32; o > 0; o >>= 1) {
     mn = fminf(mn, __shfl_xor(mn, o));
     mx = fmaxf(mx, __shfl_xor(mx, o));
-    bad += __shfl_xor(bad, o);
+    cnt += __shfl_xor(cnt, o);
   }
   __shared__ float smn[4], smx[4];
-  __shared__ double sbad[4];
+  __shared__ double scnt[4];
   const int wv = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
     smn[wv] = mn;
     smx[wv] = mx;
-    sbad[wv] = bad;
+    scnt[wv] = cnt;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    mn = fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3]));
-    mx = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
-    bad = sbad[0] + sbad[1] + sbad[2] + sbad[3];
-    atomicMin(&res[0], (double)mn);
-    atomicMax(&res[1], (double)mx);
-    atomicAdd(&res[2], bad);
+    double *o = out + 3L * blockIdx.x;
+    o[0] = fminf(fminf(smn[0], smn[1]), fminf(smn[2], smn[3]));
+    o[1] = fmaxf(fmaxf(smx[0], smx[1]), fmaxf(smx[2], smx[3]));
+    o[2] = scnt[0] + scnt[1] + scnt[2] + scnt[3];
   }
 }
 
-__global__ void k_minmax_init(double *res) {
-  res[0] = INFINITY;
-  res[1] = -INFINITY;
-  res[2] = 0.0;
+hipError_t launch_ranges(const RangeArgs &r, double *out, hipStream_t st) {
+  if (r.count < 1 || r.count > kRangeArrays) return hipErrorInvalidValue;
+  k_ranges<<<(unsigned)r.block0[r.count], 256, 0, st>>>(r, out);
+  return hipGetLastError();
 }
 
-hipError_t launch_minmax(const float *a, long n, double *res, hipStream_t st) {
-  k_minmax_init<<<1, 1, 0, st>>>(res);
-  long blocks = (n + 255) / 256;
-  if (blocks > 2048) blocks = 2048;
-  if (blocks < 1) blocks = 1;
-  k_minmax<<<(unsigned)blocks, 256, 0, st>>>(a, n, res);
+// Padded velocity V of every job and the zero start of its first two fields, in
+// one launch (each job has a range of workgroups, dealt by its cells).
+__global__ void __launch_bounds__(256) k_prep_multi(const PrepJob *jobs, int njobs) {
+  int lo = 0, hi = njobs - 1;                        // last job with block0 <= this workgroup
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (jobs[mid].block0 <= (int)blockIdx.x) lo = mid;
+    else hi = mid - 1;
+  }
+  const PrepJob j = jobs[lo];
+  const long stride = (long)j.nblocks * 256;
+  const long at = (long)(blockIdx.x - j.block0) * 256 + threadIdx.x;
+  for (long i = at; i < (long)j.NX * j.LZ; i += stride)
+    j.V[i] = padded_v2dt2(j.vel, j.nz, j.nx, j.nb, j.NZ, j.LZ, j.dt, i);
+  for (long i = at; i < j.nzero; i += stride) j.zero[i] = 0.f;
+}
+
+hipError_t launch_prep_multi(const PrepJob *jobs, int njobs, int blocks, hipStream_t st) {
+  k_prep_multi<<<(unsigned)blocks, 256, 0, st>>>(jobs, njobs);
   return hipGetLastError();
 }
 

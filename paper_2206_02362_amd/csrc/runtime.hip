@@ -286,28 +286,49 @@ int host_red_reserve(fwime_ctx_t *ctx, size_t n) {
   return FWIME_OK;
 }
 
-// min / max / non-finite count of several device arrays: one reduction per
-// array into consecutive triples of a scratch buffer at the front of the
-// arena, one copy to pinned host memory and one stream synchronization for
-// all of them.  out[3 k .. 3 k + 2] describe array k.
+// min / max / non-finite count of several device arrays: one launch for up to
+// kRangeArrays of them, whose workgroups write their triples to pinned host
+// memory, and one stream synchronization.  out[3 k .. 3 k + 2] describe array k.
+constexpr int kRangeBlocks = 2048;       // workgroups for all arrays, and one more per array
 int device_ranges(fwime_ctx_t *ctx, const std::vector<std::pair<const float *, long>> &arrays, hipStream_t st,
                   std::vector<double> &out) {
   const size_t n = arrays.size();
-  double *scratch = nullptr;
-  Carve cv;
-  cv.add(&scratch, 3 * n);
-  // later carves of the same call reuse this memory: the reductions are
-  // complete once this function returns
-  int rc = arena_get(ctx, cv);
-  if (rc) return rc;
-  if ((rc = host_red_reserve(ctx, 3 * n))) return rc;
-  for (size_t k = 0; k < n; ++k) {
-    if (!arrays[k].first) return set_err(ctx, FWIME_EINVAL, "input pointer is null");
-    HIPCHK(launch_minmax(arrays[k].first, arrays[k].second, scratch + 3 * k, st));
+  double all = 0.0;
+  for (auto &a : arrays) {
+    if (!a.first) return set_err(ctx, FWIME_EINVAL, "input pointer is null");
+    all += (double)a.second;
   }
-  HIPCHK(hipMemcpyAsync(ctx->host_red, scratch, 3 * n * sizeof(double), hipMemcpyDeviceToHost, st));
+  int rc;
+  if ((rc = host_red_reserve(ctx, 3 * (kRangeBlocks + n)))) return rc;
+  std::vector<int> first(n + 1, 0);      // workgroups before array k
+  for (size_t k = 0; k < n; ++k) {
+    const long share = (long)(kRangeBlocks * ((double)arrays[k].second / std::max(all, 1.0)));
+    first[k + 1] = first[k] + (int)std::max(1L, std::min(share, (arrays[k].second + 2047) / 2048));
+  }
+  for (size_t k0 = 0; k0 < n; k0 += kRangeArrays) {
+    RangeArgs r;
+    r.count = (int)std::min<size_t>(kRangeArrays, n - k0);
+    for (int k = 0; k < r.count; ++k) {
+      r.a[k] = arrays[k0 + k].first;
+      r.n[k] = arrays[k0 + k].second;
+      r.block0[k] = first[k0 + k] - first[k0];
+    }
+    r.block0[r.count] = first[k0 + r.count] - first[k0];
+    HIPCHK(launch_ranges(r, ctx->host_red + 3L * first[k0], st));
+  }
   HIPCHK(hipStreamSynchronize(st));
-  out.assign(ctx->host_red, ctx->host_red + 3 * n);
+  out.resize(3 * n);
+  for (size_t k = 0; k < n; ++k) {
+    double mn = INFINITY, mx = -INFINITY, bad = 0.0;
+    for (int b = first[k]; b < first[k + 1]; ++b) {
+      mn = std::min(mn, ctx->host_red[3 * b]);
+      mx = std::max(mx, ctx->host_red[3 * b + 1]);
+      bad += ctx->host_red[3 * b + 2];
+    }
+    out[3 * k] = mn;
+    out[3 * k + 1] = mx;
+    out[3 * k + 2] = bad;
+  }
   return FWIME_OK;
 }
 
@@ -539,48 +560,38 @@ size_t table_set_ints(const TableSet &ts) {
   return n;
 }
 
+// Appends the tables to `blob` (pieces on 64-int boundaries) and points
+// ts.dev into its device copy, whose first int is at `dev`.
+void layout_tables(TableSet &ts, std::vector<int> &blob, int *dev) {
+  ts.dev.clear();
+  auto put = [&](const void *src, size_t nint) -> int * {
+    const size_t off = (blob.size() + 63) / 64 * 64;
+    blob.resize(off + nint);
+    if (nint) std::memcpy(blob.data() + off, src, nint * sizeof(int));
+    return dev + off;
+  };
+  for (auto &t : ts.host) {
+    DevTables dt;
+    dt.src_ptr = put(t.src_ptr.data(), t.src_ptr.size());
+    dt.rext_ptr = put(t.rext_ptr.data(), t.rext_ptr.size());
+    dt.rinj_ptr = put(t.rinj_ptr.data(), t.rinj_ptr.size());
+    dt.cells = put(t.cells.data(), t.cells.size());
+    dt.src_ent = (int2 *)put(t.src_ent.data(), 2 * t.src_ent.size());
+    dt.rext_ent = (int2 *)put(t.rext_ent.data(), 2 * t.rext_ent.size());
+    dt.rinj_ent = (int2 *)put(t.rinj_ent.data(), 2 * t.rinj_ent.size());
+    dt.src1_ptr = put(t.src1_ptr.data(), t.src1_ptr.size());
+    dt.src1_ent = (int2 *)put(t.src1_ent.data(), 2 * t.src1_ent.size());
+    dt.rinj1_ptr = put(t.rinj1_ptr.data(), t.rinj1_ptr.size());
+    dt.rinj1_ent = (int2 *)put(t.rinj1_ent.data(), 2 * t.rinj1_ent.size());
+    ts.dev.push_back(dt);
+  }
+}
+
 // sync = false: the copy may still read ts.blob after the call returns, so
 // the caller keeps ts alive until the stream has passed the copy.
 int upload_tables(fwime_ctx_t *ctx, TableSet &ts, int *dev, hipStream_t st, bool sync = true) {
   ts.blob.clear();
-  ts.dev.clear();
-  auto put = [&](const void *src, size_t nint) -> size_t {
-    size_t off = (ts.blob.size() + 63) / 64 * 64;
-    ts.blob.resize(off + nint);
-    if (nint) std::memcpy(ts.blob.data() + off, src, nint * sizeof(int));
-    return off;
-  };
-  std::vector<std::vector<size_t>> offs;
-  for (auto &t : ts.host) {
-    std::vector<size_t> o;
-    o.push_back(put(t.src_ptr.data(), t.src_ptr.size()));
-    o.push_back(put(t.rext_ptr.data(), t.rext_ptr.size()));
-    o.push_back(put(t.rinj_ptr.data(), t.rinj_ptr.size()));
-    o.push_back(put(t.cells.data(), t.cells.size()));
-    o.push_back(put(t.src_ent.data(), 2 * t.src_ent.size()));
-    o.push_back(put(t.rext_ent.data(), 2 * t.rext_ent.size()));
-    o.push_back(put(t.rinj_ent.data(), 2 * t.rinj_ent.size()));
-    o.push_back(put(t.src1_ptr.data(), t.src1_ptr.size()));
-    o.push_back(put(t.src1_ent.data(), 2 * t.src1_ent.size()));
-    o.push_back(put(t.rinj1_ptr.data(), t.rinj1_ptr.size()));
-    o.push_back(put(t.rinj1_ent.data(), 2 * t.rinj1_ent.size()));
-    offs.push_back(o);
-  }
-  for (auto &o : offs) {
-    DevTables dt;
-    dt.src_ptr = dev + o[0];
-    dt.rext_ptr = dev + o[1];
-    dt.rinj_ptr = dev + o[2];
-    dt.cells = dev + o[3];
-    dt.src_ent = (int2 *)(dev + o[4]);
-    dt.rext_ent = (int2 *)(dev + o[5]);
-    dt.rinj_ent = (int2 *)(dev + o[6]);
-    dt.src1_ptr = dev + o[7];
-    dt.src1_ent = (int2 *)(dev + o[8]);
-    dt.rinj1_ptr = dev + o[9];
-    dt.rinj1_ent = (int2 *)(dev + o[10]);
-    ts.dev.push_back(dt);
-  }
+  layout_tables(ts, ts.blob, dev);
   // With sync the blob is copied synchronously (pageable memory): the call
   // owns no host staging that could outlive it.
   HIPCHK(hipMemcpyAsync(dev, ts.blob.data(), ts.blob.size() * sizeof(int), hipMemcpyHostToDevice, st));
@@ -609,14 +620,9 @@ void taper_host(int n, int nb, double alpha, int len, std::vector<float> &out) {
   }
 }
 
-int setup_common(fwime_ctx_t *ctx, Common &c, const fwime_grid_t *g, const float *vel, hipStream_t st) {
+// step arguments shared by every launch of a call
+void common_args(Common &c, const fwime_grid_t *g) {
   const Dims &d = c.d;
-  HIPCHK(launch_prep(vel, d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, (float)g->dt, c.V, st));
-  std::vector<float> gz, gx;
-  taper_host(d.nz, d.nb, g->sponge_alpha, d.LZ, gz);
-  taper_host(d.nx, d.nb, g->sponge_alpha, d.NX + kGxPad, gx);
-  HIPCHK(hipMemcpyAsync(c.gz, gz.data(), gz.size() * sizeof(float), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(c.gx, gx.data(), gx.size() * sizeof(float), hipMemcpyHostToDevice, st));
   StepArgs &a = c.base;
   a = StepArgs();
   a.V = c.V;
@@ -633,6 +639,17 @@ int setup_common(fwime_ctx_t *ctx, Common &c, const fwime_grid_t *g, const float
     a.cz[k] = (float)(kW[k + 1] * idz2);
     a.cx[k] = (float)(kW[k + 1] * idx2);
   }
+}
+
+int setup_common(fwime_ctx_t *ctx, Common &c, const fwime_grid_t *g, const float *vel, hipStream_t st) {
+  const Dims &d = c.d;
+  HIPCHK(launch_prep(vel, d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, (float)g->dt, c.V, st));
+  std::vector<float> gz, gx;
+  taper_host(d.nz, d.nb, g->sponge_alpha, d.LZ, gz);
+  taper_host(d.nx, d.nb, g->sponge_alpha, d.NX + kGxPad, gx);
+  HIPCHK(hipMemcpyAsync(c.gz, gz.data(), gz.size() * sizeof(float), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(c.gx, gx.data(), gx.size() * sizeof(float), hipMemcpyHostToDevice, st));
+  common_args(c, g);
   return FWIME_OK;
 }
 
@@ -1089,7 +1106,7 @@ int fwime_ctx_create(int device, size_t hbm_budget_bytes, fwime_ctx_t **out) {
   fwime_ctx_t *ctx = new fwime_ctx_t();
   ctx->device = device;
   ctx->budget = hbm_budget_bytes;
-  if (host_red_reserve(ctx, 64) != FWIME_OK) {
+  if (host_red_reserve(ctx, 3 * (kRangeBlocks + 64)) != FWIME_OK) {
     delete ctx;
     return FWIME_EHIP;
   }
@@ -2721,63 +2738,96 @@ hipError_t batch_launch(const BatchPlan &bp, const void *djobs, int tiles, int *
   return launch_bump(dstep, bp.stride(), st);
 }
 
+// Scratch of a batch and what its launches read: the tables, tapers and
+// descriptors of all jobs go to the device as one blob, and one launch
+// prepares every job's velocity and zero start.  (A copy each for a job's
+// tables and two tapers and a launch each for its velocity and fields were 240
+// commands for 48 jobs, 2 ms of a 49 ms call.)
 int batch_carve_and_setup(fwime_ctx_t *ctx, int njobs, const fwime_job_t *jobs, BatchPlan &bp, void **djobs,
                           int **dstep, hipStream_t st) {
   Carve cv;
   std::vector<float *> fields(njobs);
   const int nf = bp.two ? 4 : 2;
+  const size_t jb_bytes = bp.two ? sizeof(BatchJob2) : sizeof(BatchJob);
+  static_assert(sizeof(BatchJob2) % 8 == 0 && sizeof(BatchJob) % 8 == 0 && sizeof(PrepJob) % 8 == 0, "blob pieces");
+  size_t blob_ints = 64 * 4 + (jb_bytes + sizeof(PrepJob)) / 4 * njobs + (bp.two ? bp.total : 0);
   for (int k = 0; k < njobs; ++k) {
     const int j = bp.order[k];
     const Dims &d = bp.com[k].d;
     cv.add(&bp.com[k].V, d.field);
-    cv.add(&bp.com[k].gz, d.LZ);
-    cv.add(&bp.com[k].gx, d.NX + kGxPad);
-    cv.add(&bp.com[k].tables, table_set_ints(bp.ts[k]) + 64 * 8);
     cv.add(&fields[k], nf * d.field * jobs[j].geom.nshots);
+    blob_ints += table_set_ints(bp.ts[k]) + 64 * 8 + d.LZ + d.NX + kGxPad + 2 * 64;
   }
-  const size_t jb_bytes = bp.two ? sizeof(BatchJob2) : sizeof(BatchJob);
-  char *dj = nullptr;
-  cv.add(&dj, jb_bytes * njobs);
+  int *dblob = nullptr;
+  cv.add(&dblob, blob_ints);
   cv.add(dstep, 1);
-  if (bp.two) cv.add(&bp.dtile_job, bp.total);
   int rc = arena_get(ctx, cv);
   if (rc) return rc;
+  std::vector<int> blob;
+  blob.reserve(blob_ints);
+  // piece of `nint` ints on a 64-int boundary: its place in the blob
+  auto piece = [&](size_t nint) {
+    const size_t off = (blob.size() + 63) / 64 * 64;
+    blob.resize(off + nint);
+    return off;
+  };
+  std::vector<PrepJob> prep(njobs);
+  int blocks = 0;
   for (int k = 0; k < njobs; ++k) {
     const int j = bp.order[k];
-    const Dims &d = bp.com[k].d;
+    Common &c = bp.com[k];
+    const Dims &d = c.d;
+    const fwime_grid_t *g = &jobs[j].grid;
     const int S = jobs[j].geom.nshots;
-    if ((rc = upload_tables(ctx, bp.ts[k], bp.com[k].tables, st, false))) return rc;
-    if ((rc = setup_common(ctx, bp.com[k], &jobs[j].grid, jobs[j].vel, st))) return rc;
-    HIPCHK(launch_zero(fields[k], nf * d.field * S, st));
+    layout_tables(bp.ts[k], blob, dblob);
+    for (int axis = 0; axis < 2; ++axis) {
+      std::vector<float> t;
+      if (axis == 0) taper_host(d.nz, d.nb, g->sponge_alpha, d.LZ, t);
+      else taper_host(d.nx, d.nb, g->sponge_alpha, d.NX + kGxPad, t);
+      const size_t off = piece(t.size());
+      std::memcpy(blob.data() + off, t.data(), t.size() * sizeof(float));
+      (axis == 0 ? c.gz : c.gx) = reinterpret_cast<float *>(dblob + off);
+    }
+    common_args(c, g);
+    // u^{-1} = u^0 = 0
+    const long nzero = 2 * d.field * S;
+    const int nb = (int)std::min<long>(512, (std::max(nzero, d.field) + 4095) / 4096);
+    prep[k] = PrepJob{jobs[j].vel, c.V, fields[k], nzero, d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, (float)g->dt, blocks, nb};
+    blocks += nb;
     const DevTables &t = bp.ts[k].dev[0];
     if (bp.two) {
       BatchJob2 &bj = bp.jobs2[k];
-      bj.p.a = batch_args(bp.com[k], S, d.field);
+      bj.p.a = batch_args(c, S, d.field);
       bj.p.a.ntz = d.ntz2;
-      with_src2(bj.p, t, jobs[j].geom.wavelet, &jobs[j].grid, 0);
-      with_rec_extract(bj.p.a, t, jobs[j].data, jobs[j].grid.nt, 0);
+      with_src2(bj.p, t, jobs[j].geom.wavelet, g, 0);
+      with_rec_extract(bj.p.a, t, jobs[j].data, g->nt, 0);
       for (int q = 0; q < 4; ++q) bj.buf[q] = fields[k] + q * d.field * S;
     } else {
       BatchJob &bj = bp.jobs[k];
-      bj.a = batch_args(bp.com[k], S, d.field);
-      with_src(bj.a, t, &jobs[j].geom, &jobs[j].grid, 0, 0);
-      with_rec_extract(bj.a, t, jobs[j].data, jobs[j].grid.nt, 0);
+      bj.a = batch_args(c, S, d.field);
+      with_src(bj.a, t, &jobs[j].geom, g, 0, 0);
+      with_rec_extract(bj.a, t, jobs[j].data, g->nt, 0);
       bj.bufA = fields[k];
       bj.bufB = fields[k] + d.field * S;
     }
   }
   const void *host = bp.two ? (const void *)bp.jobs2.data() : (const void *)bp.jobs.data();
-  HIPCHK(hipMemcpyAsync(dj, host, jb_bytes * njobs, hipMemcpyHostToDevice, st));
+  const size_t dj = piece(jb_bytes / 4 * njobs);
+  std::memcpy(blob.data() + dj, host, jb_bytes * njobs);
+  const size_t dp = piece(sizeof(PrepJob) / 4 * njobs);
+  std::memcpy(blob.data() + dp, prep.data(), sizeof(PrepJob) * njobs);
   // the job of every tile, so that a workgroup finds its job with one load
-  std::vector<int> tile_job;
   if (bp.two) {
-    tile_job.resize(bp.total);
+    const size_t tj = piece(bp.total);
     for (int k = 0; k < njobs; ++k)
-      std::fill(tile_job.begin() + bp.prefix[k], tile_job.begin() + bp.prefix[k + 1], k);
-    HIPCHK(hipMemcpyAsync(bp.dtile_job, tile_job.data(), sizeof(int) * bp.total, hipMemcpyHostToDevice, st));
+      std::fill(blob.begin() + tj + bp.prefix[k], blob.begin() + tj + bp.prefix[k + 1], k);
+    bp.dtile_job = dblob + tj;
   }
+  if (blob.size() > blob_ints) return set_err(ctx, FWIME_EHIP, "batch tables exceed their scratch");
+  HIPCHK(hipMemcpyAsync(dblob, blob.data(), blob.size() * sizeof(int), hipMemcpyHostToDevice, st));
+  HIPCHK(launch_prep_multi(reinterpret_cast<PrepJob *>(dblob + dp), njobs, blocks, st));
   HIPCHK(hipStreamSynchronize(st));
-  *djobs = dj;
+  *djobs = dblob + dj;
   return FWIME_OK;
 }
 
