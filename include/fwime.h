@@ -353,9 +353,11 @@ void fwime_tape_free(fwime_tape_t *tape);
  * zn, xn: HOST double, strictly increasing, 2 to 2^24 nodes each, covering
  * [0, (nz-1) dz] and [0, (nx-1) dx] (to 1e-9 of the node span); read during
  * the call only.  mc: DEVICE [nxn][nzn]; out: DEVICE [nx][nz], z fastest.
- * The call synchronizes `stream` twice (before taking the context's arena and
- * after the node upload); the interpolation tables
- * (about 12 bytes per fine point and node) live in the context's arena.
+ * With at most 384 nodes in all and nz <= 2048 the call is one launch (the
+ * adjoint where, too, no x cell is wider than 256 dx).  Otherwise it
+ * synchronizes `stream` twice (before taking the context's arena and after the
+ * node upload), and the interpolation tables (about 12 bytes per fine point
+ * and node) live in the context's arena.
  * Argument errors (FWIME_EINVAL) are reported before anything is written;
  * non-finite node values propagate. */
 int fwime_spline_apply(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, double dx,

@@ -430,4 +430,20 @@ int lbfgs_gram_blocks(int k, long n);
 hipError_t launch_lbfgs_gram(const LbfgsVectors &v, long n, double *out, hipStream_t st);
 hipError_t launch_lbfgs_combine(const LbfgsVectors &v, const LbfgsCoefs &c, long n, float *d, hipStream_t st);
 
+// Spline operators in one launch: node coordinates of both axes (z first) in
+// the kernel arguments, whose size bounds their number; nz is bounded by the
+// per-workgroup table of the rows.
+constexpr int kSplineNodes = 384;        // nodes of both axes together (3 KB of 4)
+constexpr int kSplineRows = 2048;        // fine points along z
+constexpr int kSplineCols = 4;           // fine columns per workgroup of S
+constexpr int kSplineTmp = 8192;         // z sums held at a time by S*
+struct SplineNodes {
+  int nzn = 0, nxn = 0;
+  double n[kSplineNodes];
+};
+hipError_t launch_spline_apply1(const SplineNodes &s, int nz, int nx, double dz, double dx, const float *mc,
+                                float *out, hipStream_t st);
+hipError_t launch_spline_adjoint1(const SplineNodes &s, int nz, int nx, double dz, double dx, const float *f,
+                                  float *out, hipStream_t st);
+
 }  // namespace fw

@@ -123,4 +123,132 @@ hipError_t launch_spline_adjoint(const float *f, int nz, int nx, const float *tz
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// S and S* in one launch each, for node sets that fit the kernel arguments.
+// At the size of an inversion (35 x 171 nodes on 300 x 1700) both operators
+// move 2 MB, 0.4 us at the copy rate, and a call was all round trips: two node
+// uploads, two synchronizations, four table launches and up to two more (49
+// us).  Here the node coordinates travel with the launch and every workgroup
+// forms the part of the tables it needs in LDS, so a call is one launch: what
+// bounds it is that launch and, inside it, one chain of memory reads.
+// ---------------------------------------------------------------------------
+// cell of coordinate p (last node at or before it, at most nn - 2), as in
+// k_spline_axis
+__device__ __forceinline__ int spline_cell(const double *nodes, int nn, double p) {
+  int lo = 0, hi = nn - 2;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (nodes[mid] <= p) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+__device__ __forceinline__ float spline_weight(const double *nodes, int cell, double p) {
+  const double t = (p - nodes[cell]) / (nodes[cell + 1] - nodes[cell]);
+  return (float)fmin(fmax(t, 0.0), 1.0);
+}
+// first of the nf fine points whose cell is at least j, as in k_spline_starts
+__device__ __forceinline__ int spline_start(const double *nodes, int nn, int nf, double h, int j) {
+  if (j <= 0) return 0;
+  if (j > nn - 2) return nf;
+  int lo = 0, hi = nf;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (nodes[j] <= mid * h) hi = mid;
+    else lo = mid + 1;
+  }
+  return lo;
+}
+
+// out[ix][iz] for the workgroup's kSplineCols columns
+__global__ void __launch_bounds__(256) k_spline_apply1(const SplineNodes s, int nz, int nx, double dz, double dx,
+                                                       const float *__restrict__ mc, float *__restrict__ out) {
+  __shared__ double nodes[kSplineNodes];
+  __shared__ int cz[kSplineRows];
+  __shared__ float tz[kSplineRows];
+  for (int i = threadIdx.x; i < s.nzn + s.nxn; i += 256) nodes[i] = s.n[i];
+  __syncthreads();
+  for (int i = threadIdx.x; i < nz; i += 256) {
+    cz[i] = spline_cell(nodes, s.nzn, i * dz);
+    tz[i] = spline_weight(nodes, cz[i], i * dz);
+  }
+  __syncthreads();
+  const int x0 = blockIdx.x * kSplineCols, x1 = min(nx, x0 + kSplineCols);
+  for (int ix = x0; ix < x1; ++ix) {
+    const int kx = spline_cell(nodes + s.nzn, s.nxn, ix * dx);
+    const float wx = spline_weight(nodes + s.nzn, kx, ix * dx);
+    for (int iz = threadIdx.x; iz < nz; iz += 256) {
+      const float wz = tz[iz];
+      const float *m0 = mc + (long)kx * s.nzn + cz[iz];
+      const float *m1 = m0 + s.nzn;
+      const float a = (1.0f - wz) * m0[0] + wz * m0[1];
+      const float b = (1.0f - wz) * m1[0] + wz * m1[1];
+      out[(long)ix * nz + iz] = (1.0f - wx) * a + wx * b;
+    }
+  }
+}
+
+// out[jx][jz] for one node column jx: the fine columns of its two cells go
+// through the z gather into LDS, as many at a time as fit, and thread jz adds
+// them in ascending order (k_spline_adj_z and k_spline_adj_x in one)
+__global__ void __launch_bounds__(256) k_spline_adjoint1(const SplineNodes s, int nz, int nx, double dz, double dx,
+                                                         const float *__restrict__ f, float *__restrict__ out) {
+  __shared__ double nodes[kSplineNodes];
+  __shared__ float tz[kSplineRows];
+  __shared__ int sz[kSplineNodes + 1];
+  __shared__ float tmp[kSplineTmp];
+  const int jx = blockIdx.x, nzn = s.nzn;
+  for (int i = threadIdx.x; i < nzn + s.nxn; i += 256) nodes[i] = s.n[i];
+  __syncthreads();
+  const double *xn = nodes + nzn;
+  for (int i = threadIdx.x; i < nz; i += 256) tz[i] = spline_weight(nodes, spline_cell(nodes, nzn, i * dz), i * dz);
+  for (int j = threadIdx.x; j <= nzn; j += 256) sz[j] = spline_start(nodes, nzn, nz, dz, j);
+  const int xa = jx > 0 ? spline_start(xn, s.nxn, nx, dx, jx - 1) : 0;   // cell jx - 1: weight t
+  const int xm = spline_start(xn, s.nxn, nx, dx, jx);                    // cell jx: weight 1 - t
+  const int xe = spline_start(xn, s.nxn, nx, dx, jx + 1);
+  const int cols = kSplineTmp / nzn;                  // fine columns at a time
+  float acc[(kSplineNodes + 255) / 256];
+#pragma unroll
+  for (int q = 0; q < (kSplineNodes + 255) / 256; ++q) acc[q] = 0.0f;
+  for (int xc = jx > 0 ? xa : xm; xc < xe; xc += cols) {
+    const int n = min(cols, xe - xc);
+    __syncthreads();                                  // tables ready; the last columns are read
+    for (int p = threadIdx.x; p < n * nzn; p += 256) {
+      const int c = p / nzn, jz = p - c * nzn;
+      const float *row = f + (long)(xc + c) * nz;
+      float a = 0.0f;
+      if (jz > 0)
+        for (int iz = sz[jz - 1]; iz < sz[jz]; ++iz) a += tz[iz] * row[iz];
+      for (int iz = sz[jz]; iz < sz[jz + 1]; ++iz) a += (1.0f - tz[iz]) * row[iz];
+      tmp[p] = a;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < (kSplineNodes + 255) / 256; ++q) {
+      const int jz = threadIdx.x + 256 * q;
+      if (jz >= nzn) break;
+      for (int c = 0; c < n; ++c) {
+        const int ix = xc + c;
+        const float t = spline_weight(xn, ix < xm ? jx - 1 : min(jx, s.nxn - 2), ix * dx);
+        acc[q] += (ix < xm ? t : 1.0f - t) * tmp[c * nzn + jz];
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < (kSplineNodes + 255) / 256; ++q)
+    if (threadIdx.x + 256 * q < nzn) out[(long)jx * nzn + threadIdx.x + 256 * q] = acc[q];
+}
+
+hipError_t launch_spline_apply1(const SplineNodes &s, int nz, int nx, double dz, double dx, const float *mc,
+                                float *out, hipStream_t st) {
+  k_spline_apply1<<<(nx + kSplineCols - 1) / kSplineCols, 256, 0, st>>>(s, nz, nx, dz, dx, mc, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_spline_adjoint1(const SplineNodes &s, int nz, int nx, double dz, double dx, const float *f,
+                                  float *out, hipStream_t st) {
+  k_spline_adjoint1<<<s.nxn, 256, 0, st>>>(s, nz, nx, dz, dx, f, out);
+  return hipGetLastError();
+}
+
 }  // namespace fw

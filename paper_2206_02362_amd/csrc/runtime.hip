@@ -3354,16 +3354,38 @@ int check_spline_axis(fwime_ctx_t *ctx, const double *n, int32_t nn, int32_t nf,
   return FWIME_OK;
 }
 
-// validates, carves the tables (plus `extra` floats) from the arena, uploads
-// the node coordinates and builds the per-axis tables on `st`
-int spline_setup(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, double dx, int32_t nzn, const double *zn,
-                 int32_t nxn, const double *xn, const void *in, void *out, long extra, float **extra_ptr,
-                 SplineAxes &a, hipStream_t st) {
+int check_spline(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, double dx, int32_t nzn, const double *zn,
+                 int32_t nxn, const double *xn, const void *in, void *out) {
   int rc;
   if ((rc = check_spline_axis(ctx, zn, nzn, nz, dz, "z")) || (rc = check_spline_axis(ctx, xn, nxn, nx, dx, "x")))
     return rc;
   if (!in || !out) return set_err(ctx, FWIME_EINVAL, "input or output is null");
   HIPCHK(hipSetDevice(ctx->device));
+  return FWIME_OK;
+}
+
+// Whether S and S* run as one launch: few enough nodes and rows for it, and
+// for S* cells of at most 256 points, since one workgroup gathers the columns
+// of a node's two cells (two nodes on 1700 columns would leave the device
+// idle; the two-pass gather spreads them).
+bool spline_one_launch(int32_t nz, int32_t nx, int32_t nzn, int32_t nxn, const double *xn, double dx, bool adjoint,
+                       SplineNodes &s, const double *zn) {
+  if ((long)nzn + nxn > kSplineNodes || nz > kSplineRows) return false;
+  if (adjoint)
+    for (int j = 1; j < nxn; ++j)
+      if (xn[j] - xn[j - 1] > 256 * dx) return false;
+  s.nzn = nzn;
+  s.nxn = nxn;
+  std::copy(zn, zn + nzn, s.n);
+  std::copy(xn, xn + nxn, s.n + nzn);
+  return true;
+}
+
+// carves the tables (plus `extra` floats) from the arena, uploads the node
+// coordinates and builds the per-axis tables on `st`
+int spline_setup(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, double dx, int32_t nzn, const double *zn,
+                 int32_t nxn, const double *xn, long extra, float **extra_ptr, SplineAxes &a, hipStream_t st) {
+  int rc;
   HIPCHK(hipStreamSynchronize(st));      // earlier work on the stream may still use the arena
   Carve cv;
   cv.add(&a.zn, nzn);
@@ -3394,9 +3416,15 @@ int fwime_spline_apply(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, doub
   if (!ctx) return FWIME_EINVAL;
   ctx->err.clear();
   hipStream_t st = (hipStream_t)stream;
-  SplineAxes a;
-  int rc = spline_setup(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, mc, out, 0, nullptr, a, st);
+  int rc = check_spline(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, mc, out);
   if (rc) return rc;
+  SplineNodes nodes;
+  if (spline_one_launch(nz, nx, nzn, nxn, xn, dx, false, nodes, zn)) {
+    HIPCHK(launch_spline_apply1(nodes, nz, nx, dz, dx, mc, out, st));
+    return FWIME_OK;
+  }
+  SplineAxes a;
+  if ((rc = spline_setup(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, 0, nullptr, a, st))) return rc;
   HIPCHK(launch_spline_apply(mc, nzn, a.cz, a.tz, a.cx, a.tx, nz, nx, out, st));
   return FWIME_OK;
 }
@@ -3407,10 +3435,16 @@ int fwime_spline_adjoint(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, do
   if (!ctx) return FWIME_EINVAL;
   ctx->err.clear();
   hipStream_t st = (hipStream_t)stream;
+  int rc = check_spline(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, f, mc_out);
+  if (rc) return rc;
+  SplineNodes nodes;
+  if (spline_one_launch(nz, nx, nzn, nxn, xn, dx, true, nodes, zn)) {
+    HIPCHK(launch_spline_adjoint1(nodes, nz, nx, dz, dx, f, mc_out, st));
+    return FWIME_OK;
+  }
   SplineAxes a;
   float *tmp = nullptr;
-  int rc = spline_setup(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, f, mc_out, (long)nx * nzn, &tmp, a, st);
-  if (rc) return rc;
+  if ((rc = spline_setup(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, (long)nx * nzn, &tmp, a, st))) return rc;
   HIPCHK(launch_spline_adjoint(f, nz, nx, a.tz, a.sz, nzn, a.tx, a.sx, nxn, tmp, mc_out, st));
   return FWIME_OK;
 }
