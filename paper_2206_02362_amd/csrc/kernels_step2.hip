@@ -238,8 +238,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
     }
   };
 
-  // u^n tile, one column per wavefront access: lane = row z0 - 8 + lane, and
-  // lanes 0..7 also row z0 + 56 + lane.  No branch: a cell outside the grid
+  // u^n tile, one column per wavefront access: lane = row z0 - 8 + lane.  No branch: a cell outside the grid
   // gets a per-lane offset past the end of the buffer (the whole offset is in
   // the per-lane register, which the range check covers), so it reads as
   // zero, and every load of the tile is in flight before the first LDS write
@@ -247,39 +246,53 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   {
     constexpr int NC = C0 / kWaves;
     constexpr int kOut = kOutOfRange;
-    const int zt = z0 - 2 * kR + lane;
+    // The last 8 rows of the columns come eight columns to a load: lane = row
+    // 64 + lane % 8 of the wavefront's column lane / 8 (+ 8, + 16), issued
+    // behind those columns' own loads, whose memory lines it continues.  (A
+    // load a column, used by 8 of its lanes, cost 12 loads and LDS writes and
+    // about 40 vector instructions a wavefront: 8 shots of 300 x 1400 11.25
+    // against 10.97 ms.  With both behind all columns, a batch larger than the
+    // last-level cache took 128.8 us a launch instead of 121.)
+    constexpr int NT = (NC + 7) / 8;
+    const int zt = z0 - 2 * kR + lane, ztt = z0 - 2 * kR + 64 + (lane & 7);
     const bool zt_in = zt >= 0 && zt < NZ;
-    const bool zt2_in = lane < 2 * kR && zt + 64 < NZ;
-    float v[NC], v2[NC];
-    [[maybe_unused]] unsigned short l[NC], l2[NC];
-    // rows read for the two loads of this lane (mirrored under a free surface)
+    const bool ztt_in = ztt < NZ;
+    float v[NC], v2[NT];
+    [[maybe_unused]] unsigned short l[NC], l2[NT];
+    // rows read for the loads of this lane (mirrored under a free surface)
     [[maybe_unused]] float sg = 1.f, sg2 = 1.f;
-    int zr = zt, zr2 = zt + 64;
+    int zr = zt, zr2 = ztt;
     if constexpr (FS) {
       zr = fs_mirror_row(zt, a.fs, sg);
-      zr2 = fs_mirror_row(zt + 64, a.fs, sg2);
+      zr2 = fs_mirror_row(ztt, a.fs, sg2);
     }
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int x = x0 - 2 * kR + w + kWaves * i;
       const bool xin = x >= 0 && x < NX;      // wave-uniform
       const int o1 = xin && zt_in ? x * CB + zr * 4 : kOut;
-      const int o2 = xin && zt2_in ? x * CB + zr2 * 4 : kOut;
       v[i] = ld(r_cur, o1, 0);
-      v2[i] = ld(r_cur, o2, 0);
-      if constexpr (DF) {
-        l[i] = ld16(r_lcur, o1 == kOut ? kOut : o1 / 2, 0);
-        l2[i] = ld16(r_lcur, o2 == kOut ? kOut : o2 / 2, 0);
+      if constexpr (DF) l[i] = ld16(r_lcur, o1 == kOut ? kOut : o1 / 2, 0);
+      if (i % 8 == 7 || i == NC - 1) {          // the rows below these eight columns
+        const int t = i / 8, it = (lane >> 3) + 8 * t, xt = x0 - 2 * kR + w + kWaves * it;
+        const int o2 = it < NC && xt >= 0 && xt < NX && ztt_in ? xt * CB + zr2 * 4 : kOut;
+        v2[t] = ld(r_cur, o2, 0);
+        if constexpr (DF) l2[t] = ld16(r_lcur, o2 == kOut ? kOut : o2 / 2, 0);
       }
     }
     if constexpr (FS) {
 #pragma unroll
       for (int i = 0; i < NC; ++i) {
         v[i] *= sg;
-        v2[i] *= sg2;
         if constexpr (DF) {
           if (sg < 0.f) l[i] ^= 0x8000u;           // BF16 sign flip
-          if (sg2 < 0.f) l2[i] ^= 0x8000u;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        v2[t] *= sg2;
+        if constexpr (DF) {
+          if (sg2 < 0.f) l2[t] ^= 0x8000u;
         }
       }
     }
@@ -322,19 +335,21 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
         src2.fetch(p.inj2, lane, 0);
       }
     }
-    // Lanes 8..63 put their (zero) second value into this wave's own column
-    // of the u^{n+1} tile, which step 1 overwrites after the barrier: a write
-    // without a branch keeps the compiler from moving those loads into one.
-    const bool lo8 = lane < 2 * kR;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
       const int c = w + kWaves * i;
       sh.u0[c][lane] = v[i];
-      *(lo8 ? &sh.u0[c][64 + lane] : &sh.u1[w][lane]) = v2[i];
-      if constexpr (DF) {
-        sh.l0[c][lane] = l[i];
-        *(lo8 ? &sh.l0[c][64 + lane] : &sh.l1[w][lane]) = l2[i];
-      }
+      if constexpr (DF) sh.l0[c][lane] = l[i];
+    }
+    // Lanes past the wavefront's columns put their (zero) value into its own
+    // column of the u^{n+1} tile, which step 1 overwrites after the barrier: a
+    // write without a branch keeps the compiler from moving loads into one.
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int i = (lane >> 3) + 8 * t;
+      const bool mine = NC % 8 == 0 || t + 1 < NT || i < NC;
+      *(mine ? &sh.u0[w + kWaves * i][64 + (lane & 7)] : &sh.u1[w][lane]) = v2[t];
+      if constexpr (DF) *(mine ? &sh.l0[w + kWaves * i][64 + (lane & 7)] : &sh.l1[w][lane]) = l2[t];
     }
   }
   __syncthreads();
