@@ -229,6 +229,28 @@ constexpr int kMaxSteps = 4;
 constexpr int kHalo4 = 4 * (kMaxSteps - 1);       // cells around the tile computed in the first step
 constexpr int kTZ4 = 64 - 2 * kHalo4;             // output rows per tile
 constexpr int kWaves4 = 8;
+
+// Division of 0 <= n < 2^20 by a fixed 1 <= d < 2^20 without a divide:
+// m = floor(2^40 / d) + 1 exceeds 2^40 / d by at most 1, so n m / 2^40 is n / d
+// plus less than 2^-20, and its floor the quotient.
+struct FastDiv {
+  unsigned lo = 0, hi = 0;
+  FastDiv() = default;
+  explicit FastDiv(unsigned d) {
+    const uint64_t m = (uint64_t(1) << 40) / d + 1;
+    lo = (unsigned)m;
+    hi = (unsigned)(m >> 32);
+  }
+  __host__ __device__ unsigned div(unsigned n) const {
+    return (unsigned)((n * (uint64_t)hi + ((n * (uint64_t)lo) >> 32)) >> 8);
+  }
+};
+
+// Order of the four-step tiles of a launch: z fastest, then x, then shots.
+__host__ __device__ inline long tile_index4(int txi, int tzi, int s, int ntz, int ntx) {
+  return ((long)s * ntx + txi) * ntz + tzi;
+}
+
 struct Step4Args {
   const float *prev = nullptr, *cur = nullptr;
   float *out[kMaxSteps] = {};
@@ -244,6 +266,7 @@ struct Step4Args {
   int ez0 = 0, ez1 = INT_MAX, ex0 = 0, ex1 = INT_MAX;
   int NZ = 0, NX = 0, LZ = 0;
   int nshots = 0, ntz = 0, ntx = 0;
+  FastDiv by_ntz, by_ntx;       // (set by launch_step4)
   float cz[kR] = {}, cx[kR] = {};
   int fs = -1;
   int steps = 0;

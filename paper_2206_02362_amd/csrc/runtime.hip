@@ -155,6 +155,7 @@ void choose_steps(const fwime_ctx_t *ctx, Dims &d, int S, bool df) {
   if (!ctx->two_step) return;
   const long tiles = (long)d.ntz2 * d.ntx * S;
   if (ctx->steps ? ctx->steps != 4 : tiles > (df ? kStep4MaxTilesDF : kStep4MaxTiles)) return;
+  if ((long)d.ntz4 * ((d.NX + 7) / 8) * S + 8 >= (1L << 20)) return;   // the kernel's tile arithmetic
   d.T = 4;
   d.TX4 = (long)d.ntz4 * ((d.NX + 7) / 8) * S <= kStep4MaxNarrow ? 8 : 16;
   d.ntx4 = (d.NX + d.TX4 - 1) / d.TX4;
@@ -498,7 +499,7 @@ HostTables build_tables4(const Dims &d, const fwime_geom_t *geo, int s0, int S) 
   HostTables t;
   const int W = (d.TX4 + 2 * kHalo4) / kWaves4;
   const long ntiles = (long)d.ntz4 * d.ntx4 * S;
-  auto tile_of = [&](int s, int txi, int tzi) { return tile_index(txi, tzi, s, d.ntz4, d.ntx4, S); };
+  auto tile_of = [&](int s, int txi, int tzi) { return tile_index4(txi, tzi, s, d.ntz4, d.ntx4); };
   std::vector<std::pair<long, int2>> src, rext, rinj;
   auto add_inject = [&](int s, int px, int pz, int idx, std::vector<std::pair<long, int2>> &l) {
     const int rx = (kHalo4 + d.TX4 - 1) / d.TX4, txi = px / d.TX4, tzi = pz / kTZ4;   // the halo reaches rx tiles
