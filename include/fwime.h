@@ -302,7 +302,8 @@ int fwime_ctx_info(const fwime_ctx_t *ctx, fwime_info_t *out);
  * records per modeling call and nothing to the kernels. */
 int fwime_ctx_set_timing(fwime_ctx_t *ctx, int32_t on);
 
-/* Release the context's scratch arena after `stream` (its stream) is idle.
+/* Release the context's scratch arena, and the memory that it keeps of a
+ * freed tape for the next one, after `stream` (its stream) is idle.
  * The next call allocates again.  For schedulers that share one HBM budget
  * among several contexts. */
 int fwime_ctx_trim(fwime_ctx_t *ctx, void *stream);
@@ -341,7 +342,9 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *grid, const float *
 int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tape, const float *adjsrc,
                         float *grad_vel, float *grad_ptilde, void *stream);
 
-/* Release a tape (synchronizes the device); null is ignored. */
+/* Release a tape (synchronizes the device); null is ignored.  A context
+ * without a budget keeps the memory of the largest tape freed, for the next
+ * one, until fwime_ctx_trim or fwime_ctx_destroy. */
 void fwime_tape_free(fwime_tape_t *tape);
 
 /* Linear spline operator S of Section 2: the model lives on a spline grid of

@@ -65,3 +65,41 @@ def test_history_and_checkpoints_agree(nz, nx, nb, nt, nshots, nh):
     _, rv, rp = oracle.gradient(g, vel, geo, p64, dobs.astype(np.float64), 1e-3, dso)
     for a, b in zip([got[0][0], got[0][1], got[0][6], got[0][7]], ref + [rv, rp]):
         assert _close(a, b, 1e-4)
+
+
+def test_tape_memory_is_reused_and_given_back():
+    """Tapes of growing and shrinking sizes and two at a time, in memory kept of earlier ones, give the results of a
+    fresh context bit for bit; trim gives the memory back."""
+    import torch
+    import paper_2206_02362_amd as fw
+    ctx = fw.Context(0)
+
+    def problem(nz, nshots, seed):
+        w = synth.tiny(nz=nz, nx=70, nb=9, nt=181, nshots=nshots, nh=5, seed=seed)
+        grid, tv, tg = gpu_problem(w)
+        pt = _dev(0.2 * synth.random_ptilde(5, nz, 70, seed))
+        return grid, tg, tv.clone().requires_grad_(True), pt.requires_grad_(True)
+
+    def grads(q, c, pred=None):
+        grid, tg, v, p = q
+        pred = fw.predicted_data(v, p, c, grid, tg) if pred is None else pred
+        return [pred.detach()] + list(torch.autograd.grad(pred.square().sum(), (v, p)))
+
+    qs = [problem(40, 2, 1), problem(60, 6, 2), problem(57, 3, 3)]
+    want = []
+    for q in qs:
+        c = fw.Context(0)
+        want.append(grads(q, c))
+        c.close()
+    for i in (0, 1, 2, 0, 1):
+        assert all(torch.equal(a, b) for a, b in zip(grads(qs[i], ctx), want[i])), i
+    both = [fw.predicted_data(q[2], q[3], ctx, q[0], q[1]) for q in (qs[2], qs[1])]
+    for i, pred in zip((2, 1), both):
+        assert all(torch.equal(a, b) for a, b in zip(grads(qs[i], ctx, pred), want[i])), i
+    assert ctx.info()["tape_bytes"] == 0
+    big = 6 * 180 * 78 * 128 * 4                 # at least one T2 history of the largest problem
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    ctx.trim()
+    assert torch.cuda.mem_get_info()[0] >= before + big
+    ctx.close()
