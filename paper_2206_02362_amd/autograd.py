@@ -1,8 +1,9 @@
 """torch.autograd wrapper of the FWIME predicted-data map.
 
 d_pred(m, p~) = f(m) + B~(m) p~  (the modeled data of eq. fwime.obj).  The
-forward pass runs fwime_forward_tape, which keeps sqrt(nt)-spaced checkpoints
-of the background and scattered wavefields on the device; the backward pass
+forward pass runs fwime_forward_tape, which keeps the T2 terms of every step
+(or sqrt(nt)-spaced checkpoints, where those do not fit) of the background and
+scattered wavefields on the device; the backward pass
 runs the hand-written adjoint-state backward (fwime_backward_tape) with the
 incoming gradient as adjoint source and returns
   dL/dm  = (B^* + T^*) dL/dd   (Born and tomographic parts of

@@ -365,14 +365,20 @@ hipError_t launch_ext_scatter(const float *coef, const ExtGeom &g, int sg, const
                               int out_first = 0);
 
 // acc(z,y,h) += sum_s sum_{n<nk} a_n(z, y-h) b_n(z, y+h) (FP64 accumulator;
-// products summed in FP32 over at most 128 slots of a slot group while there
+// products summed in FP32 over at most `chain` slots of a slot group while there
 // are at most kImageGroups groups).  Slot n of a is a + n*a_slot; slot of b
 // is ring index (b_first + n) % b_ring.  parts: scratch for up to kImageGroups
 // FP32 partial images ([kImageGroups][nh][nx][nz]), one per slot group.
 constexpr int kImageGroups = 16;
+// Longest FP32 chain of an imaging launch.  Long segments (whole histories)
+// would run chains up to the general bound on most launches, so they get a
+// shorter one: a 200 x 500 Born adjoint with 61 offsets, 8 shots, nt = 800 has
+// an image error against 64 bits of 5.8e-7 with chains of 256 slots and 4.9e-7
+// with 60, which is what a segment of sqrt(nt) steps gives.
+constexpr int kImgChain = 512, kImgChainLong = 128;
 hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const float *b, long b_slot, long b_sstride,
                             int b_ring, int b_first, int nshots, int nk, const ExtGeom &g, double *acc,
-                            float *parts, hipStream_t st);
+                            float *parts, hipStream_t st, int chain = kImgChain);
 
 // Time-lag extension, lags tau_k = k L dt, k in [-K, K] (g.nh = 2K+1, g.H = K).
 // Slots hold one padded field per time step, slot n of shot s at

@@ -594,12 +594,9 @@ constexpr int kImgHT = 8;
 // Each wavefront sums its tile in FP32 registers over the slots of its
 // group, then stores the sums into its group's partial image; a second
 // kernel adds the partials to the FP64 accumulator in group order.  The launch
-// splits its slots into enough groups that no group sums more than kImgChain
+// splits its slots into enough groups that no group sums more than `chain`
 // of them (while there are kImageGroups groups), which bounds the FP32 chain's
-// rounding whatever the number of shots and steps of the launch.  Measured on
-// a 200 x 500 Born adjoint with 61 offsets, 8 shots, nt = 800: error of the
-// image against 64 bits 5.8e-7 with chains of 256 slots, 4.9e-7 with 60.
-constexpr int kImgChain = 128;
+// rounding whatever the number of shots and steps of the launch.
 
 struct ImageArgs {
   const float *a;
@@ -896,7 +893,7 @@ __global__ void k_image_reduce(double *acc, const float *parts, long n, int grou
 
 hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const float *b, long b_slot, long b_sstride,
                             int b_ring, int b_first, int nshots, int nk, const ExtGeom &g, double *acc,
-                            float *parts, hipStream_t st) {
+                            float *parts, hipStream_t st, int chain) {
   if (nk <= 0 || nshots <= 0) return hipSuccess;
   ImageArgs p;
   p.a = a;
@@ -930,10 +927,10 @@ hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const f
   const int nblk = (npair + 7) / 8 * 8;
   // one workgroup fits a CU: split the slots into groups until there are
   // about eight workgroups per CU, so the last round of workgroups leaves
-  // little of the device idle, and until no group sums more than kImgChain
+  // little of the device idle, and until no group sums more than `chain`
   // slots (at most kImageGroups partial images)
   const int total = nshots * nk;
-  const int want = std::max((2048 + nblk - 1) / nblk, (total + kImgChain - 1) / kImgChain);
+  const int want = std::max((2048 + nblk - 1) / nblk, (total + chain - 1) / chain);
   int groups = std::min(kImageGroups, std::max(1, want));
   groups = std::min(groups, total);
   p.slots_per_group = (total + groups - 1) / groups;

@@ -1621,15 +1621,17 @@ struct AdjCache {
 };
 
 static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
-                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache);
+                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache,
+                            bool short_seg);
 
 int fwime_born_ext_adj(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
                        int32_t nh, const float *data, float *ptilde_out, void *stream) {
-  return born_ext_adj_run(ctx, g, vel, geo, nh, data, ptilde_out, stream, nullptr);
+  return born_ext_adj_run(ctx, g, vel, geo, nh, data, ptilde_out, stream, nullptr, false);
 }
 
 static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
-                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache) {
+                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache,
+                            bool short_seg) {
   if (!ctx) return FWIME_EINVAL;
   ctx->err.clear();
   hipStream_t st = (hipStream_t)stream;
@@ -1648,17 +1650,22 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   if (!two) cache = nullptr;                    // the one-step path recomputes inside its checkpoints
   float *hist = cache ? cache->hist : nullptr;  // whole T2 history: the cache's, or the arena's where it fits
   const bool own_hist = !cache;
+  // short_seg: images summed in the order of the checkpointed segments, the
+  // same bits wherever the background comes from.  The variable-projection
+  // step asks for it: it tracks its objective in FP64, to below what another
+  // order of the images' FP32 sums would move it.
+  auto long_seg = [&](int S) { return short_seg ? seg_len(g->nt) : hist_seg_len(g->nt, S); };
   const long img = (long)nh * d.nx * d.nz;
   const size_t fixed = (size_t)d.field * 8 + (size_t)img * (8 + 4 * kImageGroups);   // FP64 image + partials
   auto hist_per_shot = [&](int S) {
-    const long r = hist_seg_len(g->nt, S) + 2;
+    const long r = long_seg(S) + 2;
     return (nf + 2 + r + (r + 1) / 2 + (own_hist ? g->nt - 1L : 0L)) * d.field * 4 + (long)geo->nrec * 64;
   };
   const int Sh = !two || (cache && !hist) ? 0 : hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
     return fixed + (size_t)hist_per_shot(S) * S;
   });
   const bool keep = Sh > 0 || hist;
-  const int K = Sh ? hist_seg_len(g->nt, Sh) : seg_len(g->nt);
+  const int K = Sh ? long_seg(Sh) : seg_len(g->nt);
   const int nseg = (g->nt - 1 + K - 1) / K;
   const int R = K + 2;
   // two-step path: BF16 low parts of the four work fields and the checkpoints
@@ -1748,7 +1755,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
           if ((rc = march2_back_lambda(ctx, c, ring, ring_stride, R, Sb, n0, n1, t, data_b, g->nt, st, ring_lo)))
             return rc;
           HIPCHK(launch_ext_image(hist_b + (long)n0 * d.field, d.field, hist_stride, ring, d.field, ring_stride, R, n0,
-                                  Sb, nk, eg, acc, parts, st));
+                                  Sb, nk, eg, acc, parts, st, short_seg ? kImgChain : kImgChainLong));
           continue;
         }
         Ring4 wu(pairs, d.field * Sb);
@@ -2056,7 +2063,7 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
       }
     }
     HIPCHK(launch_ext_image(t2u, d.field, pl.seg_stride, wk.lam, d.field, pl.ring_stride, R, n0, Sb, nk, eg, acc,
-                            wk.parts, st));
+                            wk.parts, st, pl.hist ? kImgChainLong : kImgChain));
     HIPCHK(launch_grad_accum(t2u, t2d, d.field, pl.seg_stride, wk.lam, wk.rho, d.field, pl.ring_stride, R, n0,
                              Sb, nk, d.NZ, d.NX, d.LZ, gacc, st));
   }
@@ -2225,7 +2232,7 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   };
   auto adj = [&](const float *d, float *x) {
     return tau ? fwime_born_ext_tau_adj(ctx, g, vel, geo, nh, lag, d, x, stream)
-               : born_ext_adj_run(ctx, g, vel, geo, nh, d, x, stream, cp);
+               : born_ext_adj_run(ctx, g, vel, geo, nh, d, x, stream, cp, true);
   };
   if ((rc = adj(dres, b))) return rc;
   HIPCHK(launch_zero(ptilde_out, img, st));
@@ -2566,9 +2573,11 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     delete tp;
     return set_err(ctx, FWIME_ENOMEM, "tape does not fit the HBM budget");
   }
+  bool small = false;                      // a fraction of the spare, which waits for a large tape
   {
     std::lock_guard<std::mutex> lock(ctx->tape_mu);
-    if (tc.total <= ctx->spare_bytes) {
+    small = tc.total < ctx->spare_bytes / 4;
+    if (!small && tc.total <= ctx->spare_bytes) {
       tp->mem = ctx->spare;
       tp->capacity = ctx->spare_bytes;
       ctx->spare = nullptr;
@@ -2576,8 +2585,8 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     }
   }
   if (!tp->mem) {
-    release_spare(ctx);                    // too small: room for the larger one
-    if (hipMalloc(&tp->mem, tc.total) != hipSuccess) {
+    if (!small) release_spare(ctx);        // too small: room for the larger one
+    if (device_alloc(ctx, &tp->mem, tc.total) != hipSuccess) {
       (void)hipGetLastError();
       delete tp;
       return set_err(ctx, FWIME_ENOMEM, "hipMalloc of the tape failed");

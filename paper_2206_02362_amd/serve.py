@@ -49,7 +49,7 @@ _OPS = {"model": FWIME_OP_MODEL, "born_fwd": FWIME_OP_BORN_FWD, "born_adj": FWIM
 # wavefield propagations per shot: modeling 1; Born forward and adjoint 2
 # (background + scattered / adjoint); gradient 6 (background and Born
 # forward, the adjoint and its Born-type partner, and the two recomputation
-# passes over the checkpoints)
+# passes over the checkpoints: slots run under a budget, which checkpoints)
 PROPAGATIONS = {"model": 1, "born_fwd": 2, "born_adj": 2, "gradient": 6}
 
 

@@ -103,3 +103,19 @@ def test_tape_memory_is_reused_and_given_back():
     ctx.trim()
     assert torch.cuda.mem_get_info()[0] >= before + big
     ctx.close()
+
+
+@pytest.mark.parametrize("nz,nx,nt,nshots,nh", [(57, 33, 158, 24, 5), (40, 50, 301, 2, 19)])
+def test_vp_step_bits_do_not_depend_on_the_store(nz, nx, nt, nshots, nh):
+    """The solver's images are summed in one order whether the background is kept whole or checkpointed."""
+    import paper_2206_02362_amd as fw
+    w = synth.tiny(nz=nz, nx=nx, nb=8, nt=nt, nshots=nshots, nh=nh, seed=6)
+    grid, tv, tg = gpu_problem(w)
+    got = []
+    for budget in (0, 1 << 30):
+        ctx = fw.Context(0, hbm_budget_bytes=budget)
+        dobs = 0.7 * ctx.model(grid, tv, tg)
+        p, phi = ctx.vp_solve(grid, tv, tg, dobs, nh, 1e-3, synth.dso_weights(nh), 3)
+        got.append((p.cpu().numpy(), np.asarray(phi)))
+        ctx.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
