@@ -371,11 +371,12 @@ hipError_t launch_ext_scatter(const float *coef, const ExtGeom &g, int sg, const
 // FP32 partial images ([kImageGroups][nh][nx][nz]), one per slot group.
 constexpr int kImageGroups = 16;
 // Longest FP32 chain of an imaging launch.  Long segments (whole histories)
-// would run chains up to the general bound on most launches, so they get a
-// shorter one: a 200 x 500 Born adjoint with 61 offsets, 8 shots, nt = 800 has
-// an image error against 64 bits of 5.8e-7 with chains of 256 slots and 4.9e-7
-// with 60, which is what a segment of sqrt(nt) steps gives.
-constexpr int kImgChain = 512, kImgChainLong = 128;
+// get a shorter one, so that their images are as close to 64 bits as those of
+// the checkpointed segments, whose launches split into about as short chains
+// by themselves.  300 x 1700, 61 offsets, 8 shots, nt = 800, error of the Born
+// adjoint: checkpointed 3.9e-7, chains of 64 slots 3.9e-7; of 128 slots 5.0e-7
+// against 4.2e-7 (other inputs) at 2 % less time for the Born pair.
+constexpr int kImgChain = 512, kImgChainLong = 64;
 hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const float *b, long b_slot, long b_sstride,
                             int b_ring, int b_first, int nshots, int nk, const ExtGeom &g, double *acc,
                             float *parts, hipStream_t st, int chain = kImgChain);

@@ -1047,7 +1047,7 @@ int seg_len(int nt) {
 // footprints).  All shots of the call must fit, or at least enough of them
 // that a launch still fills the device.
 // ---------------------------------------------------------------------------
-constexpr long kHistSlots = 2048;       // time slots (shots x steps) of a segment
+constexpr long kHistSlots = 1024;       // time slots (shots x steps) of a segment
 constexpr long kHistMinTiles = 3072;    // two rounds of two-step workgroups (six per CU)
 
 // even segment length for S shots: about kHistSlots slots, at least the
