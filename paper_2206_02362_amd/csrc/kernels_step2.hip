@@ -647,7 +647,9 @@ __global__ void __launch_bounds__(256, step2_multi_blocks<TX>()) k_step2_multi(c
   p.out2 = jb.buf[(n + 3) & 3];
   p.two = n + 2 <= jb.nt - 1;
   p.a.inj.t = n;
-  p.inj2.t = n + 1;
+  // both steps' samples are fetched ahead of the body's early exits: at the
+  // last index there is no sample n + 1
+  p.inj2.t = min(n + 1, jb.nt - 1);
   p.a.ext.t = n;
   step2_body<TX, MODE, false>(p, logical - jb.tile_begin, sh, n == jb.nt - 1, true);
 }
