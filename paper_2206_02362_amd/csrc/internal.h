@@ -91,6 +91,31 @@ __host__ __device__ inline void tile_coords(int logical, int ntz, int ntx, int S
   txi = xg * kTileGroupX + txl;
 }
 
+// Orders a wavefront's LDS accesses where its lanes exchange values without a
+// workgroup barrier.  The hardware runs them in program order, so nothing is
+// emitted; but the compiler reads the program as one lane's, and may hand a
+// lane what it stored last instead of what another lane stored there since.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Adds point samples to a wavefront's per-column source registers through
+// `cols`, W columns of LDS of its own: put() stores the lanes' samples at cells
+// [column][row] of cols, all different, and lane l takes row l of every column.
+template <int W, int ROWS, class Put>
+__device__ __forceinline__ void add_through_lds(float (*cols)[ROWS], int lane, float (&src)[W], Put put) {
+#pragma unroll
+  for (int j = 0; j < W; ++j) cols[j][lane] = 0.f;
+  wave_sync();
+  put();
+  wave_sync();
+#pragma unroll
+  for (int j = 0; j < W; ++j) src[j] += cols[j][lane];
+  wave_sync();
+}
+
 // Per-tile injection list (compressed rows over tile*kWaves + wave).
 // An entry {(j << 6) | lz, idx} adds  val[idx * stride_idx + t] * scale  to the
 // source term of the cell in column j (of the wave's columns) and row lz.

@@ -118,14 +118,12 @@ struct Sources {
       }
       return;
     }
-#pragma unroll
-    for (int j = 0; j < W; ++j) cols[j][lane] = 0.f;
-    for (int b = 0; b < cnt; b += 64) {
-      if (b > 0) fetch(inj, lane, b);
-      if (b + lane < cnt) cols[en.x >> 6][en.x & 63] = val;
-    }
-#pragma unroll
-    for (int j = 0; j < W; ++j) src[j] += cols[j][lane];
+    add_through_lds(cols, lane, src, [&]() {
+      for (int b = 0; b < cnt; b += 64) {
+        if (b > 0) fetch(inj, lane, b);
+        if (b + lane < cnt) cols[en.x >> 6][en.x & 63] = val;
+      }
+    });
   }
 };
 

@@ -262,14 +262,12 @@ __global__ void __launch_bounds__(64 * kWaves4) k_step4(const Step4Args a) {
         } else {
           // through this wavefront's own columns of the next tile, not yet written
           float(*own)[ROWS] = nxt + cl;
-#pragma unroll
-          for (int j = 0; j < W; ++j) own[j][lane] = 0.f;
-          for (int b = 0; b < cnt; b += 64) {
-            if (cnt > 64 && b + lane < cnt) en = a.inj.ent[i0 + b + lane];
-            if (b + lane < cnt) own[en.x >> 6][en.x & 63] = cnt > 64 ? sample(st) : sv[st];
-          }
-#pragma unroll
-          for (int j = 0; j < W; ++j) src[j] += own[j][lane];
+          add_through_lds(own, lane, src, [&]() {
+            for (int b = 0; b < cnt; b += 64) {
+              if (cnt > 64 && b + lane < cnt) en = a.inj.ent[i0 + b + lane];
+              if (b + lane < cnt) own[en.x >> 6][en.x & 63] = cnt > 64 ? sample(st) : sv[st];
+            }
+          });
         }
       }
     }
