@@ -389,22 +389,18 @@ hipError_t launch_ext_scatter(const float *coef, const ExtGeom &g, int sg, const
                               hipStream_t st, int in_ring = 0, int in_first = 0, int out_ring = 0,
                               int out_first = 0);
 
-// acc(z,y,h) += sum_s sum_{n<nk} a_n(z, y-h) b_n(z, y+h) (FP64 accumulator;
-// products summed in FP32 over at most `chain` slots of a slot group while there
-// are at most kImageGroups groups).  Slot n of a is a + n*a_slot; slot of b
-// is ring index (b_first + n) % b_ring.  parts: scratch for up to kImageGroups
-// FP32 partial images ([kImageGroups][nh][nx][nz]), one per slot group.
+// acc(z,y,h) += sum_s sum_{n<nk} a_n(z, y-h) b_n(z, y+h) (FP64 accumulator).
+// The steps are summed in segments of `seg` of them (the last one shorter), from
+// the last segment to the first; each segment's slots in at most kImageGroups
+// groups of FP32 sums.  A launch over several segments thus gives the bits of
+// one launch per segment.  Slot n of a is a + n*a_slot; slot of b is ring index
+// (b_first + n) % b_ring.  parts: scratch for nparts >= kImageGroups FP32
+// partial images ([nparts][nh][nx][nz]), one per group; it bounds the segments
+// taken by one kernel launch.
 constexpr int kImageGroups = 16;
-// Longest FP32 chain of an imaging launch.  Long segments (whole histories)
-// get a shorter one, so that their images are as close to 64 bits as those of
-// the checkpointed segments, whose launches split into about as short chains
-// by themselves.  300 x 1700, 61 offsets, 8 shots, nt = 800, error of the Born
-// adjoint: checkpointed 3.9e-7, chains of 64 slots 3.9e-7; of 128 slots 5.0e-7
-// against 4.2e-7 (other inputs) at 2 % less time for the Born pair.
-constexpr int kImgChain = 512, kImgChainLong = 64;
 hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const float *b, long b_slot, long b_sstride,
-                            int b_ring, int b_first, int nshots, int nk, const ExtGeom &g, double *acc,
-                            float *parts, hipStream_t st, int chain = kImgChain);
+                            int b_ring, int b_first, int nshots, int nk, int seg, const ExtGeom &g, double *acc,
+                            float *parts, int nparts, hipStream_t st);
 
 // Time-lag extension, lags tau_k = k L dt, k in [-K, K] (g.nh = 2K+1, g.H = K).
 // Slots hold one padded field per time step, slot n of shot s at
@@ -419,15 +415,16 @@ hipError_t launch_tau_image(const float *in, long in_slot, long in_sstride, cons
                             long lam_sstride, int nslots, int nshots, const ExtGeom &g, int L, const float *vel,
                             float dt, float *acc, hipStream_t st);
 
-// gacc(x,z) += sum_s sum_{n<nk} (t2u_n + t2d_n) lam_n + t2u_n rho_n
+// gacc(x,z) += sum_s sum_{n<nk} (t2u_n + t2d_n) lam_n + t2u_n rho_n, in
+// segments of `seg` steps from the last to the first, each summed by itself
 // (lam and rho in rings of the same shape)
 hipError_t launch_grad_accum(const float *t2u, const float *t2d, long slot, long seg_sstride, const float *lam,
                              const float *rho, long ring_slot, long ring_sstride, int ring, int first, int nshots,
-                             int nk, int NZ, int NX, int LZ, float *gacc, hipStream_t st);
+                             int nk, int seg, int NZ, int NX, int LZ, float *gacc, hipStream_t st);
 // the same with lam and rho in rings of their own shapes
 hipError_t launch_grad_accum2(const float *t2u, const float *t2d, long slot, long seg_sstride, const float *lam,
                               long lam_slot, long lam_sstride, int lam_ring, int lam_first, const float *rho,
-                              long rho_slot, long rho_sstride, int rho_ring, int rho_first, int nshots, int nk,
+                              long rho_slot, long rho_sstride, int rho_ring, int rho_first, int nshots, int nk, int seg,
                               int NZ, int NX, int LZ, float *gacc, hipStream_t st);
 
 // r = du + ddu - dobs (in place into du), sum r^2 ADDED to *sumsq (double);

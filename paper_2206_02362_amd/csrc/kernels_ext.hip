@@ -593,10 +593,18 @@ constexpr int kImgHT = 8;
 
 // Each wavefront sums its tile in FP32 registers over the slots of its
 // group, then stores the sums into its group's partial image; a second
-// kernel adds the partials to the FP64 accumulator in group order.  The launch
-// splits its slots into enough groups that no group sums more than `chain`
-// of them (while there are kImageGroups groups), which bounds the FP32 chain's
-// rounding whatever the number of shots and steps of the launch.
+// kernel adds the partials to the FP64 accumulator in group order.  A segment's
+// slots are split into enough groups that no group sums more than kImgChain
+// of them, which bounds the FP32 chain's rounding to about 1e-6 of a sum of
+// random-sign terms, whatever the number of shots and steps of a segment.
+//
+// A history of many segments is one launch with a range of groups per segment:
+// the order of the sums, and with it every bit, is that of one launch per
+// segment.  (Groups cut across the whole history, 64 slots each, are as long
+// as a checkpointed segment's at 300 x 1700 but hold one shot's consecutive
+// steps, and at 100 x 200 twenty times as long: the Born adjoint's error
+// against 64 bits rose from 4.9e-7 to 5.4e-7.)
+constexpr int kImgChain = 512;
 
 struct ImageArgs {
   const float *a;
@@ -610,7 +618,7 @@ struct ImageArgs {
   int nzs, nyt, nht;
   int zpad;            // rows of the first strip above the model (direct-load kernel)
   int nhb;             // offset blocks (blockIdx.x: tile and offset block, offset block fastest)
-  int groups, slots_per_group;
+  int groups, slots_per_group;   // per segment of nk steps; blockIdx.y: segment and group, group fastest
 };
 
 // Stores a wavefront's FP32 tile sums into its group's partial image.  Every
@@ -687,7 +695,9 @@ __global__ void __launch_bounds__(1024) k_ext_image_lds(const ImageArgs p) {
 #pragma unroll
     for (int hh = 0; hh < kImgHT; ++hh) acc[yy][hh] = 0.f;
 
-  const int q0 = grp * p.slots_per_group;
+  const int sub = grp / p.groups;                // segment
+  const int q0 = (grp - sub * p.groups) * p.slots_per_group;
+  const float *a = p.a + (long)sub * p.nk * p.a_slot;
   const int total = min(p.nshots * p.nk, q0 + p.slots_per_group);
   // thread (w, lane) stages rows w + 16 r at depth lane; out-of-grid columns
   // read as zero through the bounds-checked buffer loads
@@ -695,10 +705,10 @@ __global__ void __launch_bounds__(1024) k_ext_image_lds(const ImageArgs p) {
   const int zoff = zp * 4;                          // per lane
   const int CBy = p.LZ * 4;                         // bytes per column
   SlotCursor fc;                                    // fetch walks q0, q0 + 1, ... once, in order
-  fc.init(q0, p.nk, p.b_first, p.b_ring);
+  fc.init(q0, p.nk, p.b_first + sub * p.nk, p.b_ring);
   auto fetch = [&](int q, float (&pre)[PER]) {
     if (q >= total) return;
-    const auto ra = slot_rsrc(p.a + (long)fc.s * p.a_sstride + (long)fc.n * p.a_slot, slot_bytes);
+    const auto ra = slot_rsrc(a + (long)fc.s * p.a_sstride + (long)fc.n * p.a_slot, slot_bytes);
     const auto rbb = slot_rsrc(p.b + (long)fc.s * p.b_sstride + (long)fc.r * p.b_slot, slot_bytes);
     fc.next();
 #pragma unroll
@@ -815,7 +825,9 @@ __global__ void __launch_bounds__(1024) k_ext_image_dma(const ImageArgs p) {
 #pragma unroll
     for (int hh = 0; hh < kImgHT; ++hh) acc[yy][hh] = 0.f;
 
-  const int q0 = grp * p.slots_per_group;
+  const int sub = grp / p.groups;                // segment
+  const int q0 = (grp - sub * p.groups) * p.slots_per_group;
+  const float *a = p.a + (long)sub * p.nk * p.a_slot;
   const int total = min(p.nshots * p.nk, q0 + p.slots_per_group);
   const unsigned slot_bytes = (unsigned)((long)p.NX * p.LZ * 4);
   const int CBy = p.LZ * 4;
@@ -825,10 +837,10 @@ __global__ void __launch_bounds__(1024) k_ext_image_dma(const ImageArgs p) {
   const int offb = lane_off + (xb0 + 4 * w) * CBy;
   OffCursor fa, fb;                              // issue walks q0, q0 + 1, ... once, in order
   fa.init(q0, p.nk, 0, 0, p.a_slot, p.a_sstride);
-  fb.init(q0, p.nk, p.b_first, p.b_ring, p.b_slot, p.b_sstride);
+  fb.init(q0, p.nk, p.b_first + sub * p.nk, p.b_ring, p.b_slot, p.b_sstride);
   auto issue = [&](int q, float *buf) {
     if (q >= total) return;
-    const auto ra = slot_rsrc(p.a + fa.off, slot_bytes);
+    const auto ra = slot_rsrc(a + fa.off, slot_bytes);
     const auto rbb = slot_rsrc(p.b + fb.off, slot_bytes);
     fa.next();
     fb.next();
@@ -882,21 +894,27 @@ __global__ void __launch_bounds__(1024) k_ext_image_dma(const ImageArgs p) {
   image_store(p, acc, grp, y0, h0, hhi, z);
 }
 
-// acc += sum over g of parts[g], in group order (FP64)
-__global__ void k_image_reduce(double *acc, const float *parts, long n, int groups) {
+// acc += sum over g of a segment's parts[g], in group order (FP64), from the
+// last segment to the first
+__global__ void k_image_reduce(double *acc, const float *parts, long n, int groups, int segments) {
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    double s = parts[i];
-    for (int g = 1; g < groups; ++g) s += (double)parts[(long)g * n + i];
-    acc[i] += s;
+    double sum = acc[i];
+    for (int sub = segments - 1; sub >= 0; --sub) {
+      const float *part = parts + (long)sub * groups * n + i;
+      double s = part[0];
+      for (int g = 1; g < groups; ++g) s += (double)part[(long)g * n];
+      sum += s;
+    }
+    acc[i] = sum;
   }
 }
 
 hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const float *b, long b_slot, long b_sstride,
-                            int b_ring, int b_first, int nshots, int nk, const ExtGeom &g, double *acc,
-                            float *parts, hipStream_t st, int chain) {
+                            int b_ring, int b_first, int nshots, int nk, int seg, const ExtGeom &g, double *acc,
+                            float *parts, int nparts, hipStream_t st) {
   if (nk <= 0 || nshots <= 0) return hipSuccess;
+  if (seg < 1 || nparts < kImageGroups) return hipErrorInvalidValue;
   ImageArgs p;
-  p.a = a;
   p.b = b;
   p.acc = acc;
   p.parts = parts;
@@ -905,9 +923,7 @@ hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const f
   p.a_sstride = a_sstride;
   p.b_sstride = b_sstride;
   p.b_ring = b_ring;
-  p.b_first = b_first;
   p.nshots = nshots;
-  p.nk = nk;
   p.nz = g.nz;
   p.nx = g.nx;
   p.nb = g.nb;
@@ -925,27 +941,37 @@ hipError_t launch_ext_image(const float *a, long a_slot, long a_sstride, const f
   p.nhb = wide ? (g.nh + 31) / 32 : 1;
   const int npair = p.nzs * ((g.nx + (wide ? 31 : 63)) / (wide ? 32 : 64)) * p.nhb;
   const int nblk = (npair + 7) / 8 * 8;
-  // one workgroup fits a CU: split the slots into groups until there are
-  // about eight workgroups per CU, so the last round of workgroups leaves
-  // little of the device idle, and until no group sums more than `chain`
-  // slots (at most kImageGroups partial images)
-  const int total = nshots * nk;
-  const int want = std::max((2048 + nblk - 1) / nblk, (total + chain - 1) / chain);
-  int groups = std::min(kImageGroups, std::max(1, want));
-  groups = std::min(groups, total);
-  p.slots_per_group = (total + groups - 1) / groups;
-  p.groups = (total + p.slots_per_group - 1) / p.slots_per_group;
-  const dim3 grid((unsigned)nblk, (unsigned)p.groups);
-  if (wide && !staged) k_ext_image_dma<4, 4><<<grid, 1024, 0, st>>>(p);
-  else if (wide) k_ext_image_lds<4, 4><<<grid, 1024, 0, st>>>(p);
-  else k_ext_image_lds<8, 2><<<grid, 1024, 0, st>>>(p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const long n = (long)g.nh * g.nx * g.nz;
-  long blocks = (n + 255) / 256;
-  if (blocks > 8192) blocks = 8192;
-  k_image_reduce<<<(unsigned)blocks, 256, 0, st>>>(acc, parts, n, p.groups);
-  return hipGetLastError();
+  const unsigned blocks = (unsigned)std::min((n + 255) / 256, 8192L);
+  // Segments left to do: steps 0 .. left - 1, from the end; the last one may be
+  // shorter and goes by itself, then as many as the partial images hold.
+  for (int left = nk; left > 0;) {
+    p.nk = left % seg ? left % seg : seg;
+    // one workgroup fits a CU: split the slots into groups until there are
+    // about eight workgroups per CU, so the last round of workgroups leaves
+    // little of the device idle, and until no group sums more than kImgChain
+    // slots (at most kImageGroups partial images)
+    const int total = nshots * p.nk;
+    const int want = std::max((2048 + nblk - 1) / nblk, (total + kImgChain - 1) / kImgChain);
+    int groups = std::min(kImageGroups, std::max(1, want));
+    groups = std::min(groups, total);
+    p.slots_per_group = (total + groups - 1) / groups;
+    p.groups = (total + p.slots_per_group - 1) / p.slots_per_group;
+    const int segments = p.nk < seg ? 1 : std::min(left / seg, nparts / p.groups);
+    left -= segments * p.nk;
+    p.a = a + (long)left * a_slot;
+    p.b_first = b_first + left;
+    const dim3 grid((unsigned)nblk, (unsigned)(segments * p.groups));
+    if (wide && !staged) k_ext_image_dma<4, 4><<<grid, 1024, 0, st>>>(p);
+    else if (wide) k_ext_image_lds<4, 4><<<grid, 1024, 0, st>>>(p);
+    else k_ext_image_lds<8, 2><<<grid, 1024, 0, st>>>(p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_image_reduce<<<blocks, 256, 0, st>>>(acc, parts, n, p.groups, segments);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------
@@ -1279,69 +1305,73 @@ hipError_t launch_tau_image(const float *in, long in_slot, long in_sstride, cons
 //
 // One thread per cell.  The four streams are read once, so the kernel is
 // bound by HBM on large grids and, where the grid is too small to fill the
-// device, by how many loads a thread keeps in flight: kAccumChain steps are
-// loaded together before the first is used.  Their products are summed in a
-// chain of their own, so that a long launch adds chain totals and not single
-// products: the rounding error grows with chains, not with steps.
+// device, by how many loads a thread keeps in flight: kAccumLoads steps are
+// loaded together before the first is used.  A segment's products are summed in
+// the order of shots, then steps, and segments are added from the last to the
+// first: the bits are those of one launch per checkpointed segment, and no
+// FP32 chain is longer than that segment's.
 // ---------------------------------------------------------------------------
-constexpr int kAccumChain = 8;
+constexpr int kAccumLoads = 8;
 
 __global__ void k_grad_accum(const float *t2u, const float *t2d, long slot, long seg_sstride, const float *lam,
                              long ring_slot, long ring_sstride, int ring, int first, const float *rho,
                              long rho_slot, long rho_sstride, int rho_ring, int rho_first, int nshots, int nk,
-                             int NZ, long ncell, int LZ, float *gacc) {
+                             int seg, int NZ, long ncell, int LZ, float *gacc) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ncell) return;
   const int z = (int)(i % LZ);
   if (z >= NZ) return;
-  float g = 0.f;
-  for (int s = 0; s < nshots; ++s) {
-    const float *pu = t2u + (long)s * seg_sstride + i, *pd = t2d + (long)s * seg_sstride + i;
-    const float *pl = lam + (long)s * ring_sstride + i, *pr = rho + (long)s * rho_sstride + i;
-    int rl = first % ring, rr = rho_first % rho_ring;      // ring slots of step n (wave-uniform)
-    int n = 0;
-    for (; n + kAccumChain <= nk; n += kAccumChain) {
-      float u[kAccumChain], d[kAccumChain], l[kAccumChain], r[kAccumChain];
+  float sum = gacc[i];
+  for (int n0 = (nk - 1) / seg * seg; n0 >= 0; n0 -= seg) {
+    const int n1 = min(n0 + seg, nk);
+    float g = 0.f;
+    for (int s = 0; s < nshots; ++s) {
+      const float *pu = t2u + (long)s * seg_sstride + i, *pd = t2d + (long)s * seg_sstride + i;
+      const float *pl = lam + (long)s * ring_sstride + i, *pr = rho + (long)s * rho_sstride + i;
+      int rl = (first + n0) % ring, rr = (rho_first + n0) % rho_ring;   // ring slots of step n (wave-uniform)
+      int n = n0;
+      for (; n + kAccumLoads <= n1; n += kAccumLoads) {
+        float u[kAccumLoads], d[kAccumLoads], l[kAccumLoads], r[kAccumLoads];
 #pragma unroll
-      for (int k = 0; k < kAccumChain; ++k) {
-        u[k] = pu[(long)(n + k) * slot];
-        d[k] = pd[(long)(n + k) * slot];
-        l[k] = pl[(long)rl * ring_slot];
-        r[k] = pr[(long)rr * rho_slot];
+        for (int k = 0; k < kAccumLoads; ++k) {
+          u[k] = pu[(long)(n + k) * slot];
+          d[k] = pd[(long)(n + k) * slot];
+          l[k] = pl[(long)rl * ring_slot];
+          r[k] = pr[(long)rr * rho_slot];
+          rl = rl + 1 == ring ? 0 : rl + 1;
+          rr = rr + 1 == rho_ring ? 0 : rr + 1;
+        }
+#pragma unroll
+        for (int k = 0; k < kAccumLoads; ++k) g += (u[k] + d[k]) * l[k] + u[k] * r[k];
+      }
+      for (; n < n1; ++n) {
+        const float u = pu[(long)n * slot], d = pd[(long)n * slot];
+        g += (u + d) * pl[(long)rl * ring_slot] + u * pr[(long)rr * rho_slot];
         rl = rl + 1 == ring ? 0 : rl + 1;
         rr = rr + 1 == rho_ring ? 0 : rr + 1;
       }
-      float c = 0.f;
-#pragma unroll
-      for (int k = 0; k < kAccumChain; ++k) c += (u[k] + d[k]) * l[k] + u[k] * r[k];
-      g += c;
     }
-    for (; n < nk; ++n) {
-      const float u = pu[(long)n * slot], d = pd[(long)n * slot];
-      g += (u + d) * pl[(long)rl * ring_slot] + u * pr[(long)rr * rho_slot];
-      rl = rl + 1 == ring ? 0 : rl + 1;
-      rr = rr + 1 == rho_ring ? 0 : rr + 1;
-    }
+    sum += g;
   }
-  gacc[i] += g;
+  gacc[i] = sum;
 }
 
 hipError_t launch_grad_accum(const float *t2u, const float *t2d, long slot, long seg_sstride, const float *lam,
                              const float *rho, long ring_slot, long ring_sstride, int ring, int first, int nshots,
-                             int nk, int NZ, int NX, int LZ, float *gacc, hipStream_t st) {
+                             int nk, int seg, int NZ, int NX, int LZ, float *gacc, hipStream_t st) {
   return launch_grad_accum2(t2u, t2d, slot, seg_sstride, lam, ring_slot, ring_sstride, ring, first, rho, ring_slot,
-                            ring_sstride, ring, first, nshots, nk, NZ, NX, LZ, gacc, st);
+                            ring_sstride, ring, first, nshots, nk, seg, NZ, NX, LZ, gacc, st);
 }
 
 hipError_t launch_grad_accum2(const float *t2u, const float *t2d, long slot, long seg_sstride, const float *lam,
                               long lam_slot, long lam_sstride, int lam_ring, int lam_first, const float *rho,
-                              long rho_slot, long rho_sstride, int rho_ring, int rho_first, int nshots, int nk,
+                              long rho_slot, long rho_sstride, int rho_ring, int rho_first, int nshots, int nk, int seg,
                               int NZ, int NX, int LZ, float *gacc, hipStream_t st) {
   if (nk <= 0 || nshots <= 0) return hipSuccess;
   const long ncell = (long)NX * LZ;
   k_grad_accum<<<(unsigned)((ncell + 255) / 256), 256, 0, st>>>(t2u, t2d, slot, seg_sstride, lam, lam_slot,
                                                                  lam_sstride, lam_ring, lam_first, rho, rho_slot,
-                                                                 rho_sstride, rho_ring, rho_first, nshots, nk, NZ,
+                                                                 rho_sstride, rho_ring, rho_first, nshots, nk, seg, NZ,
                                                                  ncell, LZ, gacc);
   return hipGetLastError();
 }

@@ -1039,8 +1039,10 @@ int seg_len(int nt) {
 // them whole instead of checkpointing the fields and propagating them again:
 // the gradient then runs four propagations per shot instead of six and one
 // offset scatter instead of two, the adjoint two instead of three.  Without
-// checkpoints the segment length is free, and long segments spread the offset
-// kernels' weight loads and image updates over more time slots.
+// checkpoints the segment length is free: long segments spread the offset
+// kernels' weight loads over more time slots.  They hold whole checkpointed
+// segments, and images and gradient sums are formed segment by segment inside
+// them, so a result has the same bits with histories and with checkpoints.
 //
 // At most a third of the free device memory is taken for it, and only by a
 // context without a budget (one with a budget shares the device by exact
@@ -1050,12 +1052,23 @@ int seg_len(int nt) {
 constexpr long kHistSlots = 1024;       // time slots (shots x steps) of a segment
 constexpr long kHistMinTiles = 3072;    // two rounds of two-step workgroups (six per CU)
 
-// even segment length for S shots: about kHistSlots slots, at least the
-// checkpointed segment
+// segment length for S shots: about kHistSlots slots in whole checkpointed
+// segments, or the record (made even)
 int hist_seg_len(int nt, int S) {
-  const long want = std::max<long>(seg_len(nt), (kHistSlots + S - 1) / S);
-  const int K = (int)std::min<long>(want, nt - 1);
-  return K + (K & 1);
+  const long seg = seg_len(nt), want = (kHistSlots + S - 1) / S;
+  const long K = std::max(1L, (want + seg - 1) / seg) * seg;
+  return (int)std::min<long>(K, (nt - 1) + ((nt - 1) & 1));
+}
+
+// Partial images of a launch that images a history segment of K steps, img
+// cells an image: groups for every checkpointed segment in it, as far as 256 MB
+// hold them.  (With one checkpointed segment to a launch, 100 x 200 and nh 11:
+// autograd 13.66 instead of 13.29 ms, variable-projection step 41.8 instead of
+// 41.1; 200 x 600 and larger the same to 0.2 %.)
+constexpr long kHistPartsBytes = 256L << 20;
+long hist_parts(int nt, int K, long img) {
+  const long segs = (K + seg_len(nt) - 1) / seg_len(nt);
+  return std::max<long>(kImageGroups, std::min<long>(segs * kImageGroups, kHistPartsBytes / (4 * img)));
 }
 
 // Shots per batch that keep whole histories (0: checkpoint instead).
@@ -1621,17 +1634,15 @@ struct AdjCache {
 };
 
 static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
-                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache,
-                            bool short_seg);
+                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache);
 
 int fwime_born_ext_adj(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
                        int32_t nh, const float *data, float *ptilde_out, void *stream) {
-  return born_ext_adj_run(ctx, g, vel, geo, nh, data, ptilde_out, stream, nullptr, false);
+  return born_ext_adj_run(ctx, g, vel, geo, nh, data, ptilde_out, stream, nullptr);
 }
 
 static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const fwime_geom_t *geo,
-                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache,
-                            bool short_seg) {
+                            int32_t nh, const float *data, float *ptilde_out, void *stream, AdjCache *cache) {
   if (!ctx) return FWIME_EINVAL;
   ctx->err.clear();
   hipStream_t st = (hipStream_t)stream;
@@ -1650,22 +1661,19 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   if (!two) cache = nullptr;                    // the one-step path recomputes inside its checkpoints
   float *hist = cache ? cache->hist : nullptr;  // whole T2 history: the cache's, or the arena's where it fits
   const bool own_hist = !cache;
-  // short_seg: images summed in the order of the checkpointed segments, the
-  // same bits wherever the background comes from.  The variable-projection
-  // step asks for it: it tracks its objective in FP64, to below what another
-  // order of the images' FP32 sums would move it.
-  auto long_seg = [&](int S) { return short_seg ? seg_len(g->nt) : hist_seg_len(g->nt, S); };
   const long img = (long)nh * d.nx * d.nz;
-  const size_t fixed = (size_t)d.field * 8 + (size_t)img * (8 + 4 * kImageGroups);   // FP64 image + partials
+  auto fixed = [&](long parts) { return (size_t)d.field * 8 + (size_t)img * (8 + 4 * parts); };   // FP64 image + partials
   auto hist_per_shot = [&](int S) {
-    const long r = long_seg(S) + 2;
+    const long r = hist_seg_len(g->nt, S) + 2;
     return (nf + 2 + r + (r + 1) / 2 + (own_hist ? g->nt - 1L : 0L)) * d.field * 4 + (long)geo->nrec * 64;
   };
   const int Sh = !two || (cache && !hist) ? 0 : hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
-    return fixed + (size_t)hist_per_shot(S) * S;
+    return fixed(hist_parts(g->nt, hist_seg_len(g->nt, S), img)) + (size_t)hist_per_shot(S) * S;
   });
   const bool keep = Sh > 0 || hist;
-  const int K = Sh ? long_seg(Sh) : seg_len(g->nt);
+  const int seg = seg_len(g->nt);               // checkpointed segment
+  const int K = Sh ? hist_seg_len(g->nt, Sh) : seg;
+  const long nparts = hist_parts(g->nt, K, img);
   const int nseg = (g->nt - 1 + K - 1) / K;
   const int R = K + 2;
   // two-step path: BF16 low parts of the four work fields and the checkpoints
@@ -1674,7 +1682,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   // (two-step path: the adjoint ring's BF16 low parts add R / 2 fields)
   const long per_shot = (nf + (keep ? 0 : K) + R + (two ? 2L + (R + 1) / 2 : 0L) + ck_fields) * d.field * 4 +
                         (long)geo->nrec * 64;
-  const int S = Sh ? Sh : choose_batch(ctx, per_shot, fixed, geo->nshots);
+  const int S = Sh ? Sh : choose_batch(ctx, per_shot, fixed(nparts), geo->nshots);
   auto batches = split_batches(geo->nshots, S);
   choose_steps(ctx, c.d, S, true);
   TableSet ts = build_table_set(d, geo, batches, two);
@@ -1689,7 +1697,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   unsigned short *lows = nullptr, *ckpt_lo = nullptr, *ring_lo = nullptr;
   float *parts = nullptr;
   cv.add(&acc, img);
-  cv.add(&parts, kImageGroups * img);
+  cv.add(&parts, nparts * img);
   cv.add(&pairs, nf * d.field * S);
   if (!cache && !keep) cv.add(&ckpt, 2L * nseg * d.field * S);
   if (two) {
@@ -1755,7 +1763,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
           if ((rc = march2_back_lambda(ctx, c, ring, ring_stride, R, Sb, n0, n1, t, data_b, g->nt, st, ring_lo)))
             return rc;
           HIPCHK(launch_ext_image(hist_b + (long)n0 * d.field, d.field, hist_stride, ring, d.field, ring_stride, R, n0,
-                                  Sb, nk, eg, acc, parts, st, short_seg ? kImgChain : kImgChainLong));
+                                  Sb, nk, seg, eg, acc, parts, (int)nparts, st));
           continue;
         }
         Ring4 wu(pairs, d.field * Sb);
@@ -1771,7 +1779,8 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
         if (rc) return rc;
         if ((rc = march2_back_lambda(ctx, c, ring, ring_stride, R, Sb, n0, n1, t, data_b, g->nt, st, ring_lo)))
           return rc;
-        HIPCHK(launch_ext_image(t2, d.field, t2_stride, ring, d.field, ring_stride, R, n0, Sb, nk, eg, acc, parts, st));
+        HIPCHK(launch_ext_image(t2, d.field, t2_stride, ring, d.field, ring_stride, R, n0, Sb, nk, seg, eg, acc, parts,
+                               (int)nparts, st));
       }
       continue;
     }
@@ -1818,7 +1827,8 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
         with_rec_inject(a, t, data_b, g->nt, k);
         HIPCHK(launch_step(a, d.TX, kModePlain, st));
       }
-      HIPCHK(launch_ext_image(t2, d.field, t2_stride, ring, d.field, ring_stride, R, n0, Sb, nk, eg, acc, parts, st));
+      HIPCHK(launch_ext_image(t2, d.field, t2_stride, ring, d.field, ring_stride, R, n0, Sb, nk, seg, eg, acc, parts,
+                               (int)nparts, st));
     }
   }
   HIPCHK(launch_ext_finalize(acc, vel, eg, (float)g->dt, nullptr, nullptr, ptilde_out, st));
@@ -1849,6 +1859,7 @@ namespace {
 // ---------------------------------------------------------------------------
 struct GradPlan {
   int K, nseg, R;
+  int seg;                  // checkpointed segment: K, or several to a segment with histories
   bool hist = false;
   long ck_stride, seg_stride, ring_stride;
   // first slot of segment start n0 in the T2 buffers
@@ -1859,7 +1870,8 @@ struct GradPlan {
 GradPlan grad_plan(const Dims &d, int nt, int hist_shots = 0) {
   GradPlan p;
   p.hist = hist_shots > 0;
-  p.K = p.hist ? hist_seg_len(nt, hist_shots) : seg_len(nt);
+  p.seg = seg_len(nt);
+  p.K = p.hist ? hist_seg_len(nt, hist_shots) : p.seg;
   p.nseg = (nt - 1 + p.K - 1) / p.K;
   p.R = p.K + 2;
   p.ck_stride = p.hist ? 0L : 2L * p.nseg * d.field;
@@ -1871,6 +1883,7 @@ GradPlan grad_plan(const Dims &d, int nt, int hist_shots = 0) {
 struct GradWork {       // per-batch working fields (+ partial images of the imaging kernel)
   float *pairs, *t2u, *t2d, *lam, *er, *rho;
   float *parts = nullptr;
+  long nparts = 0;
 };
 
 int grad_forward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, const GradPlan &pl,
@@ -2062,10 +2075,10 @@ int grad_backward_batch(fwime_ctx_t *ctx, const Common &c, const ExtGeom &eg, co
         HIPCHK(launch_step(a, d.TX, kModeNu, st));
       }
     }
-    HIPCHK(launch_ext_image(t2u, d.field, pl.seg_stride, wk.lam, d.field, pl.ring_stride, R, n0, Sb, nk, eg, acc,
-                            wk.parts, st, pl.hist ? kImgChainLong : kImgChain));
+    HIPCHK(launch_ext_image(t2u, d.field, pl.seg_stride, wk.lam, d.field, pl.ring_stride, R, n0, Sb, nk, pl.seg, eg,
+                            acc, wk.parts, (int)wk.nparts, st));
     HIPCHK(launch_grad_accum(t2u, t2d, d.field, pl.seg_stride, wk.lam, wk.rho, d.field, pl.ring_stride, R, n0,
-                             Sb, nk, d.NZ, d.NX, d.LZ, gacc, st));
+                             Sb, nk, pl.seg, d.NZ, d.NX, d.LZ, gacc, st));
   }
   return FWIME_OK;
 }
@@ -2163,8 +2176,8 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   const long hist_elems = (g->nt - 1L) * dd.field * geo->nshots;
   const bool use_hist = use_cache && hist_batch(ctx, geo->nshots, 0, [&](int S) {
     // beside it, at the same time: the rings and chunks of B~ and B~*
-    const long K = hist_seg_len(g->nt, S);
-    return ((g->nt - 1L + 16 + 2 * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + (size_t)img * (8 + 4 * kImageGroups);
+    const int K = hist_seg_len(g->nt, S);
+    return ((g->nt - 1L + 16 + 2 * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + (size_t)img * (8 + 4 * hist_parts(g->nt, K, img));
   }, ctx->vp_bytes) > 0;
   // solver vectors, kept in the context between calls
   float *r = nullptr, *sdir = nullptr, *q = nullptr, *b = nullptr, *dres = nullptr, *dtmp = nullptr,
@@ -2232,7 +2245,7 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   };
   auto adj = [&](const float *d, float *x) {
     return tau ? fwime_born_ext_tau_adj(ctx, g, vel, geo, nh, lag, d, x, stream)
-               : born_ext_adj_run(ctx, g, vel, geo, nh, d, x, stream, cp, true);
+               : born_ext_adj_run(ctx, g, vel, geo, nh, d, x, stream, cp);
   };
   if ((rc = adj(dres, b))) return rc;
   HIPCHK(launch_zero(ptilde_out, img, st));
@@ -2297,15 +2310,18 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   ExtGeom eg{d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, nh, (nh - 1) / 2};
   const long img = (long)nh * d.nx * d.nz;
   const long nrt = (long)geo->nrec * g->nt;
-  const size_t fixed = (size_t)d.field * 12 + (size_t)img * 4 * (5 + kImageGroups);
+  auto fixed = [&](const GradPlan &p) {
+    return (size_t)d.field * 12 + (size_t)img * 4 * (5 + hist_parts(g->nt, p.K, img));
+  };
   auto per_shot = [&](const GradPlan &p) {
     return grad_work_per_shot(d, p, ctx->two_step) + 2 * p.ck_stride * 4 + 2 * nrt * 4 + (long)geo->nrec * 64;
   };
   const int Sh = hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
-    return fixed + (size_t)per_shot(grad_plan(d, g->nt, S)) * S;
+    const GradPlan p = grad_plan(d, g->nt, S);
+    return fixed(p) + (size_t)per_shot(p) * S;
   });
   const GradPlan pl = grad_plan(d, g->nt, Sh);
-  const int S = Sh ? Sh : choose_batch(ctx, per_shot(pl), fixed, geo->nshots);
+  const int S = Sh ? Sh : choose_batch(ctx, per_shot(pl), fixed(pl), geo->nshots);
   auto batches = split_batches(geo->nshots, S);
   choose_steps(ctx, c.d, S, false);
   TableSet ts = build_table_set(d, geo, batches, ctx->two_step);
@@ -2330,7 +2346,8 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   cv.add(&uck, pl.ck_stride * S);
   cv.add(&dck, pl.ck_stride * S);
   carve_work(cv, wk, d, pl, S, ctx->two_step);
-  cv.add(&wk.parts, kImageGroups * img);
+  wk.nparts = hist_parts(g->nt, pl.K, img);
+  cv.add(&wk.parts, wk.nparts * img);
   cv.add(&drec, nrt * S);
   cv.add(&ddrec, nrt * S);
   if ((rc = arena_get(ctx, cv))) return rc;
@@ -2485,7 +2502,7 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
       }, st);
       if (rc) return rc;
       HIPCHK(launch_grad_accum2(hu + (long)n0 * d.field, hdu + (long)n0 * d.field, d.field, hs, lam, d.field, hs, R,
-                                n0, rho, d.field, rs, RR, n0, Sb, n1 - n0, d.NZ, d.NX, d.LZ, gacc, st));
+                                n0, rho, d.field, rs, RR, n0, Sb, n1 - n0, kTauChunk, d.NZ, d.NX, d.LZ, gacc, st));
     }
     // B~_tau^T r (scaled by 2 / (v^3 dt^2) in the kernel)
     HIPCHK(launch_tau_image(hu, d.field, hs, lam, d.field, hs, ns, Sb, eg, lag, vel, (float)g->dt, acc, st));
@@ -2682,7 +2699,8 @@ int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tp, const float *adjsrc,
   cv.add(&imgs, img);
   cv.add(&gacc, d.field);
   carve_work(cv, wk, d, pl, S, ctx->two_step, !pl.hist);
-  cv.add(&wk.parts, kImageGroups * img);
+  wk.nparts = hist_parts(g->nt, pl.K, img);
+  cv.add(&wk.parts, wk.nparts * img);
   if ((rc = arena_get(ctx, cv))) return rc;
   if (pl.hist) {
     wk.t2u = tp->uck;

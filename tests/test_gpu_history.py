@@ -119,3 +119,28 @@ def test_vp_step_bits_do_not_depend_on_the_store(nz, nx, nt, nshots, nh):
         got.append((p.cpu().numpy(), np.asarray(phi)))
         ctx.close()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("nz,nx,nb,nt,nshots,nh", [(24, 32, 8, 3, 2, 5), (57, 33, 5, 158, 24, 5), (40, 50, 8, 301, 1, 19),
+                                                   (60, 70, 9, 181, 3, 37)])
+def test_bits_do_not_depend_on_the_store(nz, nx, nb, nt, nshots, nh):
+    """Images and gradient sums are formed per checkpointed segment, from the last to the first, whether the wavefields'
+    T2 terms are kept whole or recomputed: no FP32 sum is longer than a checkpointed segment's."""
+    import torch
+    import paper_2206_02362_amd as fw
+    print(f"case: bits of history and checkpoints {nz}x{nx} nt{nt} {nshots} shots nh{nh}", file=sys.stderr, flush=True)
+    w = synth.tiny(nz=nz, nx=nx, nb=nb, nt=nt, nshots=nshots, nh=nh, seed=14)
+    grid, tv, tg = gpu_problem(w)
+    pt = _dev(0.2 * synth.random_ptilde(nh, nz, nx, 5))
+    data = _dev(np.random.default_rng(6).standard_normal((nshots, w.nrec, nt)))
+    got = []
+    for budget in (0, 1 << 30):
+        ctx = fw.Context(0, hbm_budget_bytes=budget)
+        v, p = tv.clone().requires_grad_(True), pt.clone().requires_grad_(True)
+        pred = fw.predicted_data(v, p, ctx, grid, tg)
+        got.append([pred.detach(), *torch.autograd.grad(0.5 * (pred - data).square().sum(), (v, p)),
+                    *ctx.gradient(grid, tv, tg, pt, data, 1e-3, synth.dso_weights(nh)),
+                    ctx.born_ext_fwd(grid, tv, tg, pt), ctx.born_ext_adj(grid, tv, tg, data, nh)])
+        ctx.close()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
