@@ -44,6 +44,7 @@ struct fwime_ctx {
   int tile_x = 32;
   bool two_step = true;         // two or four time steps per launch (else one)
   int steps = 0;                // 2 or 4: steps per launch whatever the size (0: chosen by size)
+  bool frugal = false;          // a call that did not fit runs again with less scratch (see or_frugally)
   size_t tape_bytes = 0;        // device memory held by live tapes
   // memory of the largest tape freed so far, for the next one: a tape of whole
   // histories is up to gigabytes, allocated and released on every call else
@@ -162,7 +163,7 @@ Dims make_dims(const fwime_grid_t *g, int tx) {
 constexpr int kStep4MaxTiles = 320, kStep4MaxTilesDF = 160, kStep4MaxNarrow = 256;
 
 void choose_steps(const fwime_ctx_t *ctx, Dims &d, int S, bool df) {
-  if (!ctx->two_step) return;
+  if (!ctx->two_step || ctx->frugal) return;
   const long tiles = (long)d.ntz2 * d.ntx * S;
   if (ctx->steps ? ctx->steps != 4 : tiles > (df ? kStep4MaxTilesDF : kStep4MaxTiles)) return;
   if ((long)d.ntz4 * ((d.NX + 7) / 8) * S + 8 >= (1L << 20)) return;   // the kernel's tile arithmetic
@@ -262,6 +263,21 @@ int arena_get(fwime_ctx_t *ctx, Carve &cv) {
     p += it.second;
   }
   return FWIME_OK;
+}
+
+// Result rc of a call's allocations, or, where they did not fit (rc is
+// FWIME_ENOMEM; nothing is written yet) and the call can do with less scratch,
+// of the call made again with less: two steps per launch, whose source and
+// receiver lists take up to 52 bytes a receiver against 76 with four.
+template <class Call>
+int or_frugally(fwime_ctx_t *ctx, int rc, bool less, Call call) {
+  if (rc != FWIME_ENOMEM || !less || ctx->frugal) return rc;
+  struct Guard {
+    fwime_ctx_t *c;
+    ~Guard() { c->frugal = false; }
+  } guard{ctx};
+  ctx->frugal = true;
+  return call();
 }
 
 // ---------------------------------------------------------------------------
@@ -1267,7 +1283,8 @@ int fwime_model(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, const
   cv.add(&c.gx, d.NX + kGxPad);
   cv.add(&c.tables, table_set_ints(ts) + 64 * batches.size() * 8);
   cv.add(&fields, nf * d.field * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] { return fwime_model(ctx, g, vel, geo, data, stream); });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
 
@@ -1383,7 +1400,10 @@ static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   if (two) cv.add(&lows, 8 * d.field * S);
   if (!bg) cv.add(&t2, (long)KC * d.field * S);
   cv.add(&sc, (long)KC * d.field * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] {
+      return born_ext_fwd_run(ctx, g, vel, geo, nh, ptilde, data, stream, bg);
+    });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
   HIPCHK(launch_ext_coef(ptilde, vel, eg, (float)g->dt, coef, st));
@@ -1538,7 +1558,10 @@ int fwime_born_ext_tau_fwd(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
   cv.add(&lows, 4 * d.field * S);
   cv.add(&hist, (long)ns * d.field * S);
   cv.add(&sc, (long)ns * d.field * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] {
+      return fwime_born_ext_tau_fwd(ctx, g, vel, geo, ntau, lag, ptau, data, stream);
+    });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
   HIPCHK(launch_ext_coef(ptau, vel, eg, (float)g->dt, coef, st));
@@ -1600,7 +1623,10 @@ int fwime_born_ext_tau_adj(fwime_ctx_t *ctx, const fwime_grid_t *g, const float 
   cv.add(&lows, 4 * d.field * S);
   cv.add(&hist, (long)ns * d.field * S);
   cv.add(&lam, (long)R * d.field * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] {
+      return fwime_born_ext_tau_adj(ctx, g, vel, geo, ntau, lag, data, ptau_out, stream);
+    });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
   HIPCHK(launch_zero(ptau_out, (long)ntau * d.nx * d.nz, st));
@@ -1709,7 +1735,10 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   if (keep && own_hist) cv.add(&hist, hist_stride * S);
   if (!keep) cv.add(&t2, (long)K * d.field * S);
   cv.add(&ring, (long)R * d.field * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] {
+      return born_ext_adj_run(ctx, g, vel, geo, nh, data, ptilde_out, stream, cache);
+    });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
   HIPCHK(launch_zero_d(acc, img, st));
@@ -2350,7 +2379,10 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   cv.add(&wk.parts, wk.nparts * img);
   cv.add(&drec, nrt * S);
   cv.add(&ddrec, nrt * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] {
+      return fwime_gradient(ctx, g, vel, geo, nh, ptilde, dobs, eps, dso, obj, grad_vel, grad_ptilde, stream);
+    });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
   std::vector<float> e2(nh);
@@ -2447,7 +2479,10 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   cv.add(&rho, rs * S);
   cv.add(&drec, nrt * S);
   cv.add(&ddrec, nrt * S);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  if ((rc = arena_get(ctx, cv)))
+    return or_frugally(ctx, rc, d.T == 4, [&] {
+      return fwime_gradient_tau(ctx, g, vel, geo, ntau, lag, ptau, dobs, eps, dso, obj, grad_vel, grad_ptau, stream);
+    });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
   if ((rc = setup_common(ctx, c, g, vel, st))) return rc;
   std::vector<float> e2(ntau);
@@ -2586,9 +2621,11 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   tc.add(&tp->wav, (long)geo->nshots * g->nt);
   tc.add(&tp->uck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
   tc.add(&tp->dck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
+  const bool less = d.T == 4;
+  auto again = [&] { return fwime_forward_tape(ctx, g, vel, geo, nh, ptilde, data, tape_out, stream); };
   if (ctx->budget && ctx->tape_bytes + tc.total + ctx->arena_bytes > ctx->budget) {
     delete tp;
-    return set_err(ctx, FWIME_ENOMEM, "tape does not fit the HBM budget");
+    return or_frugally(ctx, set_err(ctx, FWIME_ENOMEM, "tape does not fit the HBM budget"), less, again);
   }
   bool small = false;                      // a fraction of the spare, which waits for a large tape
   {
@@ -2606,7 +2643,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
     if (device_alloc(ctx, &tp->mem, tc.total) != hipSuccess) {
       (void)hipGetLastError();
       delete tp;
-      return set_err(ctx, FWIME_ENOMEM, "hipMalloc of the tape failed");
+      return or_frugally(ctx, set_err(ctx, FWIME_ENOMEM, "hipMalloc of the tape failed"), less, again);
     }
     tp->capacity = tc.total;
   }
@@ -2648,7 +2685,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   carve_work(cv, wk, d, pl, S, ctx->two_step, !pl.hist);
   cv.add(&drec, nrt * S);
   cv.add(&ddrec, nrt * S);
-  if ((rc = arena_get(ctx, cv))) return fail(rc);
+  if ((rc = arena_get(ctx, cv))) return or_frugally(ctx, fail(rc), less, again);
   if (pl.hist) {
     wk.t2u = tp->uck;
     wk.t2d = tp->dck;

@@ -1,0 +1,66 @@
+"""Device memory of the host runtime, checked on the CPU.
+
+Every test runs calls of libfwime.so in a process of its own on a HIP runtime
+without a device (fake_hip.cpp): allocations are counted and can be made to
+fail, kernels are counted and not run.
+"""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_2206_02362_amd", "libfwime.so")
+
+pytestmark = [pytest.mark.skipif(not os.path.exists(LIB), reason="libfwime.so not built"),
+              pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")]
+
+
+@pytest.fixture(scope="session")
+def fake(tmp_path_factory):
+    so = tmp_path_factory.mktemp("fake") / "libfake_hip.so"
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-o", str(so), os.path.join(HERE, "fake_hip.cpp")],
+                   check=True)
+
+    def run(code, **env):
+        r = subprocess.run([sys.executable, os.path.join(HERE, "fake_device.py"), str(so), code], text=True,
+                           capture_output=True, env={**os.environ, **env})
+        assert r.returncode == 0, r.stderr[-2000:]
+        return r.stdout.split()
+    return run
+
+
+def test_calls_that_fit_with_two_steps_fit_with_four(fake):
+    """The four-step kernel's source and receiver lists are longer than the two-step kernel's.  A call that its budget or
+    the static scratch array holds with the shorter lists is accepted."""
+    code = """
+for budget in (200 << 10, 400 << 10, 800 << 10, 1600 << 10, 3200 << 10, 6400 << 10):
+    for nz, nx, nrec in ((20, 30, 1), (20, 30, 4000), (60, 90, 90), (60, 90, 7000), (100, 200, 200), (100, 200, 20000)):
+        f = Fake(budget=budget)
+        p = f.problem(nz, nx, 50, 1, 10, np.arange(nrec) % nx)
+        print(f.model(p))
+        f.close()
+f = Fake()
+for nrec in (500000, 800000, 900000, 1000000, 1100000):
+    p = f.problem(100, 200, 50, 1, 10, np.arange(nrec) % 200)
+    print(f.lib.fwime_model_static(f.h, p[0], PTR, p[1], PTR, None))
+"""
+    two, four, chosen = (fake(code, **e) for e in ({"FWIME_STEPS": "2"}, {"FWIME_STEPS": "4"}, {}))
+    assert "0" in two and "2" in two                    # both sides of the limits
+    assert chosen == two and four == two
+
+
+def test_footprint_budgets_of_small_requests_hold(fake):
+    """Every operator of a request whose budget is its footprint is accepted where it was with the two-step lists."""
+    code = """
+for nz, nx, shots in ((60, 90, 1), (100, 200, 1), (100, 200, 4), (40, 60, 8)):
+    q = Fake()
+    p = q.problem(nz, nx, 300, shots)
+    for op, call in enumerate(("model", "born_fwd", "born_adj", "gradient")):
+        f = Fake(budget=q.footprint(p, nx, 11, op))
+        print(getattr(f, call)(*((p,) if op == 0 else (p, 11))))
+        f.close()
+"""
+    assert fake(code) == fake(code, FWIME_STEPS="2")
