@@ -267,8 +267,10 @@ int arena_get(fwime_ctx_t *ctx, Carve &cv) {
 
 // Result rc of a call's allocations, or, where they did not fit (rc is
 // FWIME_ENOMEM; nothing is written yet) and the call can do with less scratch,
-// of the call made again with less: two steps per launch, whose source and
-// receiver lists take up to 52 bytes a receiver against 76 with four.
+// of the call made again with less: checkpoints instead of whole histories
+// (their size goes by what was free, not by what one allocation finds), and two
+// steps per launch, whose source and receiver lists take up to 52 bytes a
+// receiver against 76 with four.
 template <class Call>
 int or_frugally(fwime_ctx_t *ctx, int rc, bool less, Call call) {
   if (rc != FWIME_ENOMEM || !less || ctx->frugal) return rc;
@@ -1092,7 +1094,7 @@ long hist_parts(int nt, int K, long img) {
 // held: bytes of another buffer that this call reuses.
 template <class Bytes>
 int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, size_t held = 0) {
-  if (ctx->fixed || ctx->budget) return 0;
+  if (ctx->fixed || ctx->budget || ctx->frugal) return 0;
   size_t avail = 0, total = 0;
   if (hipMemGetInfo(&avail, &total) != hipSuccess) return 0;
   const size_t cap = (avail + ctx->arena_bytes + spare_bytes(ctx) + held) / 3;
@@ -1401,7 +1403,7 @@ static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   if (!bg) cv.add(&t2, (long)KC * d.field * S);
   cv.add(&sc, (long)KC * d.field * S);
   if ((rc = arena_get(ctx, cv)))
-    return or_frugally(ctx, rc, d.T == 4, [&] {
+    return or_frugally(ctx, rc, d.T == 4 || Sh > 0, [&] {
       return born_ext_fwd_run(ctx, g, vel, geo, nh, ptilde, data, stream, bg);
     });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
@@ -1736,7 +1738,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   if (!keep) cv.add(&t2, (long)K * d.field * S);
   cv.add(&ring, (long)R * d.field * S);
   if ((rc = arena_get(ctx, cv)))
-    return or_frugally(ctx, rc, d.T == 4, [&] {
+    return or_frugally(ctx, rc, d.T == 4 || Sh > 0, [&] {
       return born_ext_adj_run(ctx, g, vel, geo, nh, data, ptilde_out, stream, cache);
     });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
@@ -1891,6 +1893,12 @@ struct GradPlan {
   int seg;                  // checkpointed segment: K, or several to a segment with histories
   bool hist = false;
   long ck_stride, seg_stride, ring_stride;
+  void set_segment(const Dims &d, int nt, int steps) {
+    K = steps;
+    nseg = (nt - 1 + K - 1) / K;
+    R = K + 2;
+    ring_stride = (long)R * d.field;
+  }
   // first slot of segment start n0 in the T2 buffers
   long t2_off(const Dims &d, int n0) const { return hist ? (long)n0 * d.field : 0L; }
 };
@@ -1900,12 +1908,9 @@ GradPlan grad_plan(const Dims &d, int nt, int hist_shots = 0) {
   GradPlan p;
   p.hist = hist_shots > 0;
   p.seg = seg_len(nt);
-  p.K = p.hist ? hist_seg_len(nt, hist_shots) : p.seg;
-  p.nseg = (nt - 1 + p.K - 1) / p.K;
-  p.R = p.K + 2;
+  p.set_segment(d, nt, p.hist ? hist_seg_len(nt, hist_shots) : p.seg);
   p.ck_stride = p.hist ? 0L : 2L * p.nseg * d.field;
   p.seg_stride = (p.hist ? (long)(nt - 1) : (long)p.K) * d.field;
-  p.ring_stride = (long)p.R * d.field;
   return p;
 }
 
@@ -2213,28 +2218,39 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
         *e2d2 = nullptr;
   double *part = nullptr, *res = nullptr;
   AdjCache cache;
-  Carve cv;
-  if (use_hist) {
-    cv.add(&cache.hist, hist_elems);
-  } else if (use_cache) {
-    cv.add(&cache.ckpt, ck_elems);
-    cv.add(&cache.ckpt_lo, ck_elems);
-  }
-  cv.add(&r, img);
-  cv.add(&sdir, img);
-  cv.add(&q, img);
-  cv.add(&b, img);
-  cv.add(&dres, ndata);
-  cv.add(&dtmp, ndata);
-  cv.add(&e2d2, nh);
-  cv.add(&part, dot_partials());
-  cv.add(&res, 1);
+  auto layout = [&](bool whole) {
+    Carve cv;
+    cache = AdjCache();
+    if (whole) {
+      cv.add(&cache.hist, hist_elems);
+    } else if (use_cache) {
+      cv.add(&cache.ckpt, ck_elems);
+      cv.add(&cache.ckpt_lo, ck_elems);
+    }
+    cv.add(&r, img);
+    cv.add(&sdir, img);
+    cv.add(&q, img);
+    cv.add(&b, img);
+    cv.add(&dres, ndata);
+    cv.add(&dtmp, ndata);
+    cv.add(&e2d2, nh);
+    cv.add(&part, dot_partials());
+    cv.add(&res, 1);
+    return cv;
+  };
+  Carve cv = layout(use_hist);
   if (cv.total > ctx->vp_bytes) {
     HIPCHK(hipStreamSynchronize(st));
     if (ctx->vp) HIPCHK(hipFree(ctx->vp));
     ctx->vp = nullptr;
     ctx->vp_bytes = 0;
-    if (device_alloc(ctx, &ctx->vp, cv.total) != hipSuccess) {
+    hipError_t e = device_alloc(ctx, &ctx->vp, cv.total);
+    if (e != hipSuccess && use_hist) {             // checkpoints, then
+      (void)hipGetLastError();
+      cv = layout(false);
+      e = device_alloc(ctx, &ctx->vp, cv.total);
+    }
+    if (e != hipSuccess) {
       ctx->vp = nullptr;
       (void)hipGetLastError();
       return set_err(ctx, FWIME_ENOMEM, "cannot allocate the solver vectors");
@@ -2380,7 +2396,7 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   cv.add(&drec, nrt * S);
   cv.add(&ddrec, nrt * S);
   if ((rc = arena_get(ctx, cv)))
-    return or_frugally(ctx, rc, d.T == 4, [&] {
+    return or_frugally(ctx, rc, d.T == 4 || Sh > 0, [&] {
       return fwime_gradient(ctx, g, vel, geo, nh, ptilde, dobs, eps, dso, obj, grad_vel, grad_ptilde, stream);
     });
   if ((rc = upload_tables(ctx, ts, c.tables, st))) return rc;
@@ -2621,7 +2637,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   tc.add(&tp->wav, (long)geo->nshots * g->nt);
   tc.add(&tp->uck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
   tc.add(&tp->dck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
-  const bool less = d.T == 4;
+  const bool less = d.T == 4 || Sh > 0;
   auto again = [&] { return fwime_forward_tape(ctx, g, vel, geo, nh, ptilde, data, tape_out, stream); };
   if (ctx->budget && ctx->tape_bytes + tc.total + ctx->arena_bytes > ctx->budget) {
     delete tp;
@@ -2716,7 +2732,7 @@ int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tp, const float *adjsrc,
   HIPCHK(hipSetDevice(ctx->device));
   const fwime_grid_t *g = &tp->g;
   const Dims &d = tp->d;
-  const GradPlan &pl = tp->pl;
+  GradPlan pl = tp->pl;
   ExtGeom eg{d.nz, d.nx, d.nb, d.NZ, d.NX, d.LZ, tp->nh, (tp->nh - 1) / 2};
   const long img = (long)tp->nh * d.nx * d.nz;
   const long nrt = (long)tp->nrec * g->nt;
@@ -2731,14 +2747,22 @@ int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tp, const float *adjsrc,
   double *acc = nullptr;
   float *imgs = nullptr, *gacc = nullptr;
   GradWork wk;
-  Carve cv;
-  cv.add(&acc, img);
-  cv.add(&imgs, img);
-  cv.add(&gacc, d.field);
-  carve_work(cv, wk, d, pl, S, ctx->two_step, !pl.hist);
-  wk.nparts = hist_parts(g->nt, pl.K, img);
-  cv.add(&wk.parts, wk.nparts * img);
-  if ((rc = arena_get(ctx, cv))) return rc;
+  auto scratch = [&]() {
+    Carve cv;
+    cv.add(&acc, img);
+    cv.add(&imgs, img);
+    cv.add(&gacc, d.field);
+    carve_work(cv, wk, d, pl, S, ctx->two_step, !pl.hist);
+    wk.nparts = hist_parts(g->nt, pl.K, img);
+    cv.add(&wk.parts, wk.nparts * img);
+    return arena_get(ctx, cv);
+  };
+  rc = scratch();
+  if (rc == FWIME_ENOMEM && pl.hist && pl.K > pl.seg) {
+    pl.set_segment(d, g->nt, pl.seg);              // rings of checkpointed segments, then
+    rc = scratch();
+  }
+  if (rc) return rc;
   if (pl.hist) {
     wk.t2u = tp->uck;
     wk.t2d = tp->dck;

@@ -64,3 +64,30 @@ for nz, nx, shots in ((60, 90, 1), (100, 200, 1), (100, 200, 4), (40, 60, 8)):
         f.close()
 """
     assert fake(code) == fake(code, FWIME_STEPS="2")
+
+
+def test_history_that_cannot_be_allocated_gives_way_to_checkpoints(fake):
+    """Where no allocation of a history's size succeeds, every operator runs with checkpoints, as with a budget."""
+    code = """
+f = Fake(other=100 * GiB)
+p = f.problem(300, 1700, 800, 4, 60)
+b = Fake(other=100 * GiB, budget=80 * GiB)
+assert (b.born_fwd(p, 11), b.born_adj(p, 11), b.gradient(p, 11)) == (0, 0, 0)
+most = b.info().arena_bytes
+b.close()
+f.hip.fake_largest(most + (1 << 20))
+print(f.born_fwd(p, 11), f.born_adj(p, 11), f.gradient(p, 11), f.vp(p, 11), f.error())
+rc, t = f.forward(p, 11)
+print(rc, f.backward(t))
+f.free(t)
+# a tape with whole histories whose backward finds no room for long rings
+f.hip.fake_largest(2 ** 64 - 1)
+f.trim()
+rc, t = f.forward(p, 11)
+f.hip.fake_largest(1)
+assert f.backward(t) == 2                          # nothing at all
+f.hip.fake_largest(most + (1 << 20))
+assert f.lib.fwime_ctx_trim(f.h, None) == 0
+print(rc, f.backward(t))
+"""
+    assert fake(code) == ["0"] * 8
