@@ -92,9 +92,11 @@ typedef struct fwime_ctx fwime_ctx_t;
 /* Create a context on `device`.  It owns all scratch memory (wavefield
  * buffers, checkpoints, geometry tables) and never allocates beyond
  * `hbm_budget_bytes` (0 = no limit besides the device).  A context without a
- * budget may use up to a third of the device's free memory to keep wavefield
- * histories instead of recomputing them; one with a budget does not.  Returns FWIME_OK and
- * sets *out, or an error code. */
+ * budget keeps wavefield histories instead of recomputing them as long as what
+ * it then holds (its arena, the solver's buffer, live tapes and the memory kept
+ * of freed ones) stays within a third of the device memory that others leave;
+ * one with a budget does not.  Returns FWIME_OK and sets *out, or an error
+ * code. */
 int fwime_ctx_create(int device, size_t hbm_budget_bytes, fwime_ctx_t **out);
 
 /* Release every allocation of the context (synchronizes the device). */
@@ -199,14 +201,14 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *grid, const float *
  * vectors (4 model-size and 2 data-size arrays) stay in the context until
  * fwime_ctx_trim or fwime_ctx_destroy, and count against its HBM budget.
  * Without a budget, the background's T2 terms of every shot and step (nt - 1
- * padded fields per shot) are kept for the whole call when they fit in a third
- * of the free memory, so B~ and each B~* after the first propagate one field
+ * padded fields per shot) are kept for the whole call when they fit (see
+ * fwime_ctx_create), so B~ and each B~* after the first propagate one field
  * instead of two.  Otherwise, when they fit in half of the free memory (and of
  * the budget), the background checkpoints of every shot (6 bytes x
  * 2 ceil((nt-1)/K) padded fields per shot, K = ceil(sqrt(nt))) are kept, so
- * each B~* after the first skips its background forward pass.  The iterates
- * differ by the order of the image's FP32 partial sums at most
- * (FWIME_VP_NOCACHE=1 in the environment turns both off).
+ * each B~* after the first skips its background forward pass.  The results are
+ * the same bit for bit with either and without (FWIME_VP_NOCACHE=1 in the
+ * environment turns both off).
  * Argument errors (FWIME_EINVAL) are reported before anything is written; a
  * failure during the iteration leaves ptilde_out and phi_out unspecified. */
 int fwime_vp_solve(fwime_ctx_t *ctx, const fwime_grid_t *grid, const float *vel,
@@ -327,7 +329,7 @@ int fwime_footprint(const fwime_grid_t *grid, int32_t nshots, int32_t nrec, int3
  * the tape, counted against the context's HBM budget), copies of vel, ptilde
  * and the wavelets and, of the background and the scattered field of every
  * shot, either the T2 terms of every step (2 (nt - 1) padded fields per shot;
- * without a budget, when they fit in a third of the free memory) or
+ * without a budget, when they fit, see fwime_ctx_create) or
  * sqrt(nt)-spaced checkpoints, from which the backward recomputes one segment
  * at a time.  A tape serves exactly one backward (its checkpoints are
  * consumed); free it with fwime_tape_free in every case. */
@@ -344,7 +346,8 @@ int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tape, const float *adjsr
 
 /* Release a tape (synchronizes the device); null is ignored.  A context
  * without a budget keeps the memory of the largest tape freed, for the next
- * one, until fwime_ctx_trim or fwime_ctx_destroy. */
+ * one, until another of its calls needs the room, fwime_ctx_trim or
+ * fwime_ctx_destroy. */
 void fwime_tape_free(fwime_tape_t *tape);
 
 /* Linear spline operator S of Section 2: the model lives on a spline grid of

@@ -51,7 +51,8 @@ struct fwime_ctx {
   // (data and gradient through autograd on 100 x 200, one shot, a tape of
   // 0.65 GB: 13.4 ms with an allocation per call, 12.9 ms without).
   // One buffer at most, none under a budget; counted as free memory, and given
-  // back when an allocation fails, by fwime_ctx_trim and with the context.
+  // back when one of the context's allocations fails or a history needs the
+  // room, by fwime_ctx_trim and with the context.
   // Tapes are freed on any thread, so tape_mu guards these three.
   std::mutex tape_mu;
   void *spare = nullptr;
@@ -63,8 +64,9 @@ struct fwime_ctx {
   int graph_steps = 64;                   // steps per captured graph
   hipGraph_t graph = nullptr;             // last batch graph, released after the
   hipGraphExec_t graph_exec = nullptr;    // next stream synchronization
-  void *vp = nullptr;                     // variable-projection solver vectors
+  void *vp = nullptr;                     // variable-projection solver vectors, background history
   size_t vp_bytes = 0;
+  bool vp_busy = false;                   // while the solver runs
   // optional timing of the stencil launch loop of the modeling calls: two
   // events recorded on the call's stream around its launches
   bool timing = false;
@@ -207,12 +209,35 @@ size_t spare_bytes(fwime_ctx_t *ctx) {
   return ctx->spare_bytes;
 }
 
-// hipMalloc that gives the spare back when memory is short
+size_t live_tape_bytes(fwime_ctx_t *ctx) {
+  std::lock_guard<std::mutex> lock(ctx->tape_mu);
+  return ctx->tape_bytes;
+}
+
+// Frees what the context holds between calls, except the buffer of `owner`:
+// the spare, the solver's buffer and the arena.  Between the input checks of a
+// call, which wait for the stream, and its own use of them they are idle.
+void release_idle(fwime_ctx_t *ctx, void **owner, bool spare = true) {
+  if (spare) release_spare(ctx);
+  if (ctx->vp && !ctx->vp_busy && owner != &ctx->vp) {
+    (void)hipFree(ctx->vp);
+    ctx->vp = nullptr;
+    ctx->vp_bytes = 0;
+  }
+  if (ctx->arena && owner != &ctx->arena) {
+    (void)hipFree(ctx->arena);
+    ctx->arena = nullptr;
+    ctx->arena_bytes = 0;
+    ctx->last_arena_request = 0;         // the next one is as large as it needs to be
+  }
+}
+
+// hipMalloc that gives back what is held idle when memory is short
 hipError_t device_alloc(fwime_ctx_t *ctx, void **p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess && spare_bytes(ctx)) {
+  if (e != hipSuccess) {
     (void)hipGetLastError();
-    release_spare(ctx);
+    release_idle(ctx, p);
     e = hipMalloc(p, bytes);
   }
   return e;
@@ -1062,10 +1087,12 @@ int seg_len(int nt) {
 // segments, and images and gradient sums are formed segment by segment inside
 // them, so a result has the same bits with histories and with checkpoints.
 //
-// At most a third of the free device memory is taken for it, and only by a
-// context without a budget (one with a budget shares the device by exact
-// footprints).  All shots of the call must fit, or at least enough of them
-// that a launch still fills the device.
+// Only a context without a budget does so (one with a budget shares the device
+// by exact footprints), and what it then holds, its arena, the solver's buffer,
+// live tapes and the spare together, stays within a third of the device memory
+// that others leave: live tapes take from that third, and buffers held idle are
+// freed where they stand in its way.  All shots of the call must fit, or at
+// least enough of them that a launch still fills the device.
 // ---------------------------------------------------------------------------
 constexpr long kHistSlots = 1024;       // time slots (shots x steps) of a segment
 constexpr long kHistMinTiles = 3072;    // two rounds of two-step workgroups (six per CU)
@@ -1090,21 +1117,32 @@ long hist_parts(int nt, int K, long img) {
 }
 
 // Shots per batch that keep whole histories (0: checkpoint instead).
-// bytes(S): scratch of a batch of S shots.
-// held: bytes of another buffer that this call reuses.
+// bytes(S): what the call holds for a batch of S shots; owner: the buffer that
+// it is held in (null: a tape of its own).
 template <class Bytes>
-int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, size_t held = 0) {
+int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, void **owner) {
   if (ctx->fixed || ctx->budget || ctx->frugal) return 0;
   size_t avail = 0, total = 0;
   if (hipMemGetInfo(&avail, &total) != hipSuccess) return 0;
-  const size_t cap = (avail + ctx->arena_bytes + spare_bytes(ctx) + held) / 3;
-  if (bytes(nshots) <= cap) return nshots;
-  int lo = 0, hi = nshots;                       // largest S with bytes(S) <= cap
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) / 2;
-    (bytes(mid) <= cap ? lo : hi) = mid;
+  const size_t tapes = live_tape_bytes(ctx), spare = spare_bytes(ctx);
+  const size_t third = (avail + ctx->arena_bytes + ctx->vp_bytes + spare + tapes) / 3;
+  const size_t in_use = tapes + (ctx->vp_busy ? ctx->vp_bytes : 0);
+  const size_t cap = third > in_use ? third - in_use : 0;
+  int S = nshots;
+  if (bytes(nshots) > cap) {
+    int lo = 0, hi = nshots;                     // largest S with bytes(S) <= cap
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) / 2;
+      (bytes(mid) <= cap ? lo : hi) = mid;
+    }
+    S = lo * tiles_per_shot >= kHistMinTiles ? lo : 0;
   }
-  return lo * tiles_per_shot >= kHistMinTiles ? lo : 0;
+  if (S == 0) return 0;
+  const bool take_spare = !owner && bytes(S) >= spare / 4;   // (a small tape leaves it alone)
+  const size_t idle = (take_spare ? 0 : spare) + (owner != &ctx->vp && !ctx->vp_busy ? ctx->vp_bytes : 0) +
+                      (owner != &ctx->arena ? ctx->arena_bytes : 0);
+  if (bytes(S) + idle > cap) release_idle(ctx, owner, !take_spare);
+  return S;
 }
 
 }  // namespace
@@ -1383,7 +1421,7 @@ static int born_ext_fwd_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   // at 300 x 1700, 8 shots and nh = 61 that was about half of a 16-step launch.
   const int Sh = !two ? 0 : hist_batch(ctx, geo->nshots, 0, [&](int S) {
     return fixed + (size_t)per_shot(hist_seg_len(g->nt, S)) * S;
-  });
+  }, &ctx->arena);
   const int KC = Sh ? hist_seg_len(g->nt, Sh) : 16;
   const int S = Sh ? Sh : choose_batch(ctx, per_shot(KC), fixed, geo->nshots);
   auto batches = split_batches(geo->nshots, S);
@@ -1697,7 +1735,7 @@ static int born_ext_adj_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float
   };
   const int Sh = !two || (cache && !hist) ? 0 : hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
     return fixed(hist_parts(g->nt, hist_seg_len(g->nt, S), img)) + (size_t)hist_per_shot(S) * S;
-  });
+  }, &ctx->arena);
   const bool keep = Sh > 0 || hist;
   const int seg = seg_len(g->nt);               // checkpointed segment
   const int K = Sh ? hist_seg_len(g->nt, Sh) : seg;
@@ -2211,8 +2249,9 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   const bool use_hist = use_cache && hist_batch(ctx, geo->nshots, 0, [&](int S) {
     // beside it, at the same time: the rings and chunks of B~ and B~*
     const int K = hist_seg_len(g->nt, S);
-    return ((g->nt - 1L + 16 + 2 * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + (size_t)img * (8 + 4 * hist_parts(g->nt, K, img));
-  }, ctx->vp_bytes) > 0;
+    return ((g->nt - 1L + 16 + 2 * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + (size_t)img * (24 + 4 * hist_parts(g->nt, K, img)) +
+           (size_t)ndata * 8;
+  }, &ctx->vp) > 0;
   // solver vectors, kept in the context between calls
   float *r = nullptr, *sdir = nullptr, *q = nullptr, *b = nullptr, *dres = nullptr, *dtmp = nullptr,
         *e2d2 = nullptr;
@@ -2259,11 +2298,15 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   }
   cv.assign(ctx->vp);
   // the operators below size their shot batches from what is left of the budget
-  struct BudgetGuard {
+  struct Guard {
     fwime_ctx_t *c;
     size_t saved;
-    ~BudgetGuard() { c->budget = saved; }
+    ~Guard() {
+      c->budget = saved;
+      c->vp_busy = false;
+    }
   } guard{ctx, ctx->budget};
+  ctx->vp_busy = true;
   if (ctx->budget) ctx->budget = ctx->budget > ctx->vp_bytes ? ctx->budget - ctx->vp_bytes : 1;
 
   auto dot = [&](const float *x, const float *y, long n, double &out) -> int {
@@ -2364,7 +2407,7 @@ int fwime_gradient(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel, co
   const int Sh = hist_batch(ctx, geo->nshots, (long)d.ntz2 * d.ntx, [&](int S) {
     const GradPlan p = grad_plan(d, g->nt, S);
     return fixed(p) + (size_t)per_shot(p) * S;
-  });
+  }, &ctx->arena);
   const GradPlan pl = grad_plan(d, g->nt, Sh);
   const int S = Sh ? Sh : choose_batch(ctx, per_shot(pl), fixed(pl), geo->nshots);
   auto batches = split_batches(geo->nshots, S);
@@ -2615,8 +2658,10 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   const size_t rest = 2 * nrt * 4 + (size_t)geo->nrec * 64;
   // whole histories only if every shot's fit (the tape holds them all)
   const int Sh = hist_batch(ctx, geo->nshots, 0, [&](int S) {
-    return (grad_work_per_shot(d, grad_plan(d, g->nt, S), ctx->two_step) + rest) * S + (size_t)d.field * 8;
-  });
+    const GradPlan p = grad_plan(d, g->nt, S);
+    return (grad_work_per_shot(d, p, ctx->two_step) + rest) * S + (size_t)d.field * 8 +
+           (size_t)img * 4 * (5 + hist_parts(g->nt, p.K, img));
+  }, nullptr);
   tp->pl = grad_plan(d, g->nt, Sh);
   const GradPlan &pl = tp->pl;
   const size_t per_shot = grad_work_per_shot(d, pl, ctx->two_step) + rest;

@@ -104,6 +104,10 @@ class Fake:
     def peak(self):
         return self.hip.fake_peak()
 
+    @property
+    def allocations(self):
+        return self.hip.fake_allocations()
+
     def footprint(self, p, nrec, nh, op):
         n = ctypes.c_size_t()
         assert self.lib.fwime_footprint(p[0], p[3].nshots, nrec, nh, op, ctypes.byref(n)) == 0
@@ -117,6 +121,7 @@ def _load(fake_so):
     hip = ctypes.CDLL(fake_so, mode=ctypes.RTLD_GLOBAL)
     for f in ("fake_used", "fake_peak"):
         getattr(hip, f).restype = ctypes.c_size_t
+    hip.fake_allocations.restype = ctypes.c_long
     hip.fake_device.argtypes = [ctypes.c_size_t, ctypes.c_size_t]
     hip.fake_largest.argtypes = [ctypes.c_size_t]
     hip.fake_launched.argtypes, hip.fake_launched.restype = [ctypes.c_char_p], ctypes.c_long

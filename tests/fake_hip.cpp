@@ -22,6 +22,7 @@ std::map<std::string, long> launched;
 struct Call { Dim3 grid, block; size_t shmem; void *stream; };
 std::vector<Call> calls;
 int last = 0;
+long allocations = 0;
 
 int fail(int e) { return last = e; }
 
@@ -31,6 +32,7 @@ int allocate(void **p, size_t n) {
   if (n > largest_ok || used + other + n > total) return fail(kOutOfMemory);
   *p = reinterpret_cast<void *>(next_address);
   live[next_address] = n;
+  ++allocations;
   next_address += (n + 4095) / 4096 * 4096 + 4096;
   used += n;
   if (used > peak) peak = used;
@@ -54,7 +56,8 @@ void fake_device(size_t bytes, size_t held_by_others) { total = bytes; other = h
 void fake_largest(size_t bytes) { largest_ok = bytes; }
 size_t fake_used() { return used; }
 size_t fake_peak() { return peak; }
-void fake_reset_peak() { peak = used; }
+void fake_reset() { peak = used; }
+long fake_allocations() { return allocations; }
 long fake_launched(const char *part) {
   long n = 0;
   for (auto &l : launched)

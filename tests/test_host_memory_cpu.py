@@ -91,3 +91,68 @@ assert f.lib.fwime_ctx_trim(f.h, None) == 0
 print(rc, f.backward(t))
 """
     assert fake(code) == ["0"] * 8
+
+
+def test_histories_stay_within_a_third_of_the_device(fake):
+    """Arena, solver buffer, live tapes and the memory kept of freed ones together, whatever the order of the calls."""
+    code = """
+import itertools
+for other in (0, 188 * GiB):
+    for order in itertools.permutations(("gradient", "tape", "vp", "born_adj")):
+        f = Fake(other=other)
+        large = f.problem(300, 1700, 1400 if other == 0 else 500, 8, 60)
+        small = f.problem(100, 200, 300, 1, 40)
+        for op in order * 2:
+            if op == "tape":
+                rc, t = f.forward(large, 11)
+                rc2, t2 = f.forward(small, 11)
+                assert (rc, rc2, f.backward(t), f.backward(t2)) == (0, 0, 0, 0)
+                f.free(t2)
+                f.free(t)
+            else:
+                assert getattr(f, op)(large, 11) == 0
+            assert f.used <= (288 * GiB - other) // 3 + GiB // 4, (order, op, f.used / GiB)
+        assert f.peak > (288 * GiB - other) // 5       # histories were kept
+        f.close()
+        f.hip.fake_reset()
+"""
+    assert fake(code) == []
+
+
+def test_small_histories_are_not_reallocated(fake):
+    """Calls whose histories fit side by side keep their buffers: no allocation after the first round."""
+    code = """
+f = Fake()
+p = f.problem(200, 600, 400, 2)
+for i in range(3):
+    before = f.allocations
+    assert (f.gradient(p, 11), f.vp(p, 11), f.born_adj(p, 11)) == (0, 0, 0)
+    rc, t = f.forward(p, 11)
+    assert (rc, f.backward(t)) == (0, 0)
+    f.free(t)
+print(f.allocations - before)
+"""
+    assert fake(code) == ["0"]
+
+
+def test_live_tapes_share_the_third(fake):
+    """Tapes held at a time: whole histories take a third of the device at most, the rest holds checkpointed tapes."""
+    code = """
+counts = []
+for budget in (0, 8 * GiB):
+    f = Fake(size=8 * GiB, budget=budget)
+    p = f.problem(100, 200, 1500, 1)
+    tapes = []
+    while True:
+        rc, t = f.forward(p, 11)
+        if rc:
+            break
+        tapes.append(t)
+    counts.append(len(tapes))
+    for t in tapes:
+        f.free(t)
+    f.close()
+print(int(counts[0] >= 0.6 * counts[1] > 50), counts, file=__import__("sys").stderr)
+print(int(counts[0] >= 0.6 * counts[1] > 50))
+"""
+    assert fake(code) == ["1"]
