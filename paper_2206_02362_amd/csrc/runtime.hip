@@ -3316,7 +3316,7 @@ int fwime_engine_create(fwime_ctx_t *ctx, int32_t steps_per_round, int32_t max_j
   const size_t bytes = sizeof(BatchJob2) * (size_t)max_jobs;
   for (int i = 0; i < kEngineRing; ++i) {
     if (hipHostMalloc((void **)&e->host_desc[i], bytes, hipHostMallocDefault) != hipSuccess ||
-        hipMalloc((void **)&e->dev_desc[i], bytes) != hipSuccess ||
+        device_alloc(ctx, (void **)&e->dev_desc[i], bytes) != hipSuccess ||
         hipEventCreateWithFlags(&e->ring_ev[i], hipEventDisableTiming) != hipSuccess) {
       (void)hipGetLastError();
       fwime_engine_destroy(e);
@@ -3375,7 +3375,13 @@ int fwime_engine_submit(fwime_engine_t *e, const fwime_job_t *job, void *check_s
     delete j;
     return set_err(ctx, FWIME_ENOMEM, "the job exceeds the HBM budget");
   }
-  if (hipMallocAsync(&j->mem, cv.total, e->st) != hipSuccess) {
+  hipError_t alloc = hipMallocAsync(&j->mem, cv.total, e->st);
+  if (alloc != hipSuccess) {               // as device_alloc
+    (void)hipGetLastError();
+    release_idle(ctx, nullptr);
+    alloc = hipMallocAsync(&j->mem, cv.total, e->st);
+  }
+  if (alloc != hipSuccess) {
     (void)hipGetLastError();
     delete j;
     return set_err(ctx, FWIME_ENOMEM, "hipMallocAsync of " + std::to_string(cv.total) + " bytes failed");

@@ -156,3 +156,28 @@ print(int(counts[0] >= 0.6 * counts[1] > 50), counts, file=__import__("sys").std
 print(int(counts[0] >= 0.6 * counts[1] > 50))
 """
     assert fake(code) == ["1"]
+
+
+def test_engine_takes_the_memory_kept_of_a_freed_tape(fake):
+    """Descriptors and jobs of the engine are allocated although only memory that the context holds idle is left."""
+    code = """
+f = Fake(size=16 * GiB)
+p, q = f.problem(100, 200, 1500, 2), f.problem(100, 200, 50, 1)
+for part in ("descriptors", "job"):
+    rc, t = f.forward(p, 11)
+    assert (rc, f.backward(t)) == (0, 0)
+    f.free(t)
+    if part == "job":
+        assert f.submit(e, q) == 0                 # one in flight: the pool is warm
+        rc, t = f.forward(p, 11)
+        f.free(t)
+    assert f.used > GiB
+    f.hip.fake_device(16 * GiB, 16 * GiB - f.used - 1000)   # 1000 bytes are free
+    if part == "descriptors":
+        rc, e = f.engine(8)
+        print(rc)
+        f.hip.fake_device(16 * GiB, 0)
+    else:
+        print(f.submit(e, q))
+"""
+    assert fake(code) == ["0", "0"]
