@@ -53,8 +53,8 @@ struct fwime_ctx {
   // One buffer at most, none under a budget; counted as free memory, and given
   // back when one of the context's allocations fails or a history needs the
   // room, by fwime_ctx_trim and with the context.
-  // Tapes are freed on any thread, so tape_mu guards these three.
-  std::mutex tape_mu;
+  // Tapes are freed on any thread: tape_mu guards tape_bytes, spare and spare_bytes.
+  mutable std::mutex tape_mu;
   void *spare = nullptr;
   size_t spare_bytes = 0;
   size_t last_arena_request = 0;
@@ -209,7 +209,7 @@ size_t spare_bytes(fwime_ctx_t *ctx) {
   return ctx->spare_bytes;
 }
 
-size_t live_tape_bytes(fwime_ctx_t *ctx) {
+size_t live_tape_bytes(const fwime_ctx_t *ctx) {
   std::lock_guard<std::mutex> lock(ctx->tape_mu);
   return ctx->tape_bytes;
 }
@@ -1250,7 +1250,7 @@ int fwime_ctx_trim(fwime_ctx_t *ctx, void *stream) {
 int fwime_ctx_info(const fwime_ctx_t *ctx, fwime_info_t *out) {
   if (!ctx || !out) return FWIME_EINVAL;
   out->arena_bytes = ctx->arena_bytes;
-  out->tape_bytes = ctx->tape_bytes;
+  out->tape_bytes = live_tape_bytes(ctx);
   out->tile_x = ctx->tile_x;
   out->last_batch_tile_x = ctx->last_batch_tile;
   out->tuned_signatures = (int32_t)ctx->tuned.size();
@@ -2684,7 +2684,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   tc.add(&tp->dck, pl.hist ? pl.seg_stride * geo->nshots : pl.ck_stride * geo->nshots);
   const bool less = d.T == 4 || Sh > 0;
   auto again = [&] { return fwime_forward_tape(ctx, g, vel, geo, nh, ptilde, data, tape_out, stream); };
-  if (ctx->budget && ctx->tape_bytes + tc.total + ctx->arena_bytes > ctx->budget) {
+  if (ctx->budget && live_tape_bytes(ctx) + tc.total + ctx->arena_bytes > ctx->budget) {
     delete tp;
     return or_frugally(ctx, set_err(ctx, FWIME_ENOMEM, "tape does not fit the HBM budget"), less, again);
   }
