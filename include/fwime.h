@@ -300,12 +300,17 @@ typedef struct {
  * by one to four time steps).  Without timing, last_stencil_launches is -1. */
 int fwime_ctx_info(const fwime_ctx_t *ctx, fwime_info_t *out);
 
+/* *bytes: all device memory that the context holds at the moment (scratch
+ * arena, the variable-projection solver's buffer, live tapes and the memory kept
+ * of a freed one). */
+int fwime_ctx_held(const fwime_ctx_t *ctx, size_t *bytes);
+
 /* Turn the event timing above on (on != 0) or off.  It adds two event
  * records per modeling call and nothing to the kernels. */
 int fwime_ctx_set_timing(fwime_ctx_t *ctx, int32_t on);
 
-/* Release the context's scratch arena, and the memory that it keeps of a
- * freed tape for the next one, after `stream` (its stream) is idle.
+/* Release the context's scratch arena, the solver's buffer and the memory
+ * kept of a freed tape for the next one, after `stream` (its stream) is idle.
  * The next call allocates again.  For schedulers that share one HBM budget
  * among several contexts. */
 int fwime_ctx_trim(fwime_ctx_t *ctx, void *stream);

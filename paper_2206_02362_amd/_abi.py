@@ -24,7 +24,7 @@ FWIME_ENONFINITE = 4
 
 FWIME_OP_MODEL, FWIME_OP_BORN_FWD, FWIME_OP_BORN_ADJ, FWIME_OP_GRADIENT = 0, 1, 2, 3
 
-EXPORTED = ("fwime_ctx_create", "fwime_ctx_destroy", "fwime_ctx_info", "fwime_ctx_set_timing", "fwime_ctx_trim",
+EXPORTED = ("fwime_ctx_create", "fwime_ctx_destroy", "fwime_ctx_info", "fwime_ctx_held", "fwime_ctx_set_timing", "fwime_ctx_trim",
             "fwime_footprint",
             "fwime_model", "fwime_model_static", "fwime_born_ext_fwd",
             "fwime_born_ext_adj", "fwime_born_ext_tau_fwd", "fwime_born_ext_tau_adj", "fwime_gradient", "fwime_gradient_tau", "fwime_vp_solve", "fwime_vp_solve_tau", "fwime_spline_apply", "fwime_spline_adjoint", "fwime_spline_refine", "fwime_lbfgs_direction", "fwime_lbfgs_minimize", "fwime_model_batch", "fwime_engine_create", "fwime_engine_submit", "fwime_engine_run", "fwime_engine_poll",
@@ -136,6 +136,8 @@ def load() -> ctypes.CDLL:
     lib.fwime_engine_destroy.restype = None
     lib.fwime_ctx_info.argtypes = [P, P]
     lib.fwime_ctx_info.restype = I
+    lib.fwime_ctx_held.argtypes = [P, ctypes.POINTER(ctypes.c_size_t)]
+    lib.fwime_ctx_held.restype = I
     lib.fwime_ctx_set_timing.argtypes = [P, ctypes.c_int32]
     lib.fwime_ctx_set_timing.restype = I
     lib.fwime_ctx_trim.argtypes = [P, P]
@@ -369,6 +371,12 @@ class Context:
         out = _Info()
         self._check(self._lib.fwime_ctx_info(self._h, ctypes.byref(out)))
         return {k: getattr(out, k) for k, _ in _Info._fields_}
+
+    def held_bytes(self) -> int:
+        """Device memory that the context holds: arena, solver buffer, live tapes and the memory kept of a freed one."""
+        out = ctypes.c_size_t()
+        self._check(self._lib.fwime_ctx_held(self._h, ctypes.byref(out)))
+        return int(out.value)
 
     def model_batch(self, jobs):
         """jobs: sequence of (Grid, vel, Geometry); returns one data tensor per job."""

@@ -1266,6 +1266,13 @@ int fwime_ctx_info(const fwime_ctx_t *ctx, fwime_info_t *out) {
   return FWIME_OK;
 }
 
+int fwime_ctx_held(const fwime_ctx_t *ctx, size_t *bytes) {
+  if (!ctx || !bytes) return FWIME_EINVAL;
+  std::lock_guard<std::mutex> lock(ctx->tape_mu);
+  *bytes = ctx->arena_bytes + ctx->vp_bytes + ctx->tape_bytes + ctx->spare_bytes;
+  return FWIME_OK;
+}
+
 int fwime_ctx_set_timing(fwime_ctx_t *ctx, int32_t on) {
   if (!ctx) return FWIME_EINVAL;
   if (hipSetDevice(ctx->device) != hipSuccess) return FWIME_EHIP;

@@ -90,6 +90,11 @@ class Fake:
         assert self.lib.fwime_ctx_info(self.h, ctypes.byref(out)) == 0
         return out
 
+    def held(self):
+        n = ctypes.c_size_t()
+        assert self.lib.fwime_ctx_held(self.h, ctypes.byref(n)) == 0
+        return n.value
+
     def error(self):
         return self.lib.fwime_last_error(self.h).decode()
 

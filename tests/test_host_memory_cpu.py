@@ -181,3 +181,34 @@ for part in ("descriptors", "job"):
         print(f.submit(e, q))
 """
     assert fake(code) == ["0", "0"]
+
+
+def test_held_bytes_and_trim_cover_every_buffer(fake):
+    """What the context reports is what it has allocated, a live tape's unused rest aside; trim gives all of it back, the
+    memory kept of a freed tape included, and destroying a context leaves nothing."""
+    code = """
+f = Fake()
+assert f.held() == f.used == 0
+p, q = f.problem(200, 600, 400, 2), f.problem(100, 200, 400, 1)
+for call in (f.model, f.gradient, f.vp, f.born_adj):
+    assert call(*((p,) if call == f.model else (p, 11))) == 0 and f.held() == f.used
+rc, t = f.forward(p, 11)
+assert rc == 0 and f.held() == f.used
+f.free(t)
+kept = f.used - f.info().arena_bytes
+assert f.held() == f.used and kept > GiB              # solver buffer and the freed tape's memory
+arena = f.info().arena_bytes
+rc, t = f.forward(q, 11)                                # a small tape leaves the kept memory alone
+assert rc == 0 and f.held() == f.used
+f.trim()
+assert f.info().arena_bytes == 0 and f.held() == f.used == f.info().tape_bytes
+f.free(t)
+assert f.held() == f.used > 0
+f.trim()
+assert f.held() == f.used == 0
+rc, t = f.forward(p, 11)
+f.free(t)
+f.close()
+print(f.used)
+"""
+    assert fake(code) == ["0"]
