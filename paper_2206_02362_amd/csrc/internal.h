@@ -91,6 +91,43 @@ __host__ __device__ inline void tile_coords(int logical, int ntz, int ntx, int S
   txi = xg * kTileGroupX + txl;
 }
 
+// Extended-precision arithmetic of the stencil kernels (field = FP32 hi + BF16
+// lo), with contraction off and its fused multiply-adds spelled out: the bits
+// depend neither on the kernel nor on how the compiler groups a kernel's
+// columns, so a shot has the same bits alone (four steps per launch) and in a
+// set (two).
+//
+// Laplacian of the low part: a rounding residual (below 2^-24 of the field)
+// that needs only a few correct digits, so it is summed directly,
+// sum_k w_k (l(-k) + l(k)) + w_0 l with w_0 = -2 sum_k w_k, instead of in
+// difference form.  l: the cell in a tile of columns of ROWS cells, lc its value.
+template <int ROWS>
+__device__ __forceinline__ float df_low_laplacian(const unsigned short *l, float lc, float w0, const float *cz,
+                                                  const float *cx) {
+#pragma clang fp contract(off)
+  float lap = fmaf(w0, lc, cz[0] * (bf16_f32(l[-1]) + bf16_f32(l[1])));
+#pragma unroll
+  for (int k = 1; k <= kR; ++k) {
+    if (k > 1) lap = fmaf(cz[k - 1], bf16_f32(l[-k]) + bf16_f32(l[k]), lap);
+    lap = fmaf(cx[k - 1], bf16_f32(l[-k * ROWS]) + bf16_f32(l[k * ROWS]), lap);
+  }
+  return lap;
+}
+
+// u = g (2 (c + cl) - g (p + pl) + r), r = V (L u + src), in FP64, split into
+// FP32 hi (returned) and BF16 lo; r rounded to FP32
+__device__ __forceinline__ float df_update(float g, float c, float cl, float p, float pl, float V, double lap, float src,
+                                           unsigned short &lo, float &r) {
+#pragma clang fp contract(off)
+  const double gd = g, vd = V, qd = lap + (double)src;
+  const double t = fma((double)c + (double)cl, 2.0, -(gd * ((double)p + (double)pl)));
+  const double ex = fma(qd, vd, t);
+  const float hi = (float)(ex * gd);
+  lo = f32_bf16((float)fma(ex, gd, -(double)hi));
+  r = (float)(vd * qd);
+  return hi;
+}
+
 // Orders a wavefront's LDS accesses where its lanes exchange values without a
 // workgroup barrier.  The hardware runs them in program order, so nothing is
 // emitted; but the compiler reads the program as one lane's, and may hand a

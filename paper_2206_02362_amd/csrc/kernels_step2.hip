@@ -56,16 +56,6 @@ struct Step2Tile<TX, true> : Step2Tile<TX, false> {
   unsigned short l1[Step2Tile<TX, false>::C1][Step2Tile<TX, false>::ROWS];
 };
 
-// u = g (2 (c + cl) - g (p + pl) + r) in FP64, split into FP32 hi and BF16 lo
-__device__ __forceinline__ float df_update(float g, float c, float cl, float pv, float pl, double r,
-                                           unsigned short &lo) {
-  const double gd = g;
-  const double ex = gd * (2.0 * ((double)c + (double)cl) - gd * ((double)pv + (double)pl) + r);
-  const float hi = (float)ex;
-  lo = f32_bf16((float)(ex - (double)hi));
-  return hi;
-}
-
 // A wavefront's point sources (injection list entries of its columns).  The
 // chain list range -> entries -> samples misses the L2, which every launch
 // starts cold, at each link: formed where the samples are added, it took a
@@ -362,10 +352,7 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
   const int lz = lane + kR;                  // LDS row of this lane's row
   // the tile's rows z0-4 .. z0+59 reach the four rows above a free surface
   [[maybe_unused]] const bool fs_near = FS && a.fs >= 0 && z0 - kR <= a.fs - 1 && z0 + kTZ2 + kR - 1 >= a.fs - kR;
-  // The low part of the extended-precision field is a rounding residual
-  // (below 2^-24 of the field): its Laplacian needs only a few correct
-  // digits, so it is summed directly, sum_k w_k (l(-k) + l(k)) + w_0 l, with
-  // w_0 = -2 sum_k w_k, instead of in difference form.
+  // weight w_0 of the low part's Laplacian
   [[maybe_unused]] float c0l = 0.f;
   if constexpr (DF) {
 #pragma unroll
@@ -416,24 +403,17 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
       if constexpr (DF) {
         const unsigned short *cll = basel + j * ROWS;
         cl = bf16_f32(cll[0]);
-        float lapl = c0l * cl;
-#pragma unroll
-        for (int k = 1; k <= kR; ++k) {
-          lapl += a.cz[k - 1] * (bf16_f32(cll[-k]) + bf16_f32(cll[k]));
-          lapl += a.cx[k - 1] * (bf16_f32(cll[-k * ROWS]) + bf16_f32(cll[k * ROWS]));
-        }
-        lapd += (double)lapl;
+        lapd += (double)df_low_laplacian<ROWS>(cll, cl, c0l, a.cz, a.cx);
       }
       const int x = xs1 + j;
       const bool xin = x >= 0 && x < NX;     // wave-uniform
       // computed for every lane; cells outside the grid are set to zero
       const float g = gzv * gx1[j];
-      [[maybe_unused]] double r64 = 0.0;
-      if constexpr (DF) r64 = (double)vv1[j] * (lapd + (double)ds1[j]);
-      const float r = DF ? (float)r64 : vv1[j] * (lap + ds1[j]);
+      float r = 0.f;
+      if constexpr (!DF) r = vv1[j] * (lap + ds1[j]);
       unsigned short u1l = 0;
       float u1;
-      if constexpr (DF) u1 = df_update(g, c, cl, pv[j], pl[j], r64, u1l);
+      if constexpr (DF) u1 = df_update(g, c, cl, pv[j], pl[j], vv1[j], lapd, ds1[j], u1l, r);
       else u1 = g * (2.f * c - g * pv[j] + r);
       if (!(xin && zin)) {
         u1 = 0.f;
@@ -542,24 +522,17 @@ __device__ __forceinline__ void step2_body(const Step2Args &p, int logical,
       if constexpr (DF) {
         const unsigned short *cll = basel + j * ROWS;
         cl = bf16_f32(cll[0]);
-        float lapl = c0l * cl;
-#pragma unroll
-        for (int k = 1; k <= kR; ++k) {
-          lapl += a.cz[k - 1] * (bf16_f32(cll[-k]) + bf16_f32(cll[k]));
-          lapl += a.cx[k - 1] * (bf16_f32(cll[-k * ROWS]) + bf16_f32(cll[k * ROWS]));
-        }
-        lapd += (double)lapl;
+        lapd += (double)df_low_laplacian<ROWS>(cll, cl, c0l, a.cz, a.cx);
       }
       const int x = xs2 + j;
       const bool xin = x < NX;               // wave-uniform
       const float g = gzv * gx2[j];
       const float un = base0[j * ROWS];
-      [[maybe_unused]] double r64 = 0.0;
-      if constexpr (DF) r64 = (double)vv2[j] * (lapd + (double)ds2[j]);
-      const float r = DF ? (float)r64 : vv2[j] * (lap + ds2[j]);
+      float r = 0.f;
+      if constexpr (!DF) r = vv2[j] * (lap + ds2[j]);
       unsigned short u2l = 0;
       float u2;
-      if constexpr (DF) u2 = df_update(g, c, cl, un, bf16_f32(basel0[j * ROWS]), r64, u2l);
+      if constexpr (DF) u2 = df_update(g, c, cl, un, bf16_f32(basel0[j * ROWS]), vv2[j], lapd, ds2[j], u2l, r);
       else u2 = g * (2.f * c - g * un + r);
       [[maybe_unused]] float rs = r;
       if constexpr (FS) {

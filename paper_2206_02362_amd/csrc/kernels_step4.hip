@@ -1,8 +1,7 @@
 // Up to four leapfrog time steps per launch, for grids too small to fill the
 // device.  Same recursion and the same operations per cell as the one- and
-// two-step kernels: the same bits in FP32; in extended precision the same to
-// the rounding of the FP64 update, whose fused form the compiler picks column
-// by column in the two-step kernel.
+// two-step kernels, and the same bits (in extended precision through the shared
+// df_update and df_low_laplacian).
 //
 // What bounds these grids is not work but the launch: a 100 x 200 model with
 // one shot is 36 two-step workgroups, and a two-step launch took 7.5 us
@@ -299,13 +298,7 @@ __global__ void __launch_bounds__(64 * kWaves4) k_step4(const Step4Args a) {
       if constexpr (DF) {
         const unsigned short *cll = basel + j * ROWS;
         clo = bf16_f32(cll[0]);
-        float lapl = fmaf(c0l, clo, a.cz[0] * (bf16_f32(cll[-1]) + bf16_f32(cll[1])));
-#pragma unroll
-        for (int k = 1; k <= kR; ++k) {
-          if (k > 1) lapl = fmaf(a.cz[k - 1], bf16_f32(cll[-k]) + bf16_f32(cll[k]), lapl);
-          lapl = fmaf(a.cx[k - 1], bf16_f32(cll[-k * ROWS]) + bf16_f32(cll[k * ROWS]), lapl);
-        }
-        lapd += (double)lapl;
+        lapd += (double)df_low_laplacian<ROWS>(cll, clo, c0l, a.cz, a.cx);
       }
       const int x = xs + j;
       const bool xin = x >= 0 && x < NX;                     // wave-uniform
@@ -313,13 +306,7 @@ __global__ void __launch_bounds__(64 * kWaves4) k_step4(const Step4Args a) {
       float r, un;
       [[maybe_unused]] unsigned short ul = 0;
       if constexpr (DF) {
-        // in FP64, split into FP32 hi and BF16 lo
-        const double gd = g[j], vd = vv[j], qd = lapd + (double)src[j];
-        const double t = fma((double)c + (double)clo, 2.0, -(gd * ((double)pv[j] + (double)bf16_f32(pl[j]))));
-        const double ex = fma(qd, vd, t);
-        un = (float)(ex * gd);
-        ul = f32_bf16((float)fma(ex, gd, -(double)un));
-        r = (float)(vd * qd);
+        un = df_update(g[j], c, clo, pv[j], bf16_f32(pl[j]), vv[j], lapd, src[j], ul, r);
       } else {
         const float q = lap + src[j];
         un = g[j] * fmaf(q, vv[j], fmaf(c, 2.f, -(g[j] * pv[j])));
