@@ -365,7 +365,8 @@ void fwime_tape_free(fwime_tape_t *tape);
  * [0, (nz-1) dz] and [0, (nx-1) dx] (to 1e-9 of the node span); read during
  * the call only.  mc: DEVICE [nxn][nzn]; out: DEVICE [nx][nz], z fastest.
  * With at most 384 nodes in all and nz <= 2048 the call is one launch (the
- * adjoint where, too, no x cell is wider than 256 dx).  Otherwise it
+ * adjoint where, too, a node's cells hold few enough grid points: about 500
+ * times 256 values in the cells of a node column).  Otherwise it
  * synchronizes `stream` twice (before taking the context's arena and after the
  * node upload), and the interpolation tables (about 12 bytes per fine point
  * and node) live in the context's arena.

@@ -3572,16 +3572,30 @@ int check_spline(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, double dx,
   return FWIME_OK;
 }
 
+// Most fine points (of n, at multiples of h) in the two cells of any node.
+double spline_span(const double *nodes, int32_t nn, int32_t n, double h) {
+  double span = 0.0;
+  for (int j = 0; j < nn; ++j)
+    span = std::max(span, nodes[std::min(j + 1, nn - 1)] - nodes[std::max(j - 1, 0)]);
+  return std::min((double)n, std::floor(span / h) + 1.0);
+}
+
 // Whether S and S* run as one launch: few enough nodes and rows for it, and
-// for S* cells of at most 256 points, since one workgroup gathers the columns
-// of a node's two cells (two nodes on 1700 columns would leave the device
-// idle; the two-pass gather spreads them).
-bool spline_one_launch(int32_t nz, int32_t nx, int32_t nzn, int32_t nxn, const double *xn, double dx, bool adjoint,
-                       SplineNodes &s, const double *zn) {
+// for S* few enough fine points to a workgroup, which gathers the two cells of
+// its node column: kSplineSerial values read by a thread one after the other.
+// Measured, us, two passes against one launch, by that number: 60 (300 x 1700,
+// 31 x 171 nodes) 53.5 / 13.8; 320 (31 x 28) 77 / 43; 384 (2000 x 2500, 33 x 251)
+// 105 / 62; 640 (500 x 2500, 9 x 41) 83 / 79; 1080 (300 x 1700, 11 x 10) 123 / 122;
+// 1200 (2000 x 2500, 11 x 85) 116 / 155; 2176 (33 x 41) 134 / 300; the largest
+// (9 x 11) 209 / 1420.
+constexpr double kSplineSerial = 512;
+bool spline_one_launch(int32_t nz, int32_t nx, double dz, double dx, int32_t nzn, const double *zn, int32_t nxn,
+                       const double *xn, bool adjoint, SplineNodes &s) {
   if ((long)nzn + nxn > kSplineNodes || nz > kSplineRows) return false;
-  if (adjoint)
-    for (int j = 1; j < nxn; ++j)
-      if (xn[j] - xn[j - 1] > 256 * dx) return false;
+  if (adjoint) {
+    const double rounds = std::ceil(spline_span(xn, nxn, nx, dx) * nzn / 256);   // of 256 threads
+    if (rounds * spline_span(zn, nzn, nz, dz) > kSplineSerial) return false;
+  }
   s.nzn = nzn;
   s.nxn = nxn;
   std::copy(zn, zn + nzn, s.n);
@@ -3627,7 +3641,7 @@ int fwime_spline_apply(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, doub
   int rc = check_spline(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, mc, out);
   if (rc) return rc;
   SplineNodes nodes;
-  if (spline_one_launch(nz, nx, nzn, nxn, xn, dx, false, nodes, zn)) {
+  if (spline_one_launch(nz, nx, dz, dx, nzn, zn, nxn, xn, false, nodes)) {
     HIPCHK(launch_spline_apply1(nodes, nz, nx, dz, dx, mc, out, st));
     return FWIME_OK;
   }
@@ -3646,7 +3660,7 @@ int fwime_spline_adjoint(fwime_ctx_t *ctx, int32_t nz, int32_t nx, double dz, do
   int rc = check_spline(ctx, nz, nx, dz, dx, nzn, zn, nxn, xn, f, mc_out);
   if (rc) return rc;
   SplineNodes nodes;
-  if (spline_one_launch(nz, nx, nzn, nxn, xn, dx, true, nodes, zn)) {
+  if (spline_one_launch(nz, nx, dz, dx, nzn, zn, nxn, xn, true, nodes)) {
     HIPCHK(launch_spline_adjoint1(nodes, nz, nx, dz, dx, f, mc_out, st));
     return FWIME_OK;
   }
