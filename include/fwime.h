@@ -409,9 +409,10 @@ int fwime_spline_refine(fwime_ctx_t *ctx, int32_t nzn, const double *zn, int32_t
  * overlap s or y).  0 <= npairs <= 256, n >= 1.  Every pair must have
  * s_i.y_i > 0 (callers drop the others); otherwise FWIME_EINVAL before
  * anything is written.  The call synchronizes `stream` once for up to 15
- * pairs (their inner products are formed together, and the direction is one
- * FP64 linear combination rounded once); with more, once before it starts and
- * once per inner product (3 npairs + 1 of them). */
+ * pairs of at most 6e6 elements (one pair: 3e6): their inner products are formed
+ * together, and the direction is one FP64 linear combination rounded once.
+ * Otherwise it does so once before it starts and once per inner product
+ * (3 npairs + 1 of them). */
 int fwime_lbfgs_direction(fwime_ctx_t *ctx, int64_t n, int32_t npairs, const float *s, const float *y,
                           const float *g, float *d_out, void *stream);
 
@@ -437,8 +438,8 @@ typedef int (*fwime_objective_fn)(void *user, const float *x, float *g, double *
  * last value repeated past the stop; iters: HOST, iterations taken.
  * 1 <= memory <= 256.  A callback error stops with FWIME_EINVAL and a
  * non-finite objective with FWIME_ENONFINITE; x then holds the last accepted
- * iterate.  The call synchronizes `stream` once per inner product, and once
- * per direction of up to 15 pairs. */
+ * iterate.  The call synchronizes `stream` once per inner product, those of a
+ * direction counting as in fwime_lbfgs_direction. */
 int fwime_lbfgs_minimize(fwime_ctx_t *ctx, int64_t n, int32_t memory, int32_t maxiter, double gtol,
                          fwime_objective_fn fg, void *user, float *x, float *work, int64_t work_floats,
                          double *f_hist, int32_t *iters, void *stream);

@@ -3738,6 +3738,18 @@ namespace {
 constexpr int kLbfgsMaxEvals = 100;      // trial steps per line search
 constexpr long kLbfgsWorkHead = 4096;    // floats of the workspace before the vectors (dot partials)
 
+// Whether k pairs of n elements go by inner products (gram_direction) rather
+// than by the recursion on the vectors (two_loop).  Inner products save its
+// 3 k + 1 round trips of about 20 us, but read the vectors from few workgroups
+// (their partial sums go to the host) and their number grows with k squared.
+// Measured, us, recursion against inner products: n = 1e6, k = 1 106 / 65, 5 356 /
+// 116, 15 992 / 269; n = 3e6, k = 1 119 / 119; n = 4e6, k = 1 130 / 148, 2 213 / 152;
+// n = 5e6, k = 5 510 / 452, 15 1592 / 1433; n = 3.1e7, k = 5 1936 / 2773, 15 5460 /
+// 8750: the lines cross at 3e6 for one pair and between 6e6 and 1.1e7 for more.
+bool by_inner_products(long k, long n) {
+  return k <= kLbfgsGramPairs && n <= (k == 0 ? LONG_MAX : k == 1 ? 3000000L : 6000000L);
+}
+
 // d = -H g from the inner products of the pairs (oldest first) and g, at most
 // kLbfgsGramPairs of them: the same recursion as two_loop below, on numbers.
 // With q = g - sum_j alpha_j y_j and r = gamma q + sum_j (alpha_j - beta_j) s_j
@@ -3795,8 +3807,7 @@ int gram_direction(fwime_ctx_t *ctx, long n, const std::vector<const float *> &S
 
 // d = -H g by the two-loop recursion over the pairs S[i], Y[i] (oldest first),
 // H_0 = (s.y / y.y of the newest pair) I; FP64 inner products, FP32 updates.
-// Every pair's curvature is checked before d is written.  (For more pairs
-// than gram_direction takes: its inner products grow with their square.)
+// Every pair's curvature is checked before d is written.
 int two_loop(fwime_ctx_t *ctx, long n, const std::vector<const float *> &S, const std::vector<const float *> &Y,
              const float *g, float *d, double *part, double *res, hipStream_t st) {
   const int k = (int)S.size();
@@ -3857,7 +3868,7 @@ int fwime_lbfgs_direction(fwime_ctx_t *ctx, int64_t n, int32_t npairs, const flo
     S[i] = s + (long)i * n;
     Y[i] = y + (long)i * n;
   }
-  if (npairs <= kLbfgsGramPairs) return gram_direction(ctx, (long)n, S, Y, g, d_out, st);
+  if (by_inner_products(npairs, (long)n)) return gram_direction(ctx, (long)n, S, Y, g, d_out, st);
   HIPCHK(hipStreamSynchronize(st));      // earlier work on the stream may still use the arena
   double *part = nullptr, *res = nullptr;
   Carve cv;
@@ -3924,7 +3935,7 @@ int fwime_lbfgs_minimize(fwime_ctx_t *ctx, int64_t n, int32_t memory, int32_t ma
       Y.push_back(yslot[j]);
     }
     // descent direction -H g
-    if ((rc = (int)S.size() <= kLbfgsGramPairs ? gram_direction(ctx, (long)n, S, Y, g, d, st)
+    if ((rc = by_inner_products((long)S.size(), (long)n) ? gram_direction(ctx, (long)n, S, Y, g, d, st)
                                                : two_loop(ctx, (long)n, S, Y, g, d, part, res, st)))
       return rc;
     double dphi0;

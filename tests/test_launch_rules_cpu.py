@@ -23,3 +23,15 @@ assert f.spline(2000, 2500, np.append(nodes(500, 10), 20000.0), nodes(2500, 64),
 print(f.launched("k_spline_adjoint1") - before)
 """
     assert fake(code) == ["1"] * 5 + ["0"] * 7
+
+
+def test_lbfgs_direction_of_long_vectors_takes_the_recursion(fake):  # noqa: F811
+    code = """
+f = Fake()
+for n, k in ((5985, 1), (5985, 15), (3000000, 1), (6000000, 2), (6000000, 15), (3000001, 1), (6000001, 2), (31000000, 15),
+             (5985, 16)):
+    before = f.launched("k_lbfgs_gram")
+    assert f.lbfgs(n, k) == 0
+    print(f.launched("k_lbfgs_gram") - before)
+"""
+    assert fake(code) == ["1"] * 5 + ["0"] * 4
