@@ -1095,7 +1095,16 @@ int seg_len(int nt) {
 // least enough of them that a launch still fills the device.
 // ---------------------------------------------------------------------------
 constexpr long kHistSlots = 1024;       // time slots (shots x steps) of a segment
-constexpr long kHistMinTiles = 3072;    // two rounds of two-step workgroups (six per CU)
+// Two-step workgroups of a batch from which histories in several batches are
+// taken rather than checkpoints in one, which fill the device better.  Measured,
+// ms, gradient and Born adjoint, nt = 301: 300 x 1700, 12 shots, nh 61,
+// checkpointed 93.5 and 55.7; batches of 784 workgroups 109.7 and 87.5, of 1176
+// 89.9 and 68.4, of 1568 83.4 and 59.6, of 2352 72.4 and 49.4, all shots 64.0 and
+// 40.2; 16 shots, nh 11, 106.1 and 65.6, batches of 1568 94.3 and 67.0, of 3136
+// 79.8 and 52.4; 200 x 600, 24 shots, nh 41, 54.7 and 33.9, batches of 880 50.7
+// and 37.2, of 1320 44.6 and 31.9.  The adjoint crosses last, near 1900; batches
+// are evened out after the choice, to half of it at worst.
+constexpr long kHistMinTiles = 3072;
 
 // segment length for S shots: about kHistSlots slots in whole checkpointed
 // segments, or the record (made even)

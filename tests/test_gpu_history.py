@@ -144,3 +144,30 @@ def test_bits_do_not_depend_on_the_store(nz, nx, nb, nt, nshots, nh):
         ctx.close()
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+def test_histories_in_several_batches():
+    """Where not all shots' histories fit the third of the device, those of large batches do: two batches of 30 shots (1920
+    two-step workgroups) against one checkpointed batch, on a device with 14 GiB left."""
+    import torch
+    import paper_2206_02362_amd as fw
+    print("case: histories in two batches, 60x1000 nt40 60 shots", file=sys.stderr, flush=True)
+    nh, n = 5, 60
+    w = synth.tiny(nz=60, nx=1000, nb=8, nt=40, nshots=n, nh=nh, seed=9)
+    grid, tv, tg = gpu_problem(w)
+    pt = _dev(0.2 * synth.random_ptilde(nh, 60, 1000, 3))
+    data = _dev(np.random.default_rng(4).standard_normal((n, w.nrec, 40)))
+    gib, got = 1 << 30, []
+    for budget in (0, 6 * gib):
+        torch.cuda.empty_cache()
+        ctx = fw.Context(0, hbm_budget_bytes=budget)
+        hold = torch.empty(max(0, torch.cuda.mem_get_info()[0] - 14 * gib), dtype=torch.uint8, device="cuda:0")
+        got.append([*ctx.gradient(grid, tv, tg, pt, data, 1e-3, synth.dso_weights(nh)),
+                    ctx.born_ext_adj(grid, tv, tg, data, nh)])
+        got[-1].append(ctx.held_bytes() / gib)
+        ctx.close()
+        del hold
+    torch.cuda.empty_cache()
+    assert 4.2 < got[0][-1] < 4.8 and got[1][-1] < 3.0      # whole for all 60 shots: 4.85; checkpointed: 2.2
+    for a, b in zip(got[0][:-1], got[1][:-1]):
+        assert _close(_np(a), _np(b), 2e-6)
