@@ -349,7 +349,8 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *grid, const float *
 int fwime_backward_tape(fwime_ctx_t *ctx, fwime_tape_t *tape, const float *adjsrc,
                         float *grad_vel, float *grad_ptilde, void *stream);
 
-/* Release a tape (synchronizes the device); null is ignored.  A context
+/* Release a tape (synchronizes the device), also after its context was
+ * destroyed; null is ignored.  A context
  * without a budget keeps the memory of the largest tape freed, for the next
  * one, until another of its calls needs the room, fwime_ctx_trim or
  * fwime_ctx_destroy. */

@@ -53,8 +53,10 @@ struct fwime_ctx {
   // One buffer at most, none under a budget; counted as free memory, and given
   // back when one of the context's allocations fails or a history needs the
   // room, by fwime_ctx_trim and with the context.
-  // Tapes are freed on any thread: tape_mu guards tape_bytes, spare and spare_bytes.
+  // Tapes are freed on any thread, and after their context if need be: tape_mu
+  // guards tape_bytes, tapes, spare and spare_bytes.
   mutable std::mutex tape_mu;
+  std::vector<fwime_tape *> tapes;        // live ones
   void *spare = nullptr;
   size_t spare_bytes = 0;
   size_t last_arena_request = 0;
@@ -78,6 +80,8 @@ struct fwime_ctx {
   size_t fixed_bytes = 0;
   char *static_scratch = nullptr;         // device address of the static scratch array on `device`
 };
+
+static void detach_tapes(fwime_ctx_t *ctx);   // live tapes outlive the context
 
 static void release_graph(fwime_ctx_t *ctx) {
   if (ctx->graph_exec) (void)hipGraphExecDestroy(ctx->graph_exec);
@@ -1303,6 +1307,7 @@ void fwime_ctx_destroy(fwime_ctx_t *ctx) {
   if (ctx->arena) (void)hipFree(ctx->arena);
   if (ctx->vp) (void)hipFree(ctx->vp);
   release_spare(ctx);
+  detach_tapes(ctx);
   if (ctx->host_red) (void)hipHostFree(ctx->host_red);
   for (auto &e : ctx->tev)
     if (e) (void)hipEventDestroy(e);
@@ -2194,7 +2199,8 @@ void carve_work(Carve &cv, GradWork &wk, const Dims &d, const GradPlan &pl, int 
 // Tape: device-resident state between a forward and a backward call.
 // ---------------------------------------------------------------------------
 struct fwime_tape {
-  fwime_ctx_t *ctx = nullptr;
+  fwime_ctx_t *ctx = nullptr;             // null once the context is destroyed
+  int device = 0;
   fwime_grid_t g{};
   int nh = 0, nshots = 0, nrec = 0;
   Dims d{};
@@ -2208,6 +2214,12 @@ struct fwime_tape {
   int *tables = nullptr;
   bool used = false;
 };
+
+static void detach_tapes(fwime_ctx_t *ctx) {
+  std::lock_guard<std::mutex> lock(ctx->tape_mu);
+  for (fwime_tape_t *t : ctx->tapes) t->ctx = nullptr;
+  ctx->tapes.clear();
+}
 
 extern "C" {
 
@@ -2628,12 +2640,13 @@ int fwime_gradient_tau(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
 void fwime_tape_free(fwime_tape_t *tape) {
   if (!tape) return;
   if (tape->mem) {
-    (void)hipSetDevice(tape->ctx ? tape->ctx->device : 0);
+    (void)hipSetDevice(tape->device);
     (void)hipDeviceSynchronize();
     void *drop = tape->mem;
     if (fwime_ctx_t *ctx = tape->ctx) {
       std::lock_guard<std::mutex> lock(ctx->tape_mu);
       ctx->tape_bytes -= tape->bytes;
+      ctx->tapes.erase(std::find(ctx->tapes.begin(), ctx->tapes.end(), tape));
       if (!ctx->budget && tape->capacity > ctx->spare_bytes) {   // idle on every stream: kept
         drop = ctx->spare;
         ctx->spare = tape->mem;
@@ -2660,6 +2673,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
 
   fwime_tape_t *tp = new fwime_tape_t();
   tp->ctx = ctx;
+  tp->device = ctx->device;
   tp->g = *g;
   tp->nh = nh;
   tp->nshots = geo->nshots;
@@ -2728,6 +2742,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   {
     std::lock_guard<std::mutex> lock(ctx->tape_mu);
     ctx->tape_bytes += tc.total;
+    ctx->tapes.push_back(tp);
   }
   {
     char *p = (char *)tp->mem;

@@ -212,3 +212,24 @@ f.close()
 print(f.used)
 """
     assert fake(code) == ["0"]
+
+
+def test_tapes_outlive_their_context(fake):
+    """A tape freed after its context (a graph that a program still holds) gives its memory back."""
+    code = """
+f = Fake()
+p = f.problem(100, 200, 400, 1)
+tapes = [f.forward(p, 11) for _ in range(3)]
+assert all(rc == 0 for rc, _ in tapes)
+f.free(tapes[1][1])
+f.close()
+g = Fake()                                           # another context where the first one was
+for i in (2, 0):
+    f.free(tapes[i][1])
+assert g.held() == g.used == 0
+q = g.problem(100, 200, 400, 1)
+assert g.gradient(q, 11) == 0 and g.held() == g.used
+g.close()
+print(g.used)
+"""
+    assert fake(code) == ["0"]
