@@ -10,8 +10,9 @@
 // launches, and small tiles (40 rows x 8 columns, 8 wavefronts) keep the
 // serial work of a workgroup short: the halo of 12 cells is recomputed by the
 // neighbours, work that the idle compute units have room for.  Measured,
-// 1500 steps: 6.0 ms with two steps per launch, 2.8 ms with four; the launch
-// takes 7 us, of which about 2 us are arithmetic.
+// 1500 steps: 6.0 ms with two steps per launch, 2.8 ms with four; a launch
+// takes 7 to 8 us, its vector units busy 14-18 % and its wavefronts waiting for
+// memory half of their cycles.
 //
 // What a launch waits for is a chain of loads, so nothing with an address
 // known from the arguments waits behind something else: the list ranges and

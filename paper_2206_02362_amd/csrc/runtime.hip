@@ -21,6 +21,7 @@
 #include "line_search.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cmath>
 #include <cstdio>
@@ -59,6 +60,10 @@ struct fwime_ctx {
   std::vector<fwime_tape *> tapes;        // live ones
   void *spare = nullptr;
   size_t spare_bytes = 0;
+  // calls that could keep histories so far, and the last of them that needed
+  // (half of) the arena, the solver's buffer and the spare (see hist_batch)
+  std::atomic<long> calls{0}, spare_use{0};
+  long arena_use = 0, vp_use = 0;
   size_t last_arena_request = 0;
   hipStream_t capture = nullptr;          // private stream used only to record graphs
   std::map<std::string, int> tuned;       // batch signature -> tile width
@@ -218,22 +223,24 @@ size_t live_tape_bytes(const fwime_ctx_t *ctx) {
   return ctx->tape_bytes;
 }
 
-// Frees what the context holds between calls, except the buffer of `owner`:
-// the spare, the solver's buffer and the arena.  Between the input checks of a
+// Frees what the context holds between calls: the spare, the solver's buffer
+// and the arena, except the buffer of `owner`.  Between the input checks of a
 // call, which wait for the stream, and its own use of them they are idle.
-void release_idle(fwime_ctx_t *ctx, void **owner, bool spare = true) {
-  if (spare) release_spare(ctx);
-  if (ctx->vp && !ctx->vp_busy && owner != &ctx->vp) {
-    (void)hipFree(ctx->vp);
-    ctx->vp = nullptr;
-    ctx->vp_bytes = 0;
-  }
-  if (ctx->arena && owner != &ctx->arena) {
-    (void)hipFree(ctx->arena);
-    ctx->arena = nullptr;
-    ctx->arena_bytes = 0;
-    ctx->last_arena_request = 0;         // the next one is as large as it needs to be
-  }
+void release_vp(fwime_ctx_t *ctx) {
+  if (ctx->vp) (void)hipFree(ctx->vp);
+  ctx->vp = nullptr;
+  ctx->vp_bytes = 0;
+}
+void release_arena(fwime_ctx_t *ctx) {
+  if (ctx->arena) (void)hipFree(ctx->arena);
+  ctx->arena = nullptr;
+  ctx->arena_bytes = 0;
+  ctx->last_arena_request = 0;             // the next one is as large as it needs to be
+}
+void release_idle(fwime_ctx_t *ctx, void **owner) {
+  release_spare(ctx);
+  if (!ctx->vp_busy && owner != &ctx->vp) release_vp(ctx);
+  if (owner != &ctx->arena) release_arena(ctx);
 }
 
 // hipMalloc that gives back what is held idle when memory is short
@@ -286,6 +293,7 @@ int arena_get(fwime_ctx_t *ctx, Carve &cv) {
     ctx->arena_bytes = want;
   }
   ctx->last_arena_request = std::max(ctx->last_arena_request, cv.total);
+  if (cv.total >= ctx->arena_bytes / 2) ctx->arena_use = ctx->calls;
   char *p = (char *)ctx->arena;
   for (auto &it : cv.items) {
     *it.first = p;
@@ -1094,10 +1102,14 @@ int seg_len(int nt) {
 // Only a context without a budget does so (one with a budget shares the device
 // by exact footprints), and what it then holds, its arena, the solver's buffer,
 // live tapes and the spare together, stays within a third of the device memory
-// that others leave: live tapes take from that third, and buffers held idle are
-// freed where they stand in its way.  All shots of the call must fit, or at
-// least enough of them that a launch still fills the device.
+// that others leave.  Where a history does not fit beside the others, the call
+// checkpoints: allocating costs about 15 ms a gigabyte, ten times what a
+// gigabyte of history saves a call, so buffers are not freed for one another
+// from call to call.  One that the last kIdleCalls calls did without is.
+// All shots of the call must fit, or at least enough of them that a launch
+// still fills the device.
 // ---------------------------------------------------------------------------
+constexpr long kIdleCalls = 16;
 constexpr long kHistSlots = 1024;       // time slots (shots x steps) of a segment
 // Two-step workgroups of a batch from which histories in several batches are
 // taken rather than checkpoints in one, which fill the device better.  Measured,
@@ -1131,30 +1143,37 @@ long hist_parts(int nt, int K, long img) {
 
 // Shots per batch that keep whole histories (0: checkpoint instead).
 // bytes(S): what the call holds for a batch of S shots; owner: the buffer that
-// it is held in (null: a tape of its own).
+// the history is held in (null: a tape of its own); in_arena: how much of all
+// shots' is in the arena, with another owner.
 template <class Bytes>
-int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, void **owner) {
+int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, void **owner, size_t in_arena = 0) {
   if (ctx->fixed || ctx->budget || ctx->frugal) return 0;
   size_t avail = 0, total = 0;
   if (hipMemGetInfo(&avail, &total) != hipSuccess) return 0;
+  if (!ctx->vp_busy) ++ctx->calls;                 // (the solver's calls are part of one)
   const size_t tapes = live_tape_bytes(ctx), spare = spare_bytes(ctx);
   const size_t third = (avail + ctx->arena_bytes + ctx->vp_bytes + spare + tapes) / 3;
-  const size_t in_use = tapes + (ctx->vp_busy ? ctx->vp_bytes : 0);
-  const size_t cap = third > in_use ? third - in_use : 0;
+  // buffers beside the call's own (a tape takes the spare, a small one leaves it alone)
+  const bool own_spare = !owner && bytes(nshots) >= spare / 4;
+  const size_t idle[3] = {own_spare ? 0 : spare, owner == &ctx->vp || ctx->vp_busy ? 0 : ctx->vp_bytes,
+                          owner == &ctx->arena ? 0 : ctx->arena_bytes - std::min(ctx->arena_bytes, in_arena)};
+  const long now = ctx->calls, use[3] = {ctx->spare_use, ctx->vp_use, ctx->arena_use};
+  size_t held = tapes + (ctx->vp_busy ? ctx->vp_bytes : 0), old = 0;
+  for (int i = 0; i < 3; ++i) (now - use[i] > kIdleCalls ? old : held) += idle[i];
+  const size_t cap = third > held ? third - held : 0;
   int S = nshots;
   if (bytes(nshots) > cap) {
-    int lo = 0, hi = nshots;                     // largest S with bytes(S) <= cap
+    int lo = 0, hi = nshots;                       // largest S with bytes(S) <= cap
     while (hi - lo > 1) {
       const int mid = (lo + hi) / 2;
       (bytes(mid) <= cap ? lo : hi) = mid;
     }
     S = lo * tiles_per_shot >= kHistMinTiles ? lo : 0;
   }
-  if (S == 0) return 0;
-  const bool take_spare = !owner && bytes(S) >= spare / 4;   // (a small tape leaves it alone)
-  const size_t idle = (take_spare ? 0 : spare) + (owner != &ctx->vp && !ctx->vp_busy ? ctx->vp_bytes : 0) +
-                      (owner != &ctx->arena ? ctx->arena_bytes : 0);
-  if (bytes(S) + idle > cap) release_idle(ctx, owner, !take_spare);
+  if (S > 0 && bytes(S) + old > cap)
+    for (int i = 0; i < 3; ++i)
+      if (idle[i] && now - use[i] > kIdleCalls)
+        (i == 0 ? release_spare : i == 1 ? release_vp : release_arena)(ctx);
   return S;
 }
 
@@ -2274,12 +2293,14 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
     use_cache = need < (size_t)((avail + ctx->vp_bytes + spare_bytes(ctx)) * 0.5) && (!ctx->budget || need < ctx->budget / 2);
   }
   const long hist_elems = (g->nt - 1L) * dd.field * geo->nshots;
-  const bool use_hist = use_cache && hist_batch(ctx, geo->nshots, 0, [&](int S) {
-    // beside it, at the same time: the rings and chunks of B~ and B~*
+  // beside it, at the same time: the rings and chunks of B~ and B~*
+  auto beside = [&](int S) {
     const int K = hist_seg_len(g->nt, S);
-    return ((g->nt - 1L + 16 + 2 * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + (size_t)img * (24 + 4 * hist_parts(g->nt, K, img)) +
-           (size_t)ndata * 8;
-  }, &ctx->vp) > 0;
+    return ((16 + 2L * (K + 2)) * dd.field * 4 + geo->nrec * 64L) * S + img * (8 + 4 * hist_parts(g->nt, K, img));
+  };
+  const bool use_hist = use_cache && hist_batch(ctx, geo->nshots, 0, [&](int S) {
+    return (size_t)(beside(S) + (g->nt - 1L) * dd.field * 4 * S + img * 16 + ndata * 8);
+  }, &ctx->vp, (size_t)beside(geo->nshots)) > 0;
   // solver vectors, kept in the context between calls
   float *r = nullptr, *sdir = nullptr, *q = nullptr, *b = nullptr, *dres = nullptr, *dtmp = nullptr,
         *e2d2 = nullptr;
@@ -2325,6 +2346,7 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
     ctx->vp_bytes = cv.total;
   }
   cv.assign(ctx->vp);
+  if (cv.total >= ctx->vp_bytes / 2) ctx->vp_use = ctx->calls;
   // the operators below size their shot batches from what is left of the budget
   struct Guard {
     fwime_ctx_t *c;
@@ -2651,6 +2673,7 @@ void fwime_tape_free(fwime_tape_t *tape) {
         drop = ctx->spare;
         ctx->spare = tape->mem;
         ctx->spare_bytes = tape->capacity;
+        ctx->spare_use = ctx->calls.load();
       }
     }
     if (drop) (void)hipFree(drop);
@@ -2687,11 +2710,14 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   // fields in the arena
   const size_t rest = 2 * nrt * 4 + (size_t)geo->nrec * 64;
   // whole histories only if every shot's fit (the tape holds them all)
-  const int Sh = hist_batch(ctx, geo->nshots, 0, [&](int S) {
+  auto beside = [&](int S) {                       // in the arena
     const GradPlan p = grad_plan(d, g->nt, S);
-    return (grad_work_per_shot(d, p, ctx->two_step) + rest) * S + (size_t)d.field * 8 +
+    return (grad_work_per_shot(d, p, ctx->two_step) - 2L * p.seg_stride * 4 + rest) * S +
            (size_t)img * 4 * (5 + hist_parts(g->nt, p.K, img));
-  }, nullptr);
+  };
+  const int Sh = hist_batch(ctx, geo->nshots, 0, [&](int S) {
+    return beside(S) + (size_t)(2L * (g->nt - 1) * S + 2) * d.field * 4;
+  }, nullptr, beside(geo->nshots));
   tp->pl = grad_plan(d, g->nt, Sh);
   const GradPlan &pl = tp->pl;
   const size_t per_shot = grad_work_per_shot(d, pl, ctx->two_step) + rest;
