@@ -1309,7 +1309,8 @@ hipError_t launch_tau_image(const float *in, long in_slot, long in_sstride, cons
 // loaded together before the first is used.  A segment's products are summed in
 // the order of shots, then steps, and segments are added from the last to the
 // first: the bits are those of one launch per checkpointed segment, and no
-// FP32 chain is longer than that segment's.
+// FP32 chain is longer than that segment's.  Which product is fused is spelled
+// out: the compiler's choice changes with the unrolling.
 // ---------------------------------------------------------------------------
 constexpr int kAccumLoads = 8;
 
@@ -1342,11 +1343,11 @@ __global__ void k_grad_accum(const float *t2u, const float *t2d, long slot, long
           rr = rr + 1 == rho_ring ? 0 : rr + 1;
         }
 #pragma unroll
-        for (int k = 0; k < kAccumLoads; ++k) g += (u[k] + d[k]) * l[k] + u[k] * r[k];
+        for (int k = 0; k < kAccumLoads; ++k) g += fmaf(u[k] + d[k], l[k], u[k] * r[k]);
       }
       for (; n < n1; ++n) {
         const float u = pu[(long)n * slot], d = pd[(long)n * slot];
-        g += (u + d) * pl[(long)rl * ring_slot] + u * pr[(long)rr * rho_slot];
+        g += fmaf(u + d, pl[(long)rl * ring_slot], u * pr[(long)rr * rho_slot]);
         rl = rl + 1 == ring ? 0 : rl + 1;
         rr = rr + 1 == rho_ring ? 0 : rr + 1;
       }
