@@ -93,8 +93,9 @@ typedef struct fwime_ctx fwime_ctx_t;
  * buffers, checkpoints, geometry tables) and never allocates beyond
  * `hbm_budget_bytes` (0 = no limit besides the device).  A context without a
  * budget keeps wavefield histories instead of recomputing them as long as what
- * it then holds (its arena, the solver's buffer, live tapes and the memory kept
- * of freed ones) stays within a third of the device memory that others leave;
+ * it then holds for them (in its arena, the solver's buffer, live tapes and the
+ * memory kept of freed ones) stays within a third of the device memory that
+ * others leave, and within half of what is free or the call's own;
  * one with a budget does not.  Returns FWIME_OK and sets *out, or an error
  * code. */
 int fwime_ctx_create(int device, size_t hbm_budget_bytes, fwime_ctx_t **out);

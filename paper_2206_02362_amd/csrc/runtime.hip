@@ -47,6 +47,8 @@ struct fwime_ctx {
   int steps = 0;                // 2 or 4: steps per launch whatever the size (0: chosen by size)
   bool frugal = false;          // a call that did not fit runs again with less scratch (see or_frugally)
   size_t tape_bytes = 0;        // device memory held by live tapes
+  // memory held for histories: of live tapes, the arena and the solver's buffer
+  size_t tape_hist = 0, arena_hist = 0, vp_hist = 0;
   // memory of the largest tape freed so far, for the next one: a tape of whole
   // histories is up to gigabytes, allocated and released on every call else
   // (data and gradient through autograd on 100 x 200, one shot, a tape of
@@ -55,13 +57,13 @@ struct fwime_ctx {
   // back when one of the context's allocations fails or a history needs the
   // room, by fwime_ctx_trim and with the context.
   // Tapes are freed on any thread, and after their context if need be: tape_mu
-  // guards tape_bytes, tapes, spare and spare_bytes.
+  // guards tape_bytes, tape_hist, tapes, spare and spare_bytes.
   mutable std::mutex tape_mu;
   std::vector<fwime_tape *> tapes;        // live ones
   void *spare = nullptr;
   size_t spare_bytes = 0;
-  // calls that could keep histories so far, and the last of them that needed
-  // (half of) the arena, the solver's buffer and the spare (see hist_batch)
+  // calls that could keep histories so far, and the last of them that kept one
+  // in the arena, in the solver's buffer and in the spare (see hist_batch)
   std::atomic<long> calls{0}, spare_use{0};
   long arena_use = 0, vp_use = 0;
   size_t last_arena_request = 0;
@@ -218,6 +220,11 @@ size_t spare_bytes(fwime_ctx_t *ctx) {
   return ctx->spare_bytes;
 }
 
+size_t tape_hist_bytes(const fwime_ctx_t *ctx) {
+  std::lock_guard<std::mutex> lock(ctx->tape_mu);
+  return ctx->tape_hist;
+}
+
 size_t live_tape_bytes(const fwime_ctx_t *ctx) {
   std::lock_guard<std::mutex> lock(ctx->tape_mu);
   return ctx->tape_bytes;
@@ -229,12 +236,12 @@ size_t live_tape_bytes(const fwime_ctx_t *ctx) {
 void release_vp(fwime_ctx_t *ctx) {
   if (ctx->vp) (void)hipFree(ctx->vp);
   ctx->vp = nullptr;
-  ctx->vp_bytes = 0;
+  ctx->vp_bytes = ctx->vp_hist = 0;
 }
 void release_arena(fwime_ctx_t *ctx) {
   if (ctx->arena) (void)hipFree(ctx->arena);
   ctx->arena = nullptr;
-  ctx->arena_bytes = 0;
+  ctx->arena_bytes = ctx->arena_hist = 0;
   ctx->last_arena_request = 0;             // the next one is as large as it needs to be
 }
 void release_idle(fwime_ctx_t *ctx, void **owner) {
@@ -293,7 +300,6 @@ int arena_get(fwime_ctx_t *ctx, Carve &cv) {
     ctx->arena_bytes = want;
   }
   ctx->last_arena_request = std::max(ctx->last_arena_request, cv.total);
-  if (cv.total >= ctx->arena_bytes / 2) ctx->arena_use = ctx->calls;
   char *p = (char *)ctx->arena;
   for (auto &it : cv.items) {
     *it.first = p;
@@ -1100,14 +1106,14 @@ int seg_len(int nt) {
 // them, so a result has the same bits with histories and with checkpoints.
 //
 // Only a context without a budget does so (one with a budget shares the device
-// by exact footprints), and what it then holds, its arena, the solver's buffer,
-// live tapes and the spare together, stays within a third of the device memory
-// that others leave.  Where a history does not fit beside the others, the call
-// checkpoints: allocating costs about 15 ms a gigabyte, ten times what a
-// gigabyte of history saves a call, so buffers are not freed for one another
-// from call to call.  One that the last kIdleCalls calls did without is.
-// All shots of the call must fit, or at least enough of them that a launch
-// still fills the device.
+// by exact footprints), and what it then holds for histories, in its arena, the
+// solver's buffer, live tapes and the spare together, stays within a third of
+// the device memory that others leave.  Where a history does not fit beside the
+// others, the call checkpoints: allocating costs about 15 ms a gigabyte, ten
+// times what a gigabyte of history saves a call, so buffers are not freed for
+// one another from call to call.  One that the last kIdleCalls calls did
+// without is.  All shots of the call must fit, or at least enough of them that a
+// launch still fills the device.
 // ---------------------------------------------------------------------------
 constexpr long kIdleCalls = 16;
 // Time slots (shots x steps) of a segment.  Measured, ms, with one checkpointed
@@ -1156,16 +1162,20 @@ int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, v
   size_t avail = 0, total = 0;
   if (hipMemGetInfo(&avail, &total) != hipSuccess) return 0;
   if (!ctx->vp_busy) ++ctx->calls;                 // (the solver's calls are part of one)
-  const size_t tapes = live_tape_bytes(ctx), spare = spare_bytes(ctx);
-  const size_t third = (avail + ctx->arena_bytes + ctx->vp_bytes + spare + tapes) / 3;
-  // buffers beside the call's own (a tape takes the spare, a small one leaves it alone)
+  const size_t tapes = tape_hist_bytes(ctx), spare = spare_bytes(ctx);
+  const size_t third = (avail + ctx->arena_bytes + ctx->vp_bytes + spare + live_tape_bytes(ctx)) / 3;
+  // held for histories beside the call's own buffer (a tape takes the spare, a
+  // small one leaves it alone), what is free or the call's own, and what of
+  // the former the last calls did without
   const bool own_spare = !owner && bytes(nshots) >= spare / 4;
-  const size_t idle[3] = {own_spare ? 0 : spare, owner == &ctx->vp || ctx->vp_busy ? 0 : ctx->vp_bytes,
-                          owner == &ctx->arena ? 0 : ctx->arena_bytes - std::min(ctx->arena_bytes, in_arena)};
+  const size_t arena = std::min(ctx->arena_bytes, owner == &ctx->arena ? ctx->arena_bytes : in_arena);
+  const size_t idle[3] = {own_spare ? 0 : spare, owner == &ctx->vp || ctx->vp_busy ? 0 : ctx->vp_hist,
+                          owner == &ctx->arena ? 0 : std::min(ctx->arena_hist, ctx->arena_bytes - arena)};
   const long now = ctx->calls, use[3] = {ctx->spare_use, ctx->vp_use, ctx->arena_use};
-  size_t held = tapes + (ctx->vp_busy ? ctx->vp_bytes : 0), old = 0;
+  size_t held = tapes + (ctx->vp_busy ? ctx->vp_hist : 0), old = 0;
   for (int i = 0; i < 3; ++i) (now - use[i] > kIdleCalls ? old : held) += idle[i];
-  const size_t cap = third > held ? third - held : 0;
+  const size_t open = avail + old + arena + (owner == &ctx->vp ? ctx->vp_bytes : 0) + (own_spare ? spare : 0);
+  const size_t cap = std::min(third > held ? third - held : 0, open / 2);   // half of it is left alone
   int S = nshots;
   if (bytes(nshots) > cap) {
     int lo = 0, hi = nshots;                       // largest S with bytes(S) <= cap
@@ -1179,6 +1189,10 @@ int hist_batch(fwime_ctx_t *ctx, int nshots, long tiles_per_shot, Bytes bytes, v
     for (int i = 0; i < 3; ++i)
       if (idle[i] && now - use[i] > kIdleCalls)
         (i == 0 ? release_spare : i == 1 ? release_vp : release_arena)(ctx);
+  if (S > 0 && owner == &ctx->arena) {
+    ctx->arena_hist = std::max(ctx->arena_hist, bytes(S));
+    if (!ctx->vp_busy) ctx->arena_use = now;
+  }
   return S;
 }
 
@@ -1275,11 +1289,10 @@ int fwime_ctx_trim(fwime_ctx_t *ctx, void *stream) {
   release_graph(ctx);
   if (ctx->arena && hipFree(ctx->arena) != hipSuccess) return FWIME_EHIP;
   ctx->arena = nullptr;
-  ctx->arena_bytes = 0;
-  ctx->last_arena_request = 0;
+  release_arena(ctx);
   if (ctx->vp && hipFree(ctx->vp) != hipSuccess) return FWIME_EHIP;
   ctx->vp = nullptr;
-  ctx->vp_bytes = 0;
+  release_vp(ctx);
   release_spare(ctx);
   return FWIME_OK;
 }
@@ -2334,9 +2347,7 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
   Carve cv = layout(use_hist);
   if (cv.total > ctx->vp_bytes) {
     HIPCHK(hipStreamSynchronize(st));
-    if (ctx->vp) HIPCHK(hipFree(ctx->vp));
-    ctx->vp = nullptr;
-    ctx->vp_bytes = 0;
+    release_vp(ctx);
     hipError_t e = device_alloc(ctx, &ctx->vp, cv.total);
     if (e != hipSuccess && use_hist) {             // checkpoints, then
       (void)hipGetLastError();
@@ -2351,7 +2362,10 @@ static int vp_solve_run(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *ve
     ctx->vp_bytes = cv.total;
   }
   cv.assign(ctx->vp);
-  if (cv.total >= ctx->vp_bytes / 2) ctx->vp_use = ctx->calls;
+  if (cache.hist) {
+    ctx->vp_hist = cv.total;
+    ctx->vp_use = ctx->calls;
+  }
   // the operators below size their shot batches from what is left of the budget
   struct Guard {
     fwime_ctx_t *c;
@@ -2673,6 +2687,7 @@ void fwime_tape_free(fwime_tape_t *tape) {
     if (fwime_ctx_t *ctx = tape->ctx) {
       std::lock_guard<std::mutex> lock(ctx->tape_mu);
       ctx->tape_bytes -= tape->bytes;
+      if (tape->pl.hist) ctx->tape_hist -= tape->bytes;
       ctx->tapes.erase(std::find(ctx->tapes.begin(), ctx->tapes.end(), tape));
       if (!ctx->budget && tape->capacity > ctx->spare_bytes) {   // idle on every stream: kept
         drop = ctx->spare;
@@ -2773,6 +2788,7 @@ int fwime_forward_tape(fwime_ctx_t *ctx, const fwime_grid_t *g, const float *vel
   {
     std::lock_guard<std::mutex> lock(ctx->tape_mu);
     ctx->tape_bytes += tc.total;
+    if (pl.hist) ctx->tape_hist += tc.total;
     ctx->tapes.push_back(tp);
   }
   {

@@ -263,3 +263,32 @@ assert min(sizes) > 60
 print(f.allocations - before)
 """
     assert fake(code) == ["0", "0"]
+
+
+def test_large_scratch_is_not_freed_for_a_history(fake):
+    """A modeling call that fills the device with shots in flight, and autograd steps in turn with it: the tape checkpoints
+    instead of taking the arena's place, and nothing is allocated after the first round.  Scratch that leaves room does not
+    count against the third."""
+    code = """
+f = Fake(size=72 * GiB)
+many, large = f.problem(300, 1700, 20, 4800, 60, np.arange(4)), f.problem(300, 1700, 800, 2, 60)
+few = f.problem(300, 1700, 20, 1500, 60, np.arange(4))
+def tape():
+    rc, t = f.forward(large, 11)
+    n = f.info().tape_bytes / GiB
+    assert (rc, f.backward(t)) == (0, 0)
+    f.free(t)
+    return n
+assert f.model(many) == 0 and f.used > 50 * GiB
+for i in range(3):
+    before = f.allocations
+    assert tape() < 4 and f.model(many) == 0
+print(f.allocations - before)
+f.trim()
+assert f.model(few) == 0 and f.used > 18 * GiB
+for i in range(3):
+    before = f.allocations
+    assert tape() > 9 and f.model(few) == 0
+print(f.allocations - before)
+"""
+    assert fake(code) == ["0", "0"]
